@@ -53,7 +53,7 @@ Workspace caller_workspace(void *p, size_t bytes) {
 
 // the exact path of steps_cyl_forces_ex (validated arguments)
 size_t exact_bytes(int64_t N, int n_img, bool all_targets, int64_t n_targets, int mode, bool pot) {
-    if (mode == STEPS_SUM_PAIRWISE) return pairwise_bytes(N, n_img, nullptr, 0, pot);
+    if (mode == STEPS_SUM_PAIRWISE) return pairwise_bytes(N);
     return exact_per_target_bytes(N, all_targets ? N : n_targets);
 }
 
@@ -142,7 +142,7 @@ STEPS_API int steps_cyl_forces(const double *pos, const double *mass, const doub
     if (rc) return rc;
     if ((rc = require_device())) return rc;
     clear_error();
-    return with_stream_workspace(pairwise_bytes(N, n_img, nullptr, 0, out_pot != nullptr), stream,
+    return with_stream_workspace(pairwise_bytes(N), stream,
                                  [&](Workspace &ws) {
                                      return launch_forces_pairwise(pos, mass, eps, N, L, n_img, nullptr, 0,
                                                                    out_acc, out_pot, ws, stream);

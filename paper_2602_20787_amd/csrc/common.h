@@ -81,14 +81,11 @@ int check_workspace(const Workspace &ws, size_t need);
 // unordered pair once, exact images |n| <= n_img, or with a table (non-null)
 // images |n| <= 1 plus its far images (order 1 CIC, 2 TSC).  Arguments are
 // validated by the caller; pairwise_bytes() is the workspace it takes.
-// s_cap > 0 caps the parts per group (S, a power of two up to 16), which
-// sets the sum slots (2S per particle); pairwise_bytes_S() is the workspace
-// with S parts per group.
-size_t pairwise_bytes(int64_t N, int n_img, const steps_cyl_table *table, int order, bool pot);
-size_t pairwise_bytes_S(int64_t N, int S);
+// slot_budget > 0 bounds the bytes of its FP64 sum slots.
+size_t pairwise_bytes(int64_t N, size_t slot_budget = 0);
 int launch_forces_pairwise(const double *pos, const double *mass, const double *eps, int64_t N, double L,
                            int n_img, const steps_cyl_table *table, int order, float *out_acc, float *out_pot,
-                           Workspace &ws, hipStream_t stream, int s_cap = 0);
+                           Workspace &ws, hipStream_t stream, size_t slot_budget = 0);
 
 // The learned correction's pairwise path for all N particles
 // (forces_learned.hip); arguments validated by the caller.

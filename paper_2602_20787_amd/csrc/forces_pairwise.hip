@@ -10,32 +10,41 @@
 // pair once halves the arithmetic of the per-target kernels
 // (forces_exact.hip, table.hip).
 //
-// Layout.  The particles are put in spatial (Morton) order and staged as
-// 32-byte records {x, y, z wrapped, m, h}, with a bounding box per run of 64
-// records.  A part is 64 kR consecutive records (kR = 1 particle per lane);
-// a group is S parts (S = 16 up to 2^21 particles, else 8; 8 with a table).
-// Each particle has 2S slots of FP64 sums (x, y, z, potential).
+// Layout.  The particles are put in spatial (Morton) order (above kSortMin;
+// fewer keep their own order) and staged as 32-byte records {x, y, z wrapped,
+// m, h}, with a bounding box per run of 64 records.  A part is 64 consecutive
+// records, a group S parts.  Each particle has M sets of S slots of FP64 sums
+// (x, y, z, potential).
 //
-// Schedule (bitwise deterministic, no atomics).  A first launch pairs every
-// group with itself (one-sided, every ordered pair, the self pair skipped)
-// and initialises the slots.  Then G' - 1 launches (G' = G rounded up to
-// even) follow a round-robin tournament: in round r group G'-1 meets group
-// r and, for k = 1 .. G'/2 - 1, group (r + k) mod (G'-1) meets group
-// (r - k) mod (G'-1), so every unordered pair of groups meets exactly once
-// and no group appears twice in a round.  A meeting of groups a and b takes
-// S^2 workgroups of one wave: workgroup (i, j) holds part i of a in
-// registers and streams part j of b, adding a's sums into slot j of part i
-// and b's reactions into slot S + i of part j.  Within a launch each slot
-// has one writer, so every sum is a plain read-modify-write in an order
-// fixed by (N, S).  A last pass adds the slots in order and writes FP32
-// outputs at the particles' own positions.
+// Schedule (bitwise deterministic, no atomics).  G groups meet in G' rounds
+// (G' = G rounded up to even): in round 0 every group meets itself, and
+// rounds 1 .. G'-1 are a round-robin tournament: in round r + 1 group G'-1
+// meets group r and, for k = 1 .. G'/2 - 1, group (r + k) mod (G'-1) meets
+// group (r - k) mod (G'-1), so every unordered pair of groups meets exactly
+// once and no group appears twice in a round.  A meeting of groups a and b
+// takes S^2 tiles: tile (i, j) holds part i of a in registers and streams
+// part j of b, adding a's sums into slot j of part i and b's reactions into
+// slot i of part j.  A group meets itself in the S (S + 1)/2 tiles i <= j;
+// tile (i, i) is one-sided and adds to slot i alone.  So within a round each
+// slot has one writer.  A launch runs up to M rounds, each in a slot set of
+// its own; the first launch writes its sets (zeros where a partner is
+// missing), later ones add to them in launch order.  A last pass adds the
+// slots in order and writes FP32 outputs at the particles' own positions.
 //
-// Workgroup.  One wave owns its part, kR particles per lane, in registers;
-// the part's sources come through LDS as kR sub-tiles of 64: at step s lane
-// l takes source (l + s) mod 64 of the sub-tile, so no two lanes meet the
-// same source at once.  The reaction on a source is summed in FP64 in an
-// LDS slot that the lanes update in turn (64 steps visit every lane).  A
-// sub-tile whose bounding box is far from the wave's (no pair closer than
+// What bounds a call is the number of waves in flight: a wave alone takes 37
+// us for its 64 steps at |n| <= 8 where five on its SIMD take 15 us each, and
+// every launch ends in a tail of half-empty SIMDs.  So as many rounds share a
+// launch as the slots' memory allows (kSlotBytes), up to one launch of one
+// group of all parts (flat: S = P, every slot written once), and where even
+// that has too few tiles each is split over Q waves of 64/Q sources.
+//
+// Workgroup.  One wave owns its part, one particle per lane, in registers;
+// the tile's sources come through LDS: at step s lane l takes source l xor s,
+// so no two lanes meet the same source at once.  The reaction on a source is
+// summed in FP64 in an LDS slot that the lanes update in turn (64 steps visit
+// every lane).  A tile of n = 64/Q sources holds them Q times over and takes n
+// steps; the Q reactions on a source are added at the end.  A
+// tile whose sources' box is far from the wave's (no pair closer than
 // the sum of the largest softenings, no axial separation near L/2) skips the
 // softening and half-period screens and the per-pair minimum image; the pair
 // arithmetic is the same either way.  One-wave workgroups need no barrier
@@ -54,26 +63,23 @@ namespace steps {
 namespace {
 
 constexpr int kThreads = 64;  // one wave
-// Particles per lane and waves per SIMD.  The exact pair: one particle per
-// lane in at most 96 VGPRs, 5 waves per SIMD.  Measured per call at
-// N = 2^20, |n| <= 8 with the potential (ms): 1 per lane at 4, 5, 6 and 8
-// waves 1994, 1891, 1895 and 1918; 2 per lane at 2 and 3 waves 2067 and
-// 2110; 4 per lane at 2 waves (256 VGPRs) 2182.  The extra VALU work of
-// one particle per lane (139 instructions per pair in the far loop against
-// 134.5 with four, for the reaction's LDS update and the loop) costs less
-// than the latency the extra waves hide.  With a table, one per lane and a
-// bound of 4 waves (80-83 VGPRs, so 5-6 waves fit): CIC 1436 and TSC 2042 ms,
-// against 1473 and 2200 with 2 per lane at 3 waves and 1441 and 2075 with
-// the bound at 6 waves.
-constexpr int particles_per_thread(int) { return 1; }
+constexpr int kPart = 64;     // particles per part, one per lane
+constexpr int kBox = 8;       // doubles per 64-record box
+// Waves per SIMD.  Measured per call at N = 2^20, |n| <= 8 with the potential
+// (ms) with one launch per round: 1 particle per lane at 4, 5, 6 and 8 waves
+// 1994, 1891, 1895 and 1918; 2 per lane at 2 and 3 waves 2067 and 2110; 4 per
+// lane at 2 waves (256 VGPRs) 2182.  The extra VALU work of one particle per
+// lane (139 instructions per pair in the far loop against 134.5 with four, for
+// the reaction's LDS update and the loop) costs less than the latency the
+// extra waves hide.  With a table a bound of 4 waves (80-83 VGPRs, so 5-6
+// waves fit): CIC 1436 and TSC 2042 ms, against 1473 and 2200 with 2 per lane
+// at 3 waves and 1441 and 2075 with the bound at 6 waves.
 constexpr int waves_per_simd(int torder) { return torder > 0 ? 4 : 5; }
-constexpr int kSub = 64;    // sources per sub-tile (one rotation)
-constexpr int kBox = 8;     // doubles per 64-record box
 
 struct PairwiseArgs {
     const SrcRec *rec;   // [N] records in spatial order
     const double *box;   // [ceil(N/64)][8] bounding boxes of aligned runs of 64 records
-    double *sum;         // [2S][4][N] FP64 sums in spatial order (x, y, z, potential)
+    double *sum;         // [M S Q][4][N] FP64 sums in spatial order (x, y, z, potential)
     double L, invL, halfL, tie;  // tie: |d| within this of L/2 takes the check
     double far_h;                // largest softening sum for which the fast path is allowed
     float tie32;                 // FP32 screen for it: 0.5 L (1 - 1e-6), below every such |d|
@@ -81,8 +87,10 @@ struct PairwiseArgs {
     TableView tv;  // far-image table (table paths only)
     float invLf, invL2f;
     int N, G, Gp;  // particles, groups, groups rounded up to even
-    int S;         // parts per group (1, 2, 4, 8 or 16)
-    int round;     // tournament round (launches of the meetings)
+    int S, Q;      // parts per group, waves per tile (Q > 1: one group only)
+    int round;     // first round of this launch (0: the groups' own meetings)
+    int first;     // the slots are written, not added to
+    unsigned own;  // workgroups of round 0 in this launch
 };
 
 // Exact band 2 <= |n| <= n_far of one pair in one lane (delta = d/L signed,
@@ -104,29 +112,24 @@ __device__ __noinline__ void band_serial(float delta, float r, int n_far, float 
     fr = sr;
 }
 
-__global__ void stage_kernel(const double *pos, const double *mass, const double *eps, int N, double L,
-                             const int *perm, SrcRec *rec) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const int p = perm[k];
-    SrcRec r;
-    r.x = pos[p];
-    r.y = pos[N + p];
-    r.z = wrap_z(pos[2 * N + p], L);
-    r.m = (float)mass[p];
-    r.h = (float)eps[p];
-    rec[k] = r;
-}
-
-// Bounding box {x_lo, x_hi, y_lo, y_hi, z_lo, z_hi, h_max, 0} of the records
-// 64b .. 64b+63 (those below N); one wave per box.
-__global__ void box_kernel(const SrcRec *rec, int N, double *box) {
+// Records in the order of `perm` (null: the particles' own) and the bounding
+// box {x_lo, x_hi, y_lo, y_hi, z_lo, z_hi, h_max, 0} of every aligned run of
+// 64; one wave per run.
+__global__ __launch_bounds__(256) void stage_kernel(const double *pos, const double *mass, const double *eps, int N,
+                                                    double L, const int *perm, SrcRec *rec, double *box) {
     const int b = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
     const int64_t k = (int64_t)b * 64 + (threadIdx.x & 63);
     if ((int64_t)b * 64 >= N) return;  // whole wave leaves together
     double v[7];
     if (k < N) {
-        const SrcRec r = rec[k];
+        const int64_t p = perm ? perm[k] : k;
+        SrcRec r;
+        r.x = pos[p];
+        r.y = pos[N + p];
+        r.z = wrap_z(pos[2 * (int64_t)N + p], L);
+        r.m = (float)mass[p];
+        r.h = (float)eps[p];
+        rec[k] = r;
         v[0] = r.x;
         v[1] = -r.x;
         v[2] = r.y;
@@ -156,26 +159,33 @@ __global__ void box_kernel(const SrcRec *rec, int N, double *box) {
     }
 }
 
-__global__ void finish_kernel(const double *sum, int slots, const int *perm, int N, float *ax, float *ay, float *az,
-                              float *pot) {
+// One component of one particle per thread: its slots added in order.  With
+// Q > 1 waves per tile (one group) slot o Q + q is written for every q where
+// the particle's own part p <= o acted, and for q = 0 alone where it reacted.
+__global__ __launch_bounds__(256) void finish_kernel(const double *sum, int slots, int Q, const int *perm, int N,
+                                                     float *ax, float *ay, float *az, float *pot) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = blockIdx.y;
     if (k >= N) return;
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int q = 0; q < slots; ++q)
-        for (int c = 0; c < 4; ++c) s[c] += sum[((int64_t)q * 4 + c) * N + k];
-    const int p = perm[k];
+    const double *p = sum + (int64_t)c * N + k;
+    const int64_t stride = 4 * (int64_t)N;
+    double s = 0.0;
+    int o = 0;
+    if (Q > 1)
+        for (const int part = k / kPart; o < part; ++o) s += p[(int64_t)o * Q * stride];
+#pragma unroll 8
+    for (int q = o * Q; q < slots * Q; ++q) s += p[q * stride];
+    const int64_t i = perm ? perm[k] : k;
     // attraction: a = -sum m_j S (x_i - x_j), potential = -sum m_j / r
-    ax[p] = (float)(-s[0]);
-    ay[p] = (float)(-s[1]);
-    az[p] = (float)(-s[2]);
-    if (pot) pot[p] = (float)(-s[3]);
+    float *out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : pot;
+    out[i] = (float)(-s);
 }
 
-template <int kR>
+// a wave's particle
 struct Owned {
-    double x[kR], y[kR], z[kR];
-    float h[kR], m[kR];
-    int t[kR];  // record index, or N for an empty slot
+    double x, y, z;
+    float h, m;
+    int t;  // record index, or N for an empty lane
 };
 
 struct WaveBox {
@@ -210,12 +220,11 @@ __device__ __forceinline__ bool far_boxes(const PairwiseArgs &a, const WaveBox &
     return gx * gx + gy * gy + gz * gz > hs * hs * (1.0 + 1e-4) + 1e-300;
 }
 
-// LDS of a workgroup: its part's sources (SoA) and their FP64 reaction slots.
-template <int kR>
+// LDS of a workgroup: its tile's sources (SoA) and their FP64 reaction slots.
 struct Stage {
-    double x[64 * kR], y[64 * kR], z[64 * kR];
-    float m[64 * kR], h[64 * kR];
-    double r[4][64 * kR];  // reactions, FP64
+    double x[64], y[64], z[64];
+    float m[64], h[64];
+    double r[4][64];  // reactions, FP64
 };
 
 // Reaction on the source from an evaluated pair, in the owned sums'
@@ -274,167 +283,116 @@ __device__ __forceinline__ void table_far(const PairwiseArgs &a, float dx, float
     Fz = __builtin_fmaf(-Rz, a.invL2f, Fz);
 }
 
-// One wave's rotation over sub-tile s when far_boxes holds (image shift kL):
-// 64 steps, lane l taking source (l + step) mod 64.  The separation is the
-// FP64 difference of the positions, with the minimum image's shift kL taken
-// off the owned z once per sub-tile, rounded to FP32 (as exact as in
-// near_pass, with no per-pair floor).  No softening, no half-period screen.
-// FP32 pair terms, FP64 sums and reactions as in near_pass.
-template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool REACT, int kR>
-__device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned<kR> &o, Stage<kR> &st, int s, double kL,
-                                         double (*acc)[4]) {
+// One wave's passage over a tile's sources when far_boxes holds (image shift
+// kL): n steps, lane l taking source l xor step.  The separation is the FP64
+// difference of the positions, with the minimum image's shift kL taken off
+// the owned z once per tile, rounded to FP32 (as exact as in near_pass, with
+// no per-pair floor).  No softening, no half-period screen.  FP32 pair terms,
+// FP64 sums and reactions as in near_pass.
+template <int NIMG, bool POT, int TORDER, bool COMPLETE>
+__device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, Stage &st, int n, double kL,
+                                         double *acc) {
     const int lane = threadIdx.x & 63;
-    double zs[kR];
-#pragma unroll
-    for (int r = 0; r < kR; ++r) zs[r] = o.z[r] - kL;
-    for (int step = 0; step < kSub; ++step) {
-        const int k = (s << 6) | ((lane + step) & 63);
+    const double zs = o.z - kL;
+    for (int step = 0; step < n; ++step) {
+        const int k = lane ^ step;
         const double sxj = st.x[k], syj = st.y[k], szj = st.z[k];
         const double ms = (double)st.m[k];
         double jx = 0.0, jy = 0.0, jz = 0.0, jp = 0.0;
-        if (REACT && step > 0) {
+        if (step > 0) {
             // the slot as the previous lane left it
             jx = st.r[0][k];
             jy = st.r[1][k];
             jz = st.r[2][k];
             if (POT) jp = st.r[3][k];
         }
-#pragma unroll
-        for (int r = 0; r < kR; ++r) {
-            const double dx64 = o.x[r] - sxj, dy64 = o.y[r] - syj;
-            const float dx = (float)dx64, dy = (float)dy64, d = (float)(zs[r] - szj);
-            float S, Fz, P = 0.f;
-            pair_fast<NIMG, POT>(dx, dy, d, a.c, S, Fz, P);
-            if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, false, S, Fz);
-            const double S64 = (double)S, Fz64 = (double)Fz;
-            const double mS = ms * S64;
-            acc[r][0] = __builtin_fma(mS, dx64, acc[r][0]);
-            acc[r][1] = __builtin_fma(mS, dy64, acc[r][1]);
-            acc[r][2] = __builtin_fma(ms, Fz64, acc[r][2]);
-            if (POT) acc[r][3] = __builtin_fma(ms, (double)P, acc[r][3]);
-            if (REACT) {
-                const double miS = o.m[r] * S64;
-                jx = __builtin_fma(miS, dx64, jx);
-                jy = __builtin_fma(miS, dy64, jy);
-                jz = __builtin_fma(o.m[r], Fz64, jz);
-                if (POT) jp = __builtin_fma(o.m[r], (double)P, jp);
-            }
-        }
-        if (REACT) {
-            st.r[0][k] = jx;
-            st.r[1][k] = jy;
-            st.r[2][k] = jz;
-            if (POT) st.r[3][k] = jp;
-        }
+        const double dx64 = o.x - sxj, dy64 = o.y - syj;
+        const float dx = (float)dx64, dy = (float)dy64, d = (float)(zs - szj);
+        float S, Fz, P = 0.f;
+        pair_fast<NIMG, POT>(dx, dy, d, a.c, S, Fz, P);
+        if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, false, S, Fz);
+        const double S64 = (double)S, Fz64 = (double)Fz;
+        const double mS = ms * S64;
+        acc[0] = __builtin_fma(mS, dx64, acc[0]);
+        acc[1] = __builtin_fma(mS, dy64, acc[1]);
+        acc[2] = __builtin_fma(ms, Fz64, acc[2]);
+        if (POT) acc[3] = __builtin_fma(ms, (double)P, acc[3]);
+        const double miS = o.m * S64;
+        st.r[0][k] = __builtin_fma(miS, dx64, jx);
+        st.r[1][k] = __builtin_fma(miS, dy64, jy);
+        st.r[2][k] = __builtin_fma(o.m, Fz64, jz);
+        if (POT) st.r[3][k] = __builtin_fma(o.m, (double)P, jp);
     }
 }
 
-// One wave's rotation over sub-tile s in general position: FP64 separation
-// and minimum image, then FP32 pair terms and FP64 sums (the records are in
-// spatial order, so a particle's near neighbours arrive together and an FP32
-// partial would lose their cancellation).  The n = 0 image of a pair inside
-// its softening length takes the spline in FP32 (selected per pair; the
-// separation is the FP64 one cast); with a softening sum above L/2 the
-// images n != 0 may be softened too and the pair is evaluated in FP64 with
-// the spline on every image (rare: one pair per lane and pass).  REACT: the
-// sources belong to another group and their reactions are summed in the
-// FP64 LDS slots; otherwise (the group against itself) the self pair is
-// skipped.
-template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool REACT, int kR>
-__device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned<kR> &o, Stage<kR> &st, int s, int base,
-                                          float hmax, double (*acc)[4]) {
+// One wave's passage over a tile's sources in general position: FP64
+// separation and minimum image, then FP32 pair terms and FP64 sums (the
+// records are in spatial order, so a particle's near neighbours arrive
+// together and an FP32 partial would lose their cancellation).  The n = 0
+// image of a pair inside its softening length takes the spline in FP32
+// (selected per pair; the separation is the FP64 one cast); with a softening
+// sum above L/2 the images n != 0 may be softened too and the pair is
+// evaluated in FP64 with the spline on every image (rare).  REACT: the sources
+// are another part's and their reactions are summed in the FP64 LDS slots;
+// otherwise (a part against itself; the tile's first record is `base`, `cnt`
+// of its sources are real) the self pair and the padding are skipped.
+template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool REACT>
+__device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o, Stage &st, int n, int base, int cnt,
+                                          float hmax, double *acc) {
     const int lane = threadIdx.x & 63;
-    float thr2[kR];
-    bool wide[kR];
-#pragma unroll
-    for (int r = 0; r < kR; ++r) {
-        const float hb = o.h[r] + hmax;  // >= h_i + h_j for every source of the sub-tile
-        thr2[r] = hb * hb;
-        wide[r] = hb > (float)a.halfL;
-    }
-    for (int step = 0; step < kSub; ++step) {
-        const int k = (s << 6) | ((lane + step) & 63);
+    const float hb = o.h + hmax;  // >= h_i + h_j for every source of the tile
+    const float thr2 = hb * hb;
+    const bool wide = hb > (float)a.halfL;
+    for (int step = 0; step < n; ++step) {
+        const int k = lane ^ step;
         SrcRec src;
         src.x = st.x[k];
         src.y = st.y[k];
         src.z = st.z[k];
         src.m = st.m[k];
         src.h = st.h[k];
-        double dx64[kR], dy64[kR];
-        float S[kR], Fz[kR], P[kR], dr[kR];
-        bool tie[kR];
-        unsigned soft64 = 0;  // bit r: the pair (r, src) takes the FP64 spline on every image
-#pragma unroll
-        for (int r = 0; r < kR; ++r) {
-            dx64[r] = o.x[r] - src.x;
-            dy64[r] = o.y[r] - src.y;
-            const double d64 = min_image(o.z[r] - src.z, a.L, a.invL);
-            const float dx = (float)dx64[r], dy = (float)dy64[r], d = (float)d64;
-            dr[r] = d;
-            const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
-            const float r2_0 = __builtin_fmaf(d, d, rho2);
-            float T, U, Q;
-            pair_images<NIMG, POT>(rho2, d, r2_0, a.c, T, U, Q);
-            const float hij = o.h[r] + src.h;
-            const bool self = !REACT && base + k == o.t[r];
-            const bool near = (wide[r] || r2_0 < thr2[r]) && (r2_0 < hij * hij || hij > (float)a.halfL);
-            if (near && hij > (float)a.halfL && !self) soft64 |= 1u << r;
-            float s0, p0;
-            if (__ballot(near && !self) != 0) {
-                float sf, pf;
-                spline_n0(r2_0, hij, sf, pf);
-                const float ri0 = __builtin_amdgcn_rsqf(r2_0);
-                s0 = near ? sf : ri0 * ri0 * ri0;
-                p0 = near ? pf : ri0;
-            } else {
-                const float ri0 = __builtin_amdgcn_rsqf(r2_0);
-                s0 = ri0 * ri0 * ri0;
-                p0 = ri0;
-            }
-            S[r] = s0 + T;
-            Fz[r] = __builtin_fmaf(d, S[r], -a.c.Lf * U);
-            P[r] = p0 + Q;
-            if (self) {
-                // j == i: no term at all, images included
-                S[r] = 0.f;
-                Fz[r] = 0.f;
-                P[r] = 0.f;
-            }
-            tie[r] = REACT && __builtin_fabsf(d) >= a.tie32;
+        const int ks = k & (n - 1);  // source of the tile
+        const double dx64 = o.x - src.x, dy64 = o.y - src.y;
+        const double d64 = min_image(o.z - src.z, a.L, a.invL);
+        const float dx = (float)dx64, dy = (float)dy64, d = (float)d64;
+        const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
+        const float r2_0 = __builtin_fmaf(d, d, rho2);
+        float T, U, Pq;
+        pair_images<NIMG, POT>(rho2, d, r2_0, a.c, T, U, Pq);
+        const float hij = o.h + src.h;
+        const bool self = !REACT && (base + ks == o.t || ks >= cnt);
+        const bool near = (wide || r2_0 < thr2) && (r2_0 < hij * hij || hij > (float)a.halfL);
+        float s0, p0;
+        if (__ballot(near && !self) != 0) {
+            float sf, pf;
+            spline_n0(r2_0, hij, sf, pf);
+            const float ri0 = __builtin_amdgcn_rsqf(r2_0);
+            s0 = near ? sf : ri0 * ri0 * ri0;
+            p0 = near ? pf : ri0;
+        } else {
+            const float ri0 = __builtin_amdgcn_rsqf(r2_0);
+            s0 = ri0 * ri0 * ri0;
+            p0 = ri0;
         }
-        while (soft64) {
-            // rare and divergent: one pair per lane and pass, operands picked
-            // by selects so that the spline code exists once
-            const int rr = __builtin_ctz(soft64);
-            soft64 &= soft64 - 1;
-            double xr = o.x[0], yr = o.y[0], zr = o.z[0];
-            float hr = o.h[0];
-#pragma unroll
-            for (int q = 1; q < kR; ++q)
-                if (rr == q) {
-                    xr = o.x[q];
-                    yr = o.y[q];
-                    zr = o.z[q];
-                    hr = o.h[q];
-                }
+        float S = s0 + T;
+        float Fz = __builtin_fmaf(d, S, -a.c.Lf * U);
+        float P = p0 + Pq;
+        if (self) {
+            // j == i: no term at all, images included
+            S = 0.f;
+            Fz = 0.f;
+            P = 0.f;
+        }
+        if (near && hij > (float)a.halfL && !self) {
+            // rare and divergent
             double gs, gf, gp;
-            pair_spline_f64(xr - src.x, yr - src.y, min_image(zr - src.z, a.L, a.invL),
-                            (double)hr + (double)src.h, a.L, (NIMG >= 0) ? NIMG : a.c.n_img, gs, gf, gp);
-#pragma unroll
-            for (int q = 0; q < kR; ++q)
-                if (rr == q) {
-                    S[q] = (float)gs;
-                    Fz[q] = (float)gf;
-                    P[q] = (float)gp;
-                }
+            pair_spline_f64(dx64, dy64, d64, (double)o.h + (double)src.h, a.L, (NIMG >= 0) ? NIMG : a.c.n_img, gs, gf,
+                            gp);
+            S = (float)gs;
+            Fz = (float)gf;
+            P = (float)gp;
         }
-        if (TORDER > 0) {
-#pragma unroll
-            for (int r = 0; r < kR; ++r) {
-                const bool self = !REACT && base + k == o.t[r];
-                table_far<TORDER, COMPLETE>(a, (float)dx64[r], (float)dy64[r], dr[r], self, S[r], Fz[r]);
-            }
-        }
+        if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, self, S, Fz);
         const double ms = (double)src.m;
         double jx = 0.0, jy = 0.0, jz = 0.0, jp = 0.0;
         if (REACT && step > 0) {
@@ -444,185 +402,139 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned<kR>
             jz = st.r[2][k];
             if (POT) jp = st.r[3][k];
         }
-#pragma unroll
-        for (int r = 0; r < kR; ++r) {
-            const double S64 = (double)S[r], Fz64 = (double)Fz[r];
-            const double mS = ms * S64;
-            acc[r][0] = __builtin_fma(mS, dx64[r], acc[r][0]);
-            acc[r][1] = __builtin_fma(mS, dy64[r], acc[r][1]);
-            acc[r][2] = __builtin_fma(ms, Fz64, acc[r][2]);
-            if (POT) acc[r][3] = __builtin_fma(ms, (double)P[r], acc[r][3]);
-            if (REACT) {
-                const double fz = tie[r] ? tie_fz(a, o.z[r], src.z, Fz64) : Fz64;
-                const double miS = o.m[r] * S64;
-                jx = __builtin_fma(miS, dx64[r], jx);
-                jy = __builtin_fma(miS, dy64[r], jy);
-                jz = __builtin_fma(o.m[r], fz, jz);
-                if (POT) jp = __builtin_fma(o.m[r], (double)P[r], jp);
-            }
-        }
+        const double S64 = (double)S, Fz64 = (double)Fz;
+        const double mS = ms * S64;
+        acc[0] = __builtin_fma(mS, dx64, acc[0]);
+        acc[1] = __builtin_fma(mS, dy64, acc[1]);
+        acc[2] = __builtin_fma(ms, Fz64, acc[2]);
+        if (POT) acc[3] = __builtin_fma(ms, (double)P, acc[3]);
         if (REACT) {
-            st.r[0][k] = jx;
-            st.r[1][k] = jy;
-            st.r[2][k] = jz;
-            if (POT) st.r[3][k] = jp;
+            const double fz = __builtin_fabsf(d) >= a.tie32 ? tie_fz(a, o.z, src.z, Fz64) : Fz64;
+            const double miS = o.m * S64;
+            st.r[0][k] = __builtin_fma(miS, dx64, jx);
+            st.r[1][k] = __builtin_fma(miS, dy64, jy);
+            st.r[2][k] = __builtin_fma(o.m, fz, jz);
+            if (POT) st.r[3][k] = __builtin_fma(o.m, (double)P, jp);
         }
     }
 }
 
-// Workgroup (i, j) of one meeting (REACT: the groups of tournament round
-// a.round) or of one group's meeting with itself: part i of group a against
-// part j of group b.
-template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool REACT>
+// One tile: `own` workgroups of round 0 (tiles i <= j of every group, Q waves
+// each), then S^2 per meeting of the launch's other rounds.
+template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairwise_kernel(PairwiseArgs a) {
-    constexpr int kR = particles_per_thread(TORDER);
-    constexpr int kPart = 64 * kR;  // particles per part
-    __shared__ Stage<kR> st;
+    __shared__ Stage st;
     const int lane = threadIdx.x;
-    const int S = a.S;
-    const int meet = blockIdx.x / (S * S);
-    const int pi = (blockIdx.x / S) % S, pj = blockIdx.x % S;
-    int ga = meet, gb = meet;
-    if (REACT) {
+    const int S = a.S, Q = a.Q;
+    int ga, gb, pi, pj, q = 0, set = 0;
+    const bool own = blockIdx.x < a.own;
+    if (own) {
+        const unsigned T = (unsigned)S * (S + 1) / 2;
+        const unsigned tile = blockIdx.x / Q;
+        q = (int)(blockIdx.x % Q);
+        ga = gb = (int)(tile / T);
+        const unsigned t = tile % T;  // column-wise: t = j (j + 1)/2 + i, i <= j
+        pj = (int)((__builtin_sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+        while ((unsigned)(pj + 1) * (pj + 2) / 2 <= t) ++pj;
+        while ((unsigned)pj * (pj + 1) / 2 > t) --pj;
+        pi = (int)(t - (unsigned)pj * (pj + 1) / 2);
+    } else {
+        const unsigned w = blockIdx.x - a.own;
+        const unsigned per = (unsigned)S * S, half = a.Gp / 2;
+        const unsigned meeting = w / per;
+        const int meet = (int)(meeting % half);
+        const int k = (int)(meeting / half);  // rounds of the launch, in order
+        set = k + (a.own ? 1 : 0);
+        const int round = a.round + set - 1;
         const int M = a.Gp - 1;
         if (meet == 0) {
             ga = M;
-            gb = a.round;
+            gb = round;
         } else {
-            ga = (a.round + meet) % M;
-            gb = (a.round - meet + M) % M;
+            ga = (round + meet) % M;
+            gb = (round - meet + M) % M;
         }
-        if (ga >= a.G || gb >= a.G) return;  // the empty group of an odd count
+        pi = (int)((w % per) / S);
+        pj = (int)((w % per) % S);
     }
-    const int64_t g0 = ((int64_t)ga * S + pi) * kPart;  // first owned record
-    if (g0 >= a.N) return;                              // an empty part: nothing owned
-    const int64_t b0 = ((int64_t)gb * S + pj) * kPart;  // first source record
-    const int cnt = (int)max((int64_t)0, min((int64_t)kPart, (int64_t)a.N - b0));
-    if (REACT && cnt == 0) return;                      // no sources: nothing to add
-
-    // the owned particles: records g0 + r*64 + lane; empty slots copy the
-    // part's first record with no mass (they sit where a particle is, so
-    // every pair distance stays that of a real pair)
-    Owned<kR> o;
-#pragma unroll
-    for (int r = 0; r < kR; ++r) {
-        const int64_t t64 = g0 + r * 64 + lane;
-        const bool real = t64 < a.N;
-        const SrcRec rr = a.rec[real ? t64 : g0];
-        o.t[r] = real ? (int)t64 : a.N;
-        o.x[r] = rr.x;
-        o.y[r] = rr.y;
-        o.z[r] = rr.z;
-        o.h[r] = rr.h;
-        o.m[r] = real ? rr.m : 0.f;
-    }
-    // the part's bounding box (every lane ends with it)
-    WaveBox wb;
-    {
-        double v[7] = {o.x[0], -o.x[0], o.y[0], -o.y[0], o.z[0], -o.z[0], (double)o.h[0]};
-#pragma unroll
-        for (int r = 1; r < kR; ++r) {
-            v[0] = fmin(v[0], o.x[r]);
-            v[1] = fmin(v[1], -o.x[r]);
-            v[2] = fmin(v[2], o.y[r]);
-            v[3] = fmin(v[3], -o.y[r]);
-            v[4] = fmin(v[4], o.z[r]);
-            v[5] = fmin(v[5], -o.z[r]);
-            v[6] = fmax(v[6], (double)o.h[r]);
-        }
-        for (int off = 32; off >= 1; off >>= 1) {
-            for (int c = 0; c < 6; ++c) v[c] = fmin(v[c], __shfl_xor(v[c], off));
-            v[6] = fmax(v[6], __shfl_xor(v[6], off));
-        }
-        wb.x0 = v[0];
-        wb.x1 = -v[1];
-        wb.y0 = v[2];
-        wb.y1 = -v[3];
-        wb.z0 = v[4];
-        wb.z1 = -v[5];
-        wb.h = v[6];
-    }
-
-    double acc[kR][4];
-#pragma unroll
-    for (int r = 0; r < kR; ++r)
-        for (int c = 0; c < 4; ++c) acc[r][c] = 0.0;
-
-    // stage the sources; a partly filled sub-tile is padded with massless
-    // copies of its first record (inside its box)
-    const int nsub = (cnt + kSub - 1) / kSub;
-    const int base = (int)b0;  // b0 < N <= 2^29 whenever cnt > 0
-#pragma unroll
-    for (int r = 0; r < kR; ++r) {
-        const int t = r * 64 + lane;
-        if (t < nsub * kSub) {
-            const bool real = t < cnt;
-            const SrcRec rr = a.rec[real ? base + t : base + (t & ~(kSub - 1))];
-            st.x[t] = rr.x;
-            st.y[t] = rr.y;
-            st.z[t] = rr.z;
-            st.m[t] = real ? rr.m : 0.f;
-            st.h[t] = rr.h;
-        }
-    }
-    __syncthreads();
-    for (int s = 0; s < nsub; ++s) {
-        const double *b = a.box + (int64_t)((base >> 6) + s) * kBox;  // base is a multiple of 64
+    const int n = kPart / Q;  // sources of the tile
+    const int64_t g0 = ga < a.G ? ((int64_t)ga * S + pi) * kPart : a.N;               // first owned record
+    const int64_t b0 = gb < a.G ? ((int64_t)gb * S + pj) * kPart + q * n : a.N;       // first source record
+    const int ocnt = (int)max((int64_t)0, min((int64_t)kPart, (int64_t)a.N - g0));    // owned records
+    const int cnt = (int)max((int64_t)0, min((int64_t)n, (int64_t)a.N - b0));         // sources
+    const bool react = !own || pi != pj;
+    // the owned particles' slot and the sources' (whole wave: a null pointer where there are none)
+    double *pa = a.sum + ((int64_t)(set * S + pj) * Q + q) * 4 * a.N + g0 + lane;
+    double *pb = a.sum + (int64_t)(set * S + pi) * Q * 4 * a.N + b0 + lane;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (ocnt > 0 && cnt > 0) {
+        // an empty lane copies the part's first record with no mass (it sits
+        // where a particle is, so every pair distance stays that of a real pair)
+        Owned o;
+        const bool real = lane < ocnt;
+        const SrcRec rr = a.rec[real ? g0 + lane : g0];
+        o.t = real ? (int)g0 + lane : a.N;
+        o.x = rr.x;
+        o.y = rr.y;
+        o.z = rr.z;
+        o.h = rr.h;
+        o.m = real ? rr.m : 0.f;
+        // a partly filled tile is padded with massless copies of its first record
+        const int ks = lane & (n - 1);
+        const bool live = ks < cnt;
+        const SrcRec sr = a.rec[live ? b0 + ks : b0];
+        st.x[lane] = sr.x;
+        st.y[lane] = sr.y;
+        st.z[lane] = sr.z;
+        st.m[lane] = live ? sr.m : 0.f;
+        st.h[lane] = sr.h;
+        const double *w = a.box + (g0 >> 6) * kBox, *b = a.box + (b0 >> 6) * kBox;
+        const WaveBox wb = {w[0], w[1], w[2], w[3], w[4], w[5], w[6]};
+        __syncthreads();
         double kL = 0.0;
-        const bool far = far_boxes(a, wb, b, kL);
-        if (__builtin_amdgcn_readfirstlane((int)far))
-            far_pass<NIMG, POT, TORDER, COMPLETE, REACT>(a, o, st, s, kL, acc);
+        if (!react)
+            near_pass<NIMG, POT, TORDER, COMPLETE, false>(a, o, st, n, (int)b0, cnt, (float)b[6], acc);
+        else if (__builtin_amdgcn_readfirstlane((int)far_boxes(a, wb, b, kL)))
+            far_pass<NIMG, POT, TORDER, COMPLETE>(a, o, st, n, kL, acc);
         else
-            near_pass<NIMG, POT, TORDER, COMPLETE, REACT>(a, o, st, s, base, (float)b[6], acc);
-    }
-    __syncthreads();
-    if (REACT) {
-        // reactions on the sources, in the owned sums' orientation, into
-        // slot S + pi of part pj
+            near_pass<NIMG, POT, TORDER, COMPLETE, true>(a, o, st, n, (int)b0, cnt, (float)b[6], acc);
+        __syncthreads();
+        if (react && lane < cnt) {
+            // reactions on the sources, in the owned sums' orientation
 #pragma unroll
-        for (int r = 0; r < kR; ++r) {
-            const int t = r * 64 + lane;
-            if (t < cnt) {
-                double *p = a.sum + ((int64_t)(S + pi) * 4) * a.N + base + t;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (c == 3 && !POT) continue;
-                    const double v = st.r[c][t];
-                    p[(int64_t)c * a.N] = (c == 3) ? p[(int64_t)c * a.N] + v : p[(int64_t)c * a.N] - v;
-                }
+            for (int c = 0; c < (POT ? 4 : 3); ++c) {
+                double v = st.r[c][lane];
+                for (int e = n; e < kPart; e += n) v += st.r[c][lane + e];
+                if (c < 3) v = -v;
+                pb[(int64_t)c * a.N] = a.first ? v : pb[(int64_t)c * a.N] + v;
             }
         }
+    } else if (a.first && react && lane < cnt) {
+#pragma unroll
+        for (int c = 0; c < (POT ? 4 : 3); ++c) pb[(int64_t)c * a.N] = 0.0;
     }
-    // the owned particles' sums from part pj: slot pj; the self meeting
-    // initialises it and clears the reaction slot S + pj
+    if (lane < ocnt && (a.first || cnt > 0)) {
 #pragma unroll
-    for (int r = 0; r < kR; ++r) {
-        if (o.t[r] < a.N) {
-            double *p = a.sum + (int64_t)pj * 4 * a.N + o.t[r];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (REACT) {
-                    if (c < 3 || POT) p[(int64_t)c * a.N] += acc[r][c];
-                } else {
-                    p[(int64_t)c * a.N] = acc[r][c];
-                    p[((int64_t)S * 4 + c) * a.N] = 0.0;
-                }
-            }
-        }
+        for (int c = 0; c < (POT ? 4 : 3); ++c)
+            pa[(int64_t)c * a.N] = a.first ? acc[c] : pa[(int64_t)c * a.N] + acc[c];
     }
 }
 
 template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 struct Launcher {
-    static hipError_t run(PairwiseArgs a, hipStream_t stream) {
-        const unsigned per_meeting = (unsigned)(a.S * a.S);
-        hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE, false>), dim3(a.G * per_meeting),
-                           dim3(kThreads), 0, stream, a);
-        hipError_t e = hipGetLastError();
-        for (int r = 0; e == hipSuccess && r + 1 < a.Gp; ++r) {
+    static hipError_t run(PairwiseArgs a, int sets, hipStream_t stream) {
+        const int rounds = a.G > 1 ? a.Gp : 1;
+        const int launches = (rounds + sets - 1) / sets;
+        const int each = (rounds + launches - 1) / launches;  // <= sets
+        hipError_t e = hipSuccess;
+        for (int r = 0; e == hipSuccess && r < rounds; r += each) {
+            const int k = std::min(each, rounds - r);
             a.round = r;
-            hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE, true>),
-                               dim3(a.Gp / 2 * per_meeting), dim3(kThreads), 0, stream, a);
+            a.first = r == 0;
+            a.own = r == 0 ? (unsigned)a.G * a.S * (a.S + 1) / 2 * a.Q : 0;
+            const unsigned meet = (unsigned)(k - (r == 0)) * (a.Gp / 2) * a.S * a.S;
+            hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE>), dim3(a.own + meet),
+                               dim3(kThreads), 0, stream, a);
             e = hipGetLastError();
         }
         return e;
@@ -633,13 +545,13 @@ struct Launcher {
 template <class F>
 auto dispatch(int n_img, bool pot, int order, bool complete, F &&f) {
     if (order == 0) {
-        // image counts unrolled at compile time where the unrolled loop fits
-        // the register budget; the others (the compiler spills the unrolled
-        // 1-, 2- and 4-image forms with the potential and the 4-image form
-        // without) take the run-time loop, which fits
+        // image counts unrolled at compile time, the others by the run-time loop
         if (pot) {
             switch (n_img) {
                 case 0: return f(Launcher<0, true, 0, false>{});
+                case 1: return f(Launcher<1, true, 0, false>{});
+                case 2: return f(Launcher<2, true, 0, false>{});
+                case 4: return f(Launcher<4, true, 0, false>{});
                 case 8: return f(Launcher<8, true, 0, false>{});
                 default: return f(Launcher<-1, true, 0, false>{});
             }
@@ -648,6 +560,7 @@ auto dispatch(int n_img, bool pot, int order, bool complete, F &&f) {
             case 0: return f(Launcher<0, false, 0, false>{});
             case 1: return f(Launcher<1, false, 0, false>{});
             case 2: return f(Launcher<2, false, 0, false>{});
+            case 4: return f(Launcher<4, false, 0, false>{});
             case 8: return f(Launcher<8, false, 0, false>{});
             default: return f(Launcher<-1, false, 0, false>{});
         }
@@ -662,26 +575,57 @@ auto dispatch(int n_img, bool pot, int order, bool complete, F &&f) {
 
 }  // namespace
 
-// Parts per group of a pairwise call.  More parts make a launch hold more
-// workgroups at the price of 2 sum slots (64 B) per particle each.  Measured
-// per call at N = 2^20 with parts of 64: S = 16 and 32 took 1891 and 1894 ms
-// (exact), S = 8, 16 and 32 CIC 1441, 1461 and 1464 ms and TSC 2075, 2089
-// and 2085 ms.  Above 2^21 particles a call has enough meetings with S = 8
-// and the slots would grow past 2 GiB.
-int pairwise_parts(int64_t N, const steps_cyl_table *table) {
-    if (table) return 8;
-    return N <= ((int64_t)1 << 21) ? 16 : 8;
+namespace {
+
+// Below this many particles the parts are runs of the particles' own order:
+// what the order saves in near tiles is less than sorting costs.
+constexpr int64_t kSortMin = 6144;
+
+// Bytes of FP64 sum slots of a call.  Up to kScratchN particles the slots (and
+// what else a call takes) fit the 128 MiB array of steps_cyl_forces_noalloc,
+// which then runs the same schedule; above, twice as many rounds share a launch.
+constexpr int64_t kScratchN = 125000;
+constexpr size_t kSlotBytesScratch = (size_t)112 << 20, kSlotBytes = (size_t)256 << 20;
+constexpr size_t kSetBytes = 32;  // per particle and slot
+
+struct Schedule {
+    int S, M, Q;  // parts per group, slot sets, waves per tile
+};
+
+Schedule pairwise_schedule(int64_t N, size_t budget) {
+    Schedule s;
+    const int64_t P = (N + kPart - 1) / kPart;
+    if (budget == 0) budget = N <= kScratchN ? kSlotBytesScratch : kSlotBytes;
+    if (N <= kScratchN && (size_t)P * N * kSetBytes <= budget) {
+        // flat: one group, one launch; tiles split while they would not fill the device
+        const int64_t tiles = P * (P + 1) / 2;
+        s.S = (int)P;
+        s.M = 1;
+        s.Q = tiles <= 1024 ? 4 : tiles <= 2560 ? 2 : 1;
+        return s;
+    }
+    // groups of 16 parts (8 above 2^21 particles, where a call has enough
+    // meetings and the slots would grow past 1 GiB), fewer only where a
+    // smaller budget asks for it; as many sets as fit
+    s.Q = 1;
+    s.S = N <= ((int64_t)1 << 21) ? 16 : 8;
+    const bool fixed = budget < kSlotBytes && N > kScratchN;  // the static array's
+    while (fixed && s.S > 1 && (size_t)s.S * N * kSetBytes > budget) s.S >>= 1;
+    s.M = (int)std::max<int64_t>(1, (int64_t)(budget / ((size_t)s.S * N * kSetBytes)));
+    const int64_t G = (P + s.S - 1) / s.S;
+    s.M = (int)std::min<int64_t>(s.M, G + (G & 1));
+    return s;
 }
 
-size_t pairwise_bytes_S(int64_t N, int S) {
+size_t schedule_bytes(int64_t N, const Schedule &s) {
     const int64_t nbox = (N + 63) / 64;
-    return ws_total({order_targets_bytes(N), (size_t)N * sizeof(SrcRec), (size_t)nbox * kBox * sizeof(double),
-                     (size_t)2 * S * 4 * N * sizeof(double)});
+    return ws_total({N >= kSortMin ? order_targets_bytes(N) : 0, (size_t)N * sizeof(SrcRec),
+                     (size_t)nbox * kBox * sizeof(double), (size_t)s.S * s.M * s.Q * N * kSetBytes});
 }
 
-size_t pairwise_bytes(int64_t N, int, const steps_cyl_table *table, int, bool) {
-    return pairwise_bytes_S(N, pairwise_parts(N, table));
-}
+}  // namespace
+
+size_t pairwise_bytes(int64_t N, size_t slot_budget) { return schedule_bytes(N, pairwise_schedule(N, slot_budget)); }
 
 // Launches the pairwise path for all N particles: exact images |n| <= n_img,
 // or (table non-null) images |n| <= 1 plus the table's far images with CIC
@@ -689,12 +633,11 @@ size_t pairwise_bytes(int64_t N, int, const steps_cyl_table *table, int, bool) {
 // Scratch (spatial order, records, boxes, FP64 sums) comes from `ws`.
 int launch_forces_pairwise(const double *pos, const double *mass, const double *eps, int64_t N, double L,
                            int n_img, const steps_cyl_table *table, int order, float *out_acc, float *out_pot,
-                           Workspace &ws, hipStream_t stream, int s_cap) {
-    int S = pairwise_parts(N, table);
-    if (s_cap > 0) S = std::min(S, s_cap);
-    int rc = check_workspace(ws, pairwise_bytes_S(N, S));
+                           Workspace &ws, hipStream_t stream, size_t slot_budget) {
+    const Schedule sch = pairwise_schedule(N, slot_budget);
+    int rc = check_workspace(ws, schedule_bytes(N, sch));
     if (rc) return rc;
-    const int group = 64 * particles_per_thread(table ? 1 : 0) * S;
+    const int group = kPart * sch.S;
     PairwiseArgs a;
     a.L = L;
     a.invL = 1.0 / L;
@@ -712,30 +655,30 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     a.N = (int)N;
     a.G = (int)((N + group - 1) / group);
     a.Gp = a.G + (a.G & 1);
-    a.round = 0;
-    a.S = S;
+    a.S = sch.S;
+    a.Q = sch.Q;
     const int ord = table ? order : 0;
     const bool complete = table && table->complete != 0;
 
     const int *perm = nullptr;
-    if ((rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
+    if (N >= kSortMin && (rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
     const int64_t nbox = (N + 63) / 64;
+    const size_t slots = (size_t)sch.S * sch.M;
     SrcRec *rec = (SrcRec *)ws.take((size_t)N * sizeof(SrcRec));
     double *box = (double *)ws.take((size_t)nbox * kBox * sizeof(double));
-    double *sum = (double *)ws.take((size_t)2 * S * 4 * N * sizeof(double));
+    double *sum = (double *)ws.take(slots * sch.Q * N * kSetBytes);
     if (!rec || !box || !sum) return fail(STEPS_EINVAL, "workspace too small for the pairwise path");
     a.rec = rec;
     a.box = box;
     a.sum = sum;
-    const int nb = (int)((N + 255) / 256);
-    hipLaunchKernelGGL(stage_kernel, dim3(nb), dim3(256), 0, stream, pos, mass, eps, (int)N, L, perm, rec);
-    hipLaunchKernelGGL(box_kernel, dim3((unsigned)((nbox + 3) / 4)), dim3(256), 0, stream, a.rec, (int)N, box);
+    hipLaunchKernelGGL(stage_kernel, dim3((unsigned)((nbox + 3) / 4)), dim3(256), 0, stream, pos, mass, eps, (int)N, L,
+                       perm, rec, box);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess)
-        e = dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.run(a, stream); });
+        e = dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.run(a, sch.M, stream); });
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(finish_kernel, dim3(nb), dim3(256), 0, stream, a.sum, 2 * S, perm, (int)N, out_acc,
-                           out_acc + N, out_acc + 2 * N, out_pot);
+        hipLaunchKernelGGL(finish_kernel, dim3((unsigned)((N + 255) / 256), out_pot ? 4 : 3), dim3(256), 0, stream,
+                           a.sum, (int)slots, sch.Q, perm, (int)N, out_acc, out_acc + N, out_acc + 2 * N, out_pot);
         e = hipGetLastError();
     }
     return hip_status(e, "forces_pairwise launch");

@@ -422,7 +422,7 @@ STEPS_API int steps_cyl_kdk_step(double *pos, double *mom, const double *mass, c
         rc = steps_cyl_forces_table(pos, mass, eps, N, L, params->table, params->table_order, nullptr, N,
                                     acc_inout, nullptr, stream);
     else
-        rc = with_stream_workspace(pairwise_bytes(N, params->n_img, nullptr, 0, false), stream, [&](Workspace &ws) {
+        rc = with_stream_workspace(pairwise_bytes(N), stream, [&](Workspace &ws) {
             return launch_forces_pairwise(pos, mass, eps, N, L, params->n_img, nullptr, 0, acc_inout, nullptr, ws,
                                           stream);
         });

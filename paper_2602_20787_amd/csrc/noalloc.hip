@@ -3,7 +3,6 @@
 // tight serving loops, harnesses that forbid hipMalloc).  Its workspace is
 // a fixed array in the library's device image, one copy per device, shared
 // by every call on that device.
-#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -60,17 +59,20 @@ STEPS_API int steps_cyl_forces_noalloc(const double *pos, const double *mass, co
     int rc = require_device();
     if (rc) return rc;
     clear_error();
-    // groups of 16 parts as in steps_cyl_forces, or fewer parts (fewer sum
-    // slots) so that the workspace fits the static array
-    int S = 16;
-    while (S > 1 && pairwise_bytes_S(N, S) > kScratchBytes) S >>= 1;
-    if (pairwise_bytes_S(N, S) > kScratchBytes)
+    // the schedule of steps_cyl_forces, or fewer sum slots so that the
+    // workspace fits the static array
+    size_t budget = 0;
+    if (pairwise_bytes(N, budget) > kScratchBytes) {
+        budget = (size_t)112 << 20;
+        while (budget > (1 << 20) && pairwise_bytes(N, budget) > kScratchBytes) budget -= (size_t)4 << 20;
+    }
+    if (pairwise_bytes(N, budget) > kScratchBytes)
         return fail(STEPS_EINVAL, "N=%lld needs %zu bytes of scratch, above the static %zu", (long long)N,
-                    pairwise_bytes_S(N, S), kScratchBytes);
+                    pairwise_bytes(N, budget), kScratchBytes);
     void *p = nullptr;
     if ((rc = scratch_on_device(&p))) return rc;
     Workspace ws;
     ws.base = (char *)p;
     ws.size = kScratchBytes;
-    return launch_forces_pairwise(pos, mass, eps, N, L, n_img, nullptr, 0, out_acc, out_pot, ws, stream, S);
+    return launch_forces_pairwise(pos, mass, eps, N, L, n_img, nullptr, 0, out_acc, out_pot, ws, stream, budget);
 }

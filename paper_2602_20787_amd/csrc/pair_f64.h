@@ -19,6 +19,8 @@ __device__ __forceinline__ void pair_spline_f64(double dx, double dy, double d, 
     s = 0.0;
     fz = 0.0;
     p = 0.0;
+    // rolled: unrolled in a kernel of few images this rare branch sets its registers
+#pragma unroll 1
     for (int n = -n_img; n <= n_img; ++n) {
         const double dz = d - (double)n * L;
         const double r2 = rho2 + dz * dz;

@@ -405,7 +405,7 @@ int check_table_call(const double *pos, const double *mass, const double *eps, i
 
 size_t table_forces_bytes(int64_t N, const steps_cyl_table *t, int order, bool all_targets, int64_t n_targets,
                           bool pot) {
-    return all_targets ? pairwise_bytes(N, 1, t, order, pot) : per_target_bytes(n_targets);
+    return all_targets ? pairwise_bytes(N) : per_target_bytes(n_targets);
 }
 
 // The tabulated forces (arguments validated): the pairwise path for every
