@@ -121,14 +121,18 @@ typedef struct steps_cyl_table steps_cyl_table;   /* opaque; owns device memory 
  * set of (i, j)), so the reaction is the action with dx, dy and F_z negated
  * (F_z keeps its sign where both particles take the minimum image -L/2).
  * Arithmetic: pair separations and the z wrap in FP64, FP32 pair terms,
- * FP64 sums.  Groups of 64 S particles in spatial order (S parts of 64,
- * one particle per lane of a one-wave workgroup) meet in a fixed
- * round-robin tournament (one launch per round, no atomics), so repeated
- * calls are bitwise equal.  Total momentum is conserved to the rounding of
- * the sums.  Workspace (stream-ordered here; see steps_cyl_forces_ws): 32
- * bytes per particle for the records, 64 S for 2S slots of FP64 sums (S = 16
- * parts per group up to N = 2^21, else 8), 1 for boxes, plus the spatial
- * order's 16 bytes per particle and radix-sort storage (about 1.05 GiB at
+ * FP64 sums.  Parts of 64 particles (one per lane of a one-wave workgroup)
+ * meet in tiles: up to 15,000 particles all in one launch, above in groups of
+ * S = 16 parts (8 above N = 2^21) in a fixed round-robin tournament, several
+ * rounds to a launch (no atomics), so repeated calls are bitwise equal.  Up to
+ * 2304 particles every ordered pair is evaluated, one wave per particle; its
+ * terms are the unordered pair's with the signs turned.  Total momentum is
+ * conserved to the rounding of the sums.  Workspace (stream-ordered here; see
+ * steps_cyl_forces_ws; none up to 2304 particles): 32 bytes per particle for
+ * the records, 1 for boxes, 32 per particle and slot of FP64 sums (at least S
+ * slots, and as many sets of S as fit 112 MiB, 256 MiB above N = 125,000), plus
+ * the spatial order's 16 bytes per particle and radix-sort storage (about 0.55
+ * GiB at
  * N = 2^20).  Returns STEPS_OK, or STEPS_EINVAL / STEPS_ENOMEM / STEPS_EHIP.
  */
 int steps_cyl_forces(const double *pos, const double *mass, const double *eps,
@@ -175,10 +179,10 @@ int steps_cyl_forces_ws(const double *pos, const double *mass, const double *eps
  *   N   1 <= N <= STEPS_NOALLOC_MAX_N (2^20); larger N return STEPS_EINVAL
  *       with a message naming the limit, before any device work
  *
- * Groups hold 16 parts as in steps_cyl_forces, or fewer (fewer sum slots)
- * where the workspace would not fit the array (above N = 125,000); with
- * fewer the sums run in another (fixed) order than in steps_cyl_forces and
- * the results agree with it to FP32 rounding, otherwise bit for bit.  Every call on a device shares that
+ * The schedule is that of steps_cyl_forces up to N = 125,000 and has fewer sum
+ * slots above, where the workspace would not fit the array; with fewer the
+ * sums run in another (fixed) order than in steps_cyl_forces and the results
+ * agree with it to FP32 rounding, otherwise bit for bit.  Every call on a device shares that
  * device's array and finds it as the last call left it (nothing in it needs
  * to start at zero): calls that overlap on one device, on different streams
  * or from different threads, race and give undefined results.

@@ -65,6 +65,10 @@ namespace {
 constexpr int kThreads = 64;  // one wave
 constexpr int kPart = 64;     // particles per part, one per lane
 constexpr int kBox = 8;       // doubles per 64-record box
+// The one-launch form up to this many particles.  Per call (us, |n| <= 8 with
+// the potential), one launch against tiles: N = 500 13 and 50, 1000 13 and 38,
+// 2000 29 and 40, 2500 47 and 42.
+constexpr int kSmallMax = 2304;
 // Waves per SIMD.  Measured per call at N = 2^20, |n| <= 8 with the potential
 // (ms) with one launch per round: 1 particle per lane at 4, 5, 6 and 8 waves
 // 1994, 1891, 1895 and 1918; 2 per lane at 2 and 3 waves 2067 and 2110; 4 per
@@ -159,26 +163,38 @@ __global__ __launch_bounds__(256) void stage_kernel(const double *pos, const dou
     }
 }
 
-// One component of one particle per thread: its slots added in order.  With
+// One component of the 64 particles of a part per workgroup, whose waves take
+// equal runs of the slots (added in order, then the runs in order): few
+// particles have many slots, and what bounds the pass is the loads in flight
+// (N = 4096, 128 slots: 17 us with one thread per particle, 4.6 us in 16 runs).  With
 // Q > 1 waves per tile (one group) slot o Q + q is written for every q where
 // the particle's own part p <= o acted, and for q = 0 alone where it reacted.
-__global__ __launch_bounds__(256) void finish_kernel(const double *sum, int slots, int Q, const int *perm, int N,
-                                                     float *ax, float *ay, float *az, float *pot) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (k >= N) return;
-    const double *p = sum + (int64_t)c * N + k;
-    const int64_t stride = 4 * (int64_t)N;
+__global__ __launch_bounds__(1024) void finish_kernel(const double *sum, int slots, int Q, const int *perm, int N,
+                                                      float *ax, float *ay, float *az, float *pot) {
+    __shared__ double run[16][kPart];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int part = blockIdx.x, c = blockIdx.y;
+    const int k = part * kPart + lane;
     double s = 0.0;
-    int o = 0;
-    if (Q > 1)
-        for (const int part = k / kPart; o < part; ++o) s += p[(int64_t)o * Q * stride];
+    if (k < N) {
+        const double *p = sum + (int64_t)c * N + k;
+        const int64_t stride = 4 * (int64_t)N;
+        const int skip = Q > 1 ? part : 0;  // parts that hold one slot
+        const int total = skip + (slots - skip) * Q;
+        const int each = (total + waves - 1) / waves;
+        const int end = min(total, (wave + 1) * each);
 #pragma unroll 8
-    for (int q = o * Q; q < slots * Q; ++q) s += p[q * stride];
-    const int64_t i = perm ? perm[k] : k;
-    // attraction: a = -sum m_j S (x_i - x_j), potential = -sum m_j / r
-    float *out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : pot;
-    out[i] = (float)(-s);
+        for (int e = wave * each; e < end; ++e) s += p[(e < skip ? e * Q : skip * Q + (e - skip)) * stride];
+    }
+    run[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && k < N) {
+        for (int w = 1; w < waves; ++w) s += run[w][lane];
+        const int64_t i = perm ? perm[k] : k;
+        // attraction: a = -sum m_j S (x_i - x_j), potential = -sum m_j / r
+        float *out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : pot;
+        out[i] = (float)(-s);
+    }
 }
 
 // a wave's particle
@@ -325,17 +341,71 @@ __device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, 
     }
 }
 
-// One wave's passage over a tile's sources in general position: FP64
-// separation and minimum image, then FP32 pair terms and FP64 sums (the
-// records are in spatial order, so a particle's near neighbours arrive
-// together and an FP32 partial would lose their cancellation).  The n = 0
-// image of a pair inside its softening length takes the spline in FP32
-// (selected per pair; the separation is the FP64 one cast); with a softening
-// sum above L/2 the images n != 0 may be softened too and the pair is
-// evaluated in FP64 with the spline on every image (rare).  REACT: the sources
-// are another part's and their reactions are summed in the FP64 LDS slots;
-// otherwise (a part against itself; the tile's first record is `base`, `cnt`
-// of its sources are real) the self pair and the padding are skipped.
+// A pair in general position: FP64 separation and minimum image, FP32 terms.
+// The n = 0 image of a pair inside its softening length takes the spline in
+// FP32 (selected per pair; the separation is the FP64 one cast); with a
+// softening sum above L/2 the images n != 0 may be softened too and the pair
+// is evaluated in FP64 with the spline on every image (rare).  `maybe`: the
+// pair may be softened, from a bound; `self`: no term at all, images included.
+struct PairTerms {
+    double dx, dy;
+    float d, S, Fz, P;
+};
+
+template <int NIMG, bool POT, int TORDER, bool COMPLETE>
+__device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, double xi, double yi, double zi, float hi,
+                                                  const SrcRec &src, float thr2, bool wide, bool self) {
+    PairTerms t;
+    t.dx = xi - src.x;
+    t.dy = yi - src.y;
+    const double d64 = min_image(zi - src.z, a.L, a.invL);
+    const float dx = (float)t.dx, dy = (float)t.dy, d = (float)d64;
+    t.d = d;
+    const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
+    const float r2_0 = __builtin_fmaf(d, d, rho2);
+    float T, U, Q;
+    pair_images<NIMG, POT>(rho2, d, r2_0, a.c, T, U, Q);
+    const float hij = hi + src.h;
+    const bool near = (wide || r2_0 < thr2) && (r2_0 < hij * hij || hij > (float)a.halfL);
+    float s0, p0;
+    if (__ballot(near && !self) != 0) {
+        float sf, pf;
+        spline_n0(r2_0, hij, sf, pf);
+        const float ri0 = __builtin_amdgcn_rsqf(r2_0);
+        s0 = near ? sf : ri0 * ri0 * ri0;
+        p0 = near ? pf : ri0;
+    } else {
+        const float ri0 = __builtin_amdgcn_rsqf(r2_0);
+        s0 = ri0 * ri0 * ri0;
+        p0 = ri0;
+    }
+    t.S = s0 + T;
+    t.Fz = __builtin_fmaf(d, t.S, -a.c.Lf * U);
+    t.P = p0 + Q;
+    if (self) {
+        t.S = 0.f;
+        t.Fz = 0.f;
+        t.P = 0.f;
+    }
+    if (near && hij > (float)a.halfL && !self) {
+        // rare and divergent
+        double gs, gf, gp;
+        pair_spline_f64(t.dx, t.dy, d64, (double)hi + (double)src.h, a.L, (NIMG >= 0) ? NIMG : a.c.n_img, gs, gf, gp);
+        t.S = (float)gs;
+        t.Fz = (float)gf;
+        t.P = (float)gp;
+    }
+    if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, self, t.S, t.Fz);
+    return t;
+}
+
+// One wave's passage over a tile's sources in general position, summed in
+// FP64 (the records are in spatial order, so a particle's near neighbours
+// arrive together and an FP32 partial would lose their cancellation).  REACT:
+// the sources are another part's and their reactions are summed in the FP64
+// LDS slots; otherwise (a part against itself; the tile's first record is
+// `base`, `cnt` of its sources are real) the self pair and the padding are
+// skipped.
 template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool REACT>
 __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o, Stage &st, int n, int base, int cnt,
                                           float hmax, double *acc) {
@@ -352,47 +422,8 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o,
         src.m = st.m[k];
         src.h = st.h[k];
         const int ks = k & (n - 1);  // source of the tile
-        const double dx64 = o.x - src.x, dy64 = o.y - src.y;
-        const double d64 = min_image(o.z - src.z, a.L, a.invL);
-        const float dx = (float)dx64, dy = (float)dy64, d = (float)d64;
-        const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
-        const float r2_0 = __builtin_fmaf(d, d, rho2);
-        float T, U, Pq;
-        pair_images<NIMG, POT>(rho2, d, r2_0, a.c, T, U, Pq);
-        const float hij = o.h + src.h;
         const bool self = !REACT && (base + ks == o.t || ks >= cnt);
-        const bool near = (wide || r2_0 < thr2) && (r2_0 < hij * hij || hij > (float)a.halfL);
-        float s0, p0;
-        if (__ballot(near && !self) != 0) {
-            float sf, pf;
-            spline_n0(r2_0, hij, sf, pf);
-            const float ri0 = __builtin_amdgcn_rsqf(r2_0);
-            s0 = near ? sf : ri0 * ri0 * ri0;
-            p0 = near ? pf : ri0;
-        } else {
-            const float ri0 = __builtin_amdgcn_rsqf(r2_0);
-            s0 = ri0 * ri0 * ri0;
-            p0 = ri0;
-        }
-        float S = s0 + T;
-        float Fz = __builtin_fmaf(d, S, -a.c.Lf * U);
-        float P = p0 + Pq;
-        if (self) {
-            // j == i: no term at all, images included
-            S = 0.f;
-            Fz = 0.f;
-            P = 0.f;
-        }
-        if (near && hij > (float)a.halfL && !self) {
-            // rare and divergent
-            double gs, gf, gp;
-            pair_spline_f64(dx64, dy64, d64, (double)o.h + (double)src.h, a.L, (NIMG >= 0) ? NIMG : a.c.n_img, gs, gf,
-                            gp);
-            S = (float)gs;
-            Fz = (float)gf;
-            P = (float)gp;
-        }
-        if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, self, S, Fz);
+        const PairTerms t = general_pair<NIMG, POT, TORDER, COMPLETE>(a, o.x, o.y, o.z, o.h, src, thr2, wide, self);
         const double ms = (double)src.m;
         double jx = 0.0, jy = 0.0, jz = 0.0, jp = 0.0;
         if (REACT && step > 0) {
@@ -402,19 +433,71 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o,
             jz = st.r[2][k];
             if (POT) jp = st.r[3][k];
         }
-        const double S64 = (double)S, Fz64 = (double)Fz;
+        const double S64 = (double)t.S, Fz64 = (double)t.Fz;
         const double mS = ms * S64;
-        acc[0] = __builtin_fma(mS, dx64, acc[0]);
-        acc[1] = __builtin_fma(mS, dy64, acc[1]);
+        acc[0] = __builtin_fma(mS, t.dx, acc[0]);
+        acc[1] = __builtin_fma(mS, t.dy, acc[1]);
         acc[2] = __builtin_fma(ms, Fz64, acc[2]);
-        if (POT) acc[3] = __builtin_fma(ms, (double)P, acc[3]);
+        if (POT) acc[3] = __builtin_fma(ms, (double)t.P, acc[3]);
         if (REACT) {
-            const double fz = __builtin_fabsf(d) >= a.tie32 ? tie_fz(a, o.z, src.z, Fz64) : Fz64;
+            const double fz = __builtin_fabsf(t.d) >= a.tie32 ? tie_fz(a, o.z, src.z, Fz64) : Fz64;
             const double miS = o.m * S64;
-            st.r[0][k] = __builtin_fma(miS, dx64, jx);
-            st.r[1][k] = __builtin_fma(miS, dy64, jy);
+            st.r[0][k] = __builtin_fma(miS, t.dx, jx);
+            st.r[1][k] = __builtin_fma(miS, t.dy, jy);
             st.r[2][k] = __builtin_fma(o.m, fz, jz);
-            if (POT) st.r[3][k] = __builtin_fma(o.m, (double)P, jp);
+            if (POT) st.r[3][k] = __builtin_fma(o.m, (double)t.P, jp);
+        }
+    }
+}
+
+// Few particles (N <= kSmallMax): every ordered pair, one wave per target with
+// the sources over its lanes, straight from the caller's arrays to the
+// outputs.  What bounds such a call is the chain of launches and the workspace
+// around it (N = 500, |n| <= 2: 66 us in ten launches), so this form has one
+// launch and no workspace (13 us, most of it the host's).  Two targets per
+// wave took 33 us against 29 at N = 2000.  The pair term of (j, i) is that of
+// (i, j) with the signs turned, bit for bit, so momentum is conserved as in
+// the pairwise form.  The lanes' FP64 sums are added in a fixed tree.
+struct SmallArgs {
+    PairwiseArgs a;
+    const double *pos, *mass, *eps;
+    float *acc, *pot;
+};
+
+template <int NIMG, bool POT, int TORDER, bool COMPLETE>
+__global__ __launch_bounds__(256) void forces_small_kernel(SmallArgs p) {
+    const PairwiseArgs &a = p.a;
+    const int lane = threadIdx.x & 63;
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= a.N) return;  // whole wave
+    const double *x = p.pos, *y = p.pos + a.N, *z = p.pos + 2 * a.N;
+    const double xi = x[i], yi = y[i], zi = wrap_z(z[i], a.L);
+    const float hi = (float)p.eps[i];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int j0 = 0; j0 < a.N; j0 += 64) {
+        const int j = j0 + lane;
+        const bool live = j < a.N;
+        const int js = live ? j : a.N - 1;
+        SrcRec src;
+        src.x = x[js];
+        src.y = y[js];
+        src.z = wrap_z(z[js], a.L);
+        src.m = (float)p.mass[js];
+        src.h = (float)p.eps[js];
+        const PairTerms t =
+            general_pair<NIMG, POT, TORDER, COMPLETE>(a, xi, yi, zi, hi, src, 0.f, true, !live || j == i);
+        const double ms = (double)src.m, mS = ms * (double)t.S;
+        acc[0] = __builtin_fma(mS, t.dx, acc[0]);
+        acc[1] = __builtin_fma(mS, t.dy, acc[1]);
+        acc[2] = __builtin_fma(ms, (double)t.Fz, acc[2]);
+        if (POT) acc[3] = __builtin_fma(ms, (double)t.P, acc[3]);
+    }
+#pragma unroll
+    for (int c = 0; c < (POT ? 4 : 3); ++c) {
+        for (int off = 32; off >= 1; off >>= 1) acc[c] += __shfl_xor(acc[c], off);
+        if (lane == 0) {
+            float *o = c < 3 ? p.acc + (int64_t)c * a.N : p.pot;
+            o[i] = (float)(-acc[c]);
         }
     }
 }
@@ -463,10 +546,11 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
     const int ocnt = (int)max((int64_t)0, min((int64_t)kPart, (int64_t)a.N - g0));    // owned records
     const int cnt = (int)max((int64_t)0, min((int64_t)n, (int64_t)a.N - b0));         // sources
     const bool react = !own || pi != pj;
-    // the owned particles' slot and the sources' (whole wave: a null pointer where there are none)
-    double *pa = a.sum + ((int64_t)(set * S + pj) * Q + q) * 4 * a.N + g0 + lane;
-    double *pb = a.sum + (int64_t)(set * S + pi) * Q * 4 * a.N + b0 + lane;
+    // the owned particles' slot and the sources'
+    double *pa = a.sum + ((int64_t)(set * S + pj) * Q + q) * 4 * a.N + g0;
+    double *pb = a.sum + (int64_t)(set * S + pi) * Q * 4 * a.N + b0;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int out = lane;
     if (ocnt > 0 && cnt > 0) {
         // an empty lane copies the part's first record with no mass (it sits
         // where a particle is, so every pair distance stays that of a real pair)
@@ -499,36 +583,45 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
         else
             near_pass<NIMG, POT, TORDER, COMPLETE, true>(a, o, st, n, (int)b0, cnt, (float)b[6], acc);
         __syncthreads();
-        if (react && lane < cnt) {
+        // the lane's addresses are formed here: held over the loops they would cost 4 VGPRs
+        asm volatile("" : "+v"(out));
+        if (react && out < cnt) {
             // reactions on the sources, in the owned sums' orientation
 #pragma unroll
             for (int c = 0; c < (POT ? 4 : 3); ++c) {
-                double v = st.r[c][lane];
-                for (int e = n; e < kPart; e += n) v += st.r[c][lane + e];
+                double v = st.r[c][out];
+                for (int e = n; e < kPart; e += n) v += st.r[c][out + e];
                 if (c < 3) v = -v;
-                pb[(int64_t)c * a.N] = a.first ? v : pb[(int64_t)c * a.N] + v;
+                double *p = pb + (int64_t)c * a.N;
+                p[out] = a.first ? v : p[out] + v;
             }
         }
     } else if (a.first && react && lane < cnt) {
 #pragma unroll
-        for (int c = 0; c < (POT ? 4 : 3); ++c) pb[(int64_t)c * a.N] = 0.0;
+        for (int c = 0; c < (POT ? 4 : 3); ++c) pb[(int64_t)c * a.N + lane] = 0.0;
     }
-    if (lane < ocnt && (a.first || cnt > 0)) {
+    if (out < ocnt && (a.first || cnt > 0)) {
 #pragma unroll
-        for (int c = 0; c < (POT ? 4 : 3); ++c)
-            pa[(int64_t)c * a.N] = a.first ? acc[c] : pa[(int64_t)c * a.N] + acc[c];
+        for (int c = 0; c < (POT ? 4 : 3); ++c) {
+            double *p = pa + (int64_t)c * a.N;
+            p[out] = a.first ? acc[c] : p[out] + acc[c];
+        }
     }
 }
 
 template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 struct Launcher {
+    static hipError_t small(const SmallArgs &p, hipStream_t stream) {
+        hipLaunchKernelGGL((forces_small_kernel<NIMG, POT, TORDER, COMPLETE>), dim3((p.a.N + 3) / 4), dim3(256), 0,
+                           stream, p);
+        return hipGetLastError();
+    }
+
     static hipError_t run(PairwiseArgs a, int sets, hipStream_t stream) {
         const int rounds = a.G > 1 ? a.Gp : 1;
-        const int launches = (rounds + sets - 1) / sets;
-        const int each = (rounds + launches - 1) / launches;  // <= sets
         hipError_t e = hipSuccess;
-        for (int r = 0; e == hipSuccess && r < rounds; r += each) {
-            const int k = std::min(each, rounds - r);
+        for (int r = 0; e == hipSuccess && r < rounds; r += sets) {
+            const int k = std::min(sets, rounds - r);
             a.round = r;
             a.first = r == 0;
             a.own = r == 0 ? (unsigned)a.G * a.S * (a.S + 1) / 2 * a.Q : 0;
@@ -578,8 +671,10 @@ auto dispatch(int n_img, bool pot, int order, bool complete, F &&f) {
 namespace {
 
 // Below this many particles the parts are runs of the particles' own order:
-// what the order saves in near tiles is less than sorting costs.
-constexpr int64_t kSortMin = 6144;
+// what the order saves in near tiles is less than the 60 us that sorting costs
+// (us per call without and with it: N = 8000 167 and 200, 12000 339 and 352;
+// with a CIC table 148 and 171, 283 and 284).
+constexpr int64_t kSortMin = 10240;
 
 // Bytes of FP64 sum slots of a call.  Up to kScratchN particles the slots (and
 // what else a call takes) fit the 128 MiB array of steps_cyl_forces_noalloc,
@@ -597,11 +692,13 @@ Schedule pairwise_schedule(int64_t N, size_t budget) {
     const int64_t P = (N + kPart - 1) / kPart;
     if (budget == 0) budget = N <= kScratchN ? kSlotBytesScratch : kSlotBytes;
     if (N <= kScratchN && (size_t)P * N * kSetBytes <= budget) {
-        // flat: one group, one launch; tiles split while they would not fill the device
+        // flat: one group, one launch; tiles split while they would not fill
+        // the device (us per call at Q = 1, 2, 4: N = 2800 49, 43, 43; 4096
+        // 78, 70, 68; 6000 114, 103, 110; 8000 166, 162, 168)
         const int64_t tiles = P * (P + 1) / 2;
         s.S = (int)P;
         s.M = 1;
-        s.Q = tiles <= 1024 ? 4 : tiles <= 2560 ? 2 : 1;
+        s.Q = tiles <= 1024 ? 4 : tiles <= 8192 ? 2 : 1;
         return s;
     }
     // groups of 16 parts (8 above 2^21 particles, where a call has enough
@@ -613,11 +710,14 @@ Schedule pairwise_schedule(int64_t N, size_t budget) {
     while (fixed && s.S > 1 && (size_t)s.S * N * kSetBytes > budget) s.S >>= 1;
     s.M = (int)std::max<int64_t>(1, (int64_t)(budget / ((size_t)s.S * N * kSetBytes)));
     const int64_t G = (P + s.S - 1) / s.S;
-    s.M = (int)std::min<int64_t>(s.M, G + (G & 1));
+    const int rounds = G > 1 ? (int)(G + (G & 1)) : 1;
+    const int launches = (rounds + s.M - 1) / s.M;
+    s.M = (rounds + launches - 1) / launches;  // launches of equal length, every set written by the first
     return s;
 }
 
 size_t schedule_bytes(int64_t N, const Schedule &s) {
+    if (N <= kSmallMax) return 0;
     const int64_t nbox = (N + 63) / 64;
     return ws_total({N >= kSortMin ? order_targets_bytes(N) : 0, (size_t)N * sizeof(SrcRec),
                      (size_t)nbox * kBox * sizeof(double), (size_t)s.S * s.M * s.Q * N * kSetBytes});
@@ -660,6 +760,18 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     const int ord = table ? order : 0;
     const bool complete = table && table->complete != 0;
 
+    if (N <= kSmallMax) {
+        SmallArgs p;
+        p.a = a;
+        p.pos = pos;
+        p.mass = mass;
+        p.eps = eps;
+        p.acc = out_acc;
+        p.pot = out_pot;
+        return hip_status(
+            dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.small(p, stream); }),
+            "forces_pairwise launch");
+    }
     const int *perm = nullptr;
     if (N >= kSortMin && (rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
     const int64_t nbox = (N + 63) / 64;
@@ -677,8 +789,9 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     if (e == hipSuccess)
         e = dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.run(a, sch.M, stream); });
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(finish_kernel, dim3((unsigned)((N + 255) / 256), out_pot ? 4 : 3), dim3(256), 0, stream,
-                           a.sum, (int)slots, sch.Q, perm, (int)N, out_acc, out_acc + N, out_acc + 2 * N, out_pot);
+        hipLaunchKernelGGL(finish_kernel, dim3((unsigned)nbox, out_pot ? 4 : 3), dim3(slots * sch.Q > 64 ? 1024 : 256),
+                           0, stream, a.sum, (int)slots, sch.Q, perm, (int)N, out_acc, out_acc + N, out_acc + 2 * N,
+                           out_pot);
         e = hipGetLastError();
     }
     return hip_status(e, "forces_pairwise launch");

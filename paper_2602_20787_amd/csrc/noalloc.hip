@@ -10,9 +10,10 @@
 namespace steps {
 namespace {
 
-// Largest workspace of one call: the pairwise path at N = 2^20 with groups
-// of one part (spatial order 16 B, records 32 B and two slots of FP64 sums
-// 64 B per particle, boxes, the radix sort's storage) fits with room.
+// Largest workspace of one call: the schedule of steps_cyl_forces up to
+// 125,000 particles; at N = 2^20 the pairwise path with groups of two parts
+// (spatial order 16 B, records 32 B and two slots of FP64 sums 64 B per
+// particle, boxes, the radix sort's storage) fits with room.
 constexpr size_t kScratchBytes = (size_t)128 << 20;
 
 static __device__ __align__(256) char scratch[kScratchBytes];

@@ -1,0 +1,150 @@
+"""The schedules of the pairwise exact and tabulated paths, at the sizes where
+one gives way to the next: one wave per target, flat tiles split over four, two
+and one waves (parts and tiles full, ragged and nearly empty), sorted and
+unsorted parts, groups meeting over one or several launches with even and odd
+group counts and a ragged last group, and the launches of the static scratch.
+
+Bars against the FP64 GPU reference (itself pinned to the oracle): a pair term
+in FP32 is within 8 rounding errors (the three casts, r^2, the hardware's
+reciprocal square root and its cube, the product with d), 5e-7 of it, and the
+sums are FP64, so an acceleration is held to 1e-6 of the sum of its terms'
+sizes (not of itself: a particle whose terms cancel has no relative bound) and
+the potential, whose terms have one sign, to 1e-6; total momentum to 1e-6 of
+the sum of forces; the tabulated path against its per-target kernel (FP32 sums)
+at the 2e-5 of the octree's comparison with it.  Repeated calls, in any
+workspace, are equal bit for bit.
+"""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_20787_amd as m
+    return m
+
+
+def to_dev(p):
+    d = torch.device("cuda:0")
+    return (torch.from_numpy(p.pos).to(d), torch.from_numpy(p.mass).to(d), torch.from_numpy(p.eps).to(d))
+
+
+def rel(a, ref):
+    a, ref = a.double(), ref.double()
+    return (torch.linalg.norm(a - ref, dim=0) / torch.linalg.norm(ref, dim=0)).max().item()
+
+
+def term_sizes(pos, m, e, L, n_img):
+    """Sum over the pairs and images of the size of each term, per target."""
+    N = m.numel()
+    out = torch.zeros(N, dtype=torch.float64, device=pos.device)
+    step = max(1, (1 << 24) // N)
+    for a in range(0, N, step):
+        d = [pos[c, a:a + step, None] - pos[c][None] for c in range(3)]
+        d[2] = d[2] - L * torch.floor(d[2] / L + 0.5)
+        h = e[a:a + step, None] + e[None]
+        for n in range(-n_img, n_img + 1):
+            r2 = d[0] ** 2 + d[1] ** 2 + (d[2] - n * L) ** 2
+            # inside the softening length the spline's force is at most 2.2 / h^2
+            out[a:a + step] += (m / torch.maximum(r2, h * h / 2.2)).sum(1)
+    return out
+
+
+def check(sc, pos, m, e, L, n_img, acc, pot):
+    ref, ref_pot = sc.steps_cyl_forces_f64(pos, m, e, L, n_img)
+    err = (torch.linalg.norm(acc.double() - ref, dim=0) / term_sizes(pos, m, e, L, n_img)).max().item()
+    print(f"error over the terms' sizes {err:.2e}")
+    assert err <= 1e-6
+    if pot is not None:
+        assert (torch.abs(pot.double() - ref_pot) / torch.abs(ref_pot)).max().item() <= 1e-6
+
+
+# 2304/2305: one launch / tiles; 2880/2881: 4 and 2 waves per tile; 8128/8129:
+# 2 and 1; 10239/10240: sorted; 15296/15297: flat / groups; 20011: several
+# launches; 30720 and 31745: even and odd group counts, one particle in the last
+@pytest.mark.parametrize("N", [2, 63, 64, 65, 2304, 2305, 2368, 2369, 2880, 2881, 4109, 8128, 8129, 10239, 10240, 15296,
+                               15297, 20011, 30720, 31745])
+@pytest.mark.parametrize("n_img", [0, 2])
+def test_exact_schedules(sc, N, n_img):
+    print(f"[case] N={N} n_img={n_img}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    pos, m, e = to_dev(p)
+    acc, pot = sc.steps_cyl_forces(pos, m, e, p.L, n_img)
+    # in a workspace full of NaN: every slot is written before it is added to
+    nb = sc.steps_cyl_forces_workspace(sc.STEPS_PATH_EXACT, N, n_img, 0, sc.STEPS_SUM_PAIRWISE)
+    ws = torch.full((max(nb, 1),), 255, dtype=torch.uint8, device="cuda:0")
+    again, pot_again = sc.steps_cyl_forces_ws(pos, m, e, p.L, n_img, ws)
+    assert torch.equal(acc, again) and torch.equal(pot, pot_again)
+    only, none = sc.steps_cyl_forces(pos, m, e, p.L, n_img, potential=False)
+    assert none is None
+    check(sc, pos, m, e, p.L, n_img, acc, pot)
+    check(sc, pos, m, e, p.L, n_img, only, None)
+    mom = torch.abs((m[None] * acc.double()).sum(1)) / (m[None] * torch.abs(acc.double())).sum(1)
+    assert mom.max().item() <= 1e-6
+
+
+@pytest.mark.parametrize("n_img", [0, 1, 2, 3, 4, 8])
+@pytest.mark.parametrize("N", [700, 5000])
+def test_image_counts_with_and_without_the_potential(sc, N, n_img):
+    # clustered: softened pairs in every tile
+    p = synth.clustered_load(N, n_clumps=8, clump_frac=0.05, seed=5)
+    pos, m, e = to_dev(p)
+    acc, pot = sc.steps_cyl_forces(pos, m, e, p.L, n_img)
+    only, _ = sc.steps_cyl_forces(pos, m, e, p.L, n_img, potential=False)
+    check(sc, pos, m, e, p.L, n_img, acc, pot)
+    check(sc, pos, m, e, p.L, n_img, only, None)
+
+
+@pytest.mark.parametrize("N", [1, 100, 3000])
+def test_half_periods_and_large_softening(sc, N):
+    # axial separations of exactly L/2, and softening lengths above L/4, where
+    # images n != 0 are softened too
+    p = synth.cylinder_load(N, seed=3)
+    pos = p.pos.copy()
+    pos[2] = np.floor(pos[2] * 4.0) / 4.0
+    for eps in (p.eps, p.eps * (0.3 / p.eps.min())):
+        d = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (pos, p.mass, eps)]
+        acc, pot = sc.steps_cyl_forces(*d, p.L, 2)
+        if N == 1:
+            assert not acc.any() and not pot.any()
+        else:
+            check(sc, *d, p.L, 2, acc, pot)
+
+
+@pytest.mark.parametrize("N", [300, 2305, 5000, 10240, 17000])
+@pytest.mark.parametrize("order,complete", [(1, False), (2, True)])
+def test_table_schedules(sc, N, order, complete):
+    print(f"[case] table N={N} order={order}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    pos, m, e = to_dev(p)
+    tab = sc.CorrectionTable.ewald(32, 36, 4.5, 2.0, 5, 12) if complete else sc.CorrectionTable(32, 36, 4.5, 64)
+    t = torch.arange(N, dtype=torch.int64, device="cuda:0")
+    acc, pot = sc.steps_cyl_forces_table(pos, m, e, p.L, tab, order=order)
+    nb = sc.steps_cyl_forces_workspace(sc.STEPS_PATH_TABLE, N, 0, 0, 0, table=tab, order=order)
+    ws = torch.full((max(nb, 1),), 255, dtype=torch.uint8, device="cuda:0")
+    again, _ = sc.steps_cyl_forces_table_ws(pos, m, e, p.L, tab, ws, order=order)
+    assert torch.equal(acc, again)
+    ref, ref_pot = sc.steps_cyl_forces_table(pos, m, e, p.L, tab, order=order, targets=t)
+    print(f"difference {rel(acc, ref):.2e}")
+    assert rel(acc, ref) <= 2e-5
+    assert (torch.abs(pot - ref_pot) / torch.abs(ref_pot)).max().item() <= 2e-5
+    tab.close()
+
+
+@pytest.mark.parametrize("N", [2304, 15296, 100001, 125000, 125001, 300000])
+def test_static_scratch_runs_the_same_schedule(sc, N):
+    # bit for bit up to 125,000 particles; above, other sums of the same terms
+    p = synth.cylinder_load(N, seed=7)
+    pos, m, e = to_dev(p)
+    a, ap = sc.steps_cyl_forces(pos, m, e, p.L, 0)
+    b, bp = sc.steps_cyl_forces_noalloc(pos, m, e, p.L, 0)
+    if N <= 125000:
+        assert torch.equal(a, b) and torch.equal(ap, bp)
+    assert rel(b, a) <= 1e-6
