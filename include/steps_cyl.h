@@ -351,10 +351,10 @@ int steps_cyl_mlp_load(const char *path, steps_cyl_mlp **out);
  * away; h_i + h_j below that is assumed).  The learned pair term is odd in
  * the separation (R_z odd in d, R_rho even), so, as in steps_cyl_forces,
  * every unordered pair is evaluated once and applied to both particles, with
- * FP64 sums: groups of 1024 particles (8 sub-groups of 128) meet in the
- * round-robin tournament of steps_cyl_forces (no atomics; repeated calls
- * are bitwise equal).
- * Workspace about 80 bytes per particle (records, sums, spatial order).
+ * FP64 sums: parts of 128 particles, in groups of 1024 above 21,000
+ * particles, meet on the schedule of steps_cyl_forces (no atomics; repeated
+ * calls are bitwise equal).  Workspace as there (32 bytes per particle and
+ * slot, S = 8).
  */
 int steps_cyl_forces_learned(const double *pos, const double *mass, const double *eps,
                              int64_t N, double L, const steps_cyl_mlp *net,

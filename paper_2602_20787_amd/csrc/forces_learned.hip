@@ -25,6 +25,7 @@
 #include "learned_model.h"
 #include "mlp_device.h"
 #include "pair_fp32.h"
+#include "pair_schedule.h"
 
 namespace steps {
 
@@ -471,107 +472,72 @@ int launch_forces_learned(const double *pos, const double *mass, const double *e
 // F_z negated (F_z keeps its sign where both particles take the minimum
 // image -L/2).
 //
-// Schedule (no atomics, bitwise reproducible).  Particles in spatial order
-// form sub-groups of 128 (a workgroup's 4 waves x 32 columns) and groups of
-// kSubs sub-groups.  The groups meet on the schedule of the pairwise exact
-// path: a first launch pairs every group with itself (one-sided, every
-// ordered pair, the self pair skipped), then G' - 1 launches (G' = G rounded
-// up to even) follow the round-robin tournament in which round r pairs group
-// G'-1 with group r and group (r + k) mod (G'-1) with group (r - k) mod
-// (G'-1).  A meeting of groups A and B takes kSubs^2 workgroups, workgroup
-// (i, j) holding sub-group i of A as targets and streaming sub-group j of B:
-// it adds its actions to slot j of the sums of a_i and the reactions to slot
-// kSubs + i of the sums of b_j.  No group appears twice in a launch, so each
-// slot has one writer per launch and every sum is a plain read-modify-write
-// in an order fixed by N.  A launch holds kSubs^2 G'/2 workgroups of equal
-// size, so one slow meeting (a near pair of groups, with many pairs outside
-// the network's domain) is a small part of it.  A wave walks the sources in
-// blocks of 64, 32 steps per block: at step u lane (h, c) takes source
-// 32h + (c + u) mod 32 of the block, so the 64 lanes meet 64 different
-// sources and each source meets the wave's 32 targets over the 32 steps.
-// The reaction on a source is then summed in an FP64 LDS slot per wave that
-// the lanes update in turn (no cross-lane reduction), and the 4 waves'
-// slots are added in order at the end.  Both sides are summed in FP64
-// (sources in spatial order would cost FP32 partials their cancellation).
+// Schedule: pair_schedule.h, with parts of 128 particles (a workgroup's 4 waves
+// x 32 columns) in groups of kSubs.  A wave takes 5 us per step alone (two
+// network tiles one after the other) and three share a SIMD, so what bounds a
+// small call is the number of workgroups and how evenly they fall on the 256
+// CUs: the rounds of a call share launches, and up to kFlatSplit tiles
+// each is split by its sources.  A wave walks the sources in blocks of up to
+// 64, n per block in n/2 steps: at step u lane l takes LDS entry l xor u, where
+// each lane half holds its n/2 sources 64/n times over, so no two lanes meet
+// one entry at once and each source meets the wave's 32 targets.  The reaction
+// on a source is summed in an FP64 LDS slot per wave and entry that the lanes
+// update in turn (no cross-lane reduction), and the waves' and copies' slots
+// are added in order at the end.  Both sides are summed in FP64 (sources in
+// spatial order would cost FP32 partials their cancellation).
 namespace {
 
-constexpr int kOwn = 128;  // particles per sub-group, one per wave column
-constexpr int kSubs = 8;   // sub-groups per group
-constexpr int kSlots = 2 * kSubs;  // sums per particle: actions by source sub-group, reactions by target sub-group
+constexpr int kOwn = 128;  // particles per part, one per wave column
+constexpr int kSubs = 8;   // parts per group
+// Flat calls split their tiles over up to 16 workgroups each while that leaves
+// at most this many (us per call with at most 1024, 2048, 4096, 8192: N = 2000
+// 230, 195, 191, 185; 4096 815, 675, 637, 618; 8000 1989, 1997, 1957, 1948).
+constexpr int kFlatSplit = 8192;
 
 struct PairwiseLearnedArgs {
     LearnedArgs la;   // L, invL, halfL, invLf, invL2f, c, P of the per-target kernel
     const SrcRec *rec;
-    double *acc;      // [kSlots][4][N] in spatial order
+    double *acc;      // [M S Q][4][N] in spatial order
     double tie;
     float tie32;
-    int N, G, Gp;     // particles, groups (of kSubs sub-groups), groups rounded up to even
-    int round;        // tournament round (meeting launches)
+    int N;
+    Rounds rd;        // this launch's meetings
 };
 
-__global__ void lp_stage_kernel(const double *pos, const double *mass, const double *eps, int N, double L,
-                                const int *perm, SrcRec *rec) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const int p = perm[k];
-    SrcRec r;
-    r.x = pos[p];
-    r.y = pos[(int64_t)N + p];
-    r.z = wrap_z(pos[2 * (int64_t)N + p], L);
-    r.m = (float)mass[p];
-    r.h = (float)eps[p];
-    rec[k] = r;
-}
-
-__global__ void lp_finish_kernel(const double *acc, const int *perm, int N, float *ax, float *ay, float *az,
-                                 float *pot) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int q = 0; q < kSlots; ++q)
-        for (int c = 0; c < 4; ++c) v[c] += acc[((int64_t)q * 4 + c) * N + k];
-    const int p = perm[k];
-    ax[p] = (float)(-v[0]);
-    ay[p] = (float)(-v[1]);
-    az[p] = (float)(-v[2]);
-    if (pot) pot[p] = (float)(-v[3]);
-}
-
-// Workgroup (i, j) of one meeting (REACT: the groups of tournament round
-// pa.round) or of one group's meeting with itself.
-template <bool POT, bool REACT>
+// One tile.
+template <bool POT>
 __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(PairwiseLearnedArgs pa) {
     __shared__ mlp::Packed P;
     __shared__ SrcRec tile[kOwn];
-    __shared__ double jpart[kBlock / 64][4][kOwn];  // per wave, component, source
+    __shared__ double jpart[kBlock / 64][4][kOwn];  // per wave, component, entry
     __shared__ BandSeries bands;
     const LearnedArgs &a = pa.la;
-    const int meet = blockIdx.x / (kSubs * kSubs);
-    const int si = (blockIdx.x / kSubs) % kSubs, sj = blockIdx.x % kSubs;
-    int ga = meet, gb = meet;
-    if (REACT) {
-        const int M = pa.Gp - 1;
-        if (meet == 0) {
-            ga = M;
-            gb = pa.round;
-        } else {
-            ga = (pa.round + meet) % M;
-            gb = (pa.round - meet + M) % M;
+    const Tile tl = tile_of_block(pa.rd);
+    const int n = kOwn / pa.rd.Q;                                            // sources of the tile
+    const int64_t g0 = min((int64_t)pa.N, tl.pa * kOwn);                     // first target
+    const int base = (int)min((int64_t)pa.N, tl.pb * kOwn + tl.q * n);       // first source
+    const int ocnt = (int)min((int64_t)kOwn, (int64_t)pa.N - g0);
+    const int cnt = min(n, pa.N - base);
+    const bool react = tl.pa != tl.pb;
+    const int tid = threadIdx.x;
+    double *own = pa.acc + (int64_t)tl.slot_a * 4 * pa.N + g0;     // the targets' slot
+    double *other = pa.acc + (int64_t)tl.slot_b * 4 * pa.N + base;  // the sources'
+    if (ocnt == 0 || cnt == 0) {
+        // no partner (whole workgroup): a first launch still writes the slots
+        if (!pa.rd.first) return;
+#pragma unroll
+        for (int k = 0; k < (POT ? 4 : 3); ++k) {
+            if (tid < ocnt) own[(int64_t)k * pa.N + tid] = 0.0;
+            if (react && tid < cnt) other[(int64_t)k * pa.N + tid] = 0.0;
         }
-        if (ga >= pa.G || gb >= pa.G) return;  // the empty group of an odd count (whole workgroup)
+        return;
     }
-    // target sub-group ga*kSubs + si, source sub-group gb*kSubs + sj
-    const int ta = ga * kSubs + si, sb = gb * kSubs + sj;
-    if ((int64_t)ta * kOwn >= pa.N) return;                   // no targets (whole workgroup)
-    if (REACT && (int64_t)sb * kOwn >= pa.N) return;          // no sources: nothing to add
     mlp::load_packed(&P, a.P);
     load_band_series(&bands, a.bs);
-    const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, h = lane >> 5;
-    const int64_t t64 = (int64_t)ta * kOwn + wave * 32 + col;
-    const bool active = t64 < pa.N;
-    const int t = active ? (int)t64 : pa.N;
+    const bool active = wave * 32 + col < ocnt;
+    const int t = active ? (int)g0 + wave * 32 + col : pa.N;
     // an empty slot sits far away with no mass: no reaction, never written
     double xi = 1e18, yi = 0.0, zi = 0.0;
     float hi = 0.f, mi = 0.f;
@@ -586,21 +552,24 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(Pair
     // this half's sums for target `col` (h = 0: even sources, h = 1: odd)
     double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
 
-    const int base = sb * kOwn;
-    const int cnt = max(0, min(kOwn, pa.N - base));  // 0: an empty sub-group of the self meeting
-    if (tid < cnt) tile[tid] = pa.rec[base + tid];
-    if (REACT) {
+    // entry e of a block holds source (e / 32) steps + e mod steps
+    const int block = min(n, 64), steps = block / 2, blocks = n / block;
+    if (tid < 64 * blocks) {
+        const int s = (tid >> 6) * 64 + ((tid & 63) >> 5) * steps + (tid & (steps - 1));
+        tile[tid] = pa.rec[base + (s < cnt ? s : 0)];
+    }
+    if (react) {
         double *jz0 = &jpart[0][0][0];
         for (int q = tid; q < (kBlock / 64) * 4 * kOwn; q += kBlock) jz0[q] = 0.0;
     }
     __syncthreads();  // the tile, the parameters and the cleared slots are in LDS
     for (int s0 = 0; s0 < cnt; s0 += 64) {
-        for (int u = 0; u < 32; ++u) {
-            const int jr = s0 + 32 * h + ((col + u) & 31);
-            const bool live = jr < cnt;
-            const int js = live ? jr : 0;  // a dead lane reads a real record and adds nothing
+        for (int u = 0; u < steps; ++u) {
+            const int js = s0 + (lane ^ u);  // entry
+            const int jr = s0 + h * steps + (js & (steps - 1));
+            const bool live = jr < cnt;  // a dead lane meets a real record and adds nothing
             const SrcRec src = tile[js];
-            const bool self = !REACT && (base + js == t);
+            const bool self = !react && (base + jr == t);
             PairState q = pair_state<POT>(src, self, live, xi, yi, zi, hi, a);
             const float g1 = __shfl_xor(q.f1, 32), g2 = __shfl_xor(q.f2, 32);
             const float fa1 = h ? g1 : q.f1, fa2 = h ? g2 : q.f2;
@@ -632,7 +601,7 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(Pair
             sy = __builtin_fma(mj * Seff, (double)q.dy, sy);
             sz = __builtin_fma(mj, Fzeff, sz);
             if (POT) sp = __builtin_fma(mj, Pn, sp);
-            if (REACT && live) {
+            if (react && live) {
                 // the source sees -dx, -dy and -d, except where |d| = L/2 up
                 // to rounding and its own minimum image has the sign of d
                 double fz = Fzeff;
@@ -657,18 +626,21 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(Pair
             asm volatile("" ::: "memory");
         }
     }
-    if (REACT) {
+    if (react) {
         __syncthreads();
         if (tid < cnt) {
-            // reaction on source base + tid in the owned sums' orientation:
-            // the 4 waves' parts in order, into the source's slot kSubs + si
-            const int64_t jj = base + tid;
+            // reaction on source base + tid in the owned sums' orientation: its
+            // entries' copies in order, of each the 4 waves' parts in order
+            const int in = tid & 63;
+            const int e0 = (tid & ~63) + (in / steps) * 32 + (in & (steps - 1));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (k == 3 && !POT) continue;
-                const double v = (jpart[0][k][tid] + jpart[1][k][tid]) + (jpart[2][k][tid] + jpart[3][k][tid]);
-                double *p = pa.acc + ((int64_t)(kSubs + si) * 4 + k) * pa.N + jj;
-                *p = (k == 3) ? *p + v : *p - v;
+            for (int k = 0; k < (POT ? 4 : 3); ++k) {
+                double v = 0.0;
+                for (int e = e0; e < e0 + 32; e += steps)
+                    v += (jpart[0][k][e] + jpart[1][k][e]) + (jpart[2][k][e] + jpart[3][k][e]);
+                if (k < 3) v = -v;
+                double *p = other + (int64_t)k * pa.N + tid;
+                *p = pa.rd.first ? v : *p + v;
             }
         }
     }
@@ -678,40 +650,28 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(Pair
     sz += __shfl_xor(sz, 32);
     sp += __shfl_xor(sp, 32);
     if (active && h == 0) {
-        // the targets' actions from sub-group sj: slot sj; the self meeting
-        // initialises it and clears the reaction slot kSubs + sj
         const double v[4] = {sx, sy, sz, sp};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            double *p = pa.acc + ((int64_t)sj * 4 + k) * pa.N + t;
-            if (REACT) {
-                if (k < 3 || POT) *p += v[k];
-            } else {
-                *p = v[k];
-                p[(int64_t)kSubs * 4 * pa.N] = 0.0;
-            }
+        for (int k = 0; k < (POT ? 4 : 3); ++k) {
+            double *p = own + (int64_t)k * pa.N + wave * 32 + col;
+            *p = pa.rd.first ? v[k] : *p + v[k];
         }
     }
 }
 
-template <bool POT>
-hipError_t launch_learned_pairwise(PairwiseLearnedArgs pa, hipStream_t stream) {
-    hipLaunchKernelGGL((forces_learned_pairwise_kernel<POT, false>), dim3(pa.G * kSubs * kSubs), dim3(kBlock), 0,
-                       stream, pa);
-    hipError_t e = hipGetLastError();
-    for (int r = 0; e == hipSuccess && r + 1 < pa.Gp; ++r) {
-        pa.round = r;
-        hipLaunchKernelGGL((forces_learned_pairwise_kernel<POT, true>), dim3(pa.Gp / 2 * kSubs * kSubs), dim3(kBlock),
-                           0, stream, pa);
-        e = hipGetLastError();
-    }
-    return e;
+Schedule learned_schedule(int64_t N) {
+    Schedule s = make_schedule(N, kOwn, kSubs, 0);
+    const int tiles = s.S * (s.S + 1) / 2;
+    while (s.flat && s.Q < 16 && tiles * s.Q * 2 <= kFlatSplit) s.Q *= 2;
+    return s;
 }
 
 }  // namespace
 
 size_t learned_pairwise_bytes(int64_t N) {
-    return ws_total({order_targets_bytes(N), (size_t)N * sizeof(SrcRec), (size_t)N * kSlots * 4 * sizeof(double)});
+    const int64_t nbox = (N + 63) / 64;
+    return ws_total({N >= kSortMin ? order_targets_bytes(N) : 0, (size_t)N * sizeof(SrcRec),
+                     (size_t)nbox * kBox * sizeof(double), slot_bytes(learned_schedule(N), N)});
 }
 
 // Pairwise learned forces of all N particles (see above); arguments already
@@ -722,10 +682,12 @@ int launch_forces_learned_pairwise(const double *pos, const double *mass, const 
     int rc = check_workspace(ws, learned_pairwise_bytes(N));
     if (rc) return rc;
     const int *perm = nullptr;
-    if ((rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
+    if (N >= kSortMin && (rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
+    const Schedule sch = learned_schedule(N);
     SrcRec *rec = (SrcRec *)ws.take((size_t)N * sizeof(SrcRec));
-    double *acc = (double *)ws.take((size_t)N * kSlots * 4 * sizeof(double));
-    if (!rec || !acc) return fail(STEPS_EINVAL, "workspace too small for the pairwise learned path");
+    double *box = (double *)ws.take((size_t)((N + 63) / 64) * kBox * sizeof(double));
+    double *acc = (double *)ws.take(slot_bytes(sch, N));
+    if (!rec || !box || !acc) return fail(STEPS_EINVAL, "workspace too small for the pairwise learned path");
     PairwiseLearnedArgs pa;
     LearnedArgs &a = pa.la;
     a.x = a.y = a.z = a.m = a.h = nullptr;
@@ -750,18 +712,17 @@ int launch_forces_learned_pairwise(const double *pos, const double *mass, const 
     pa.tie = 1e-12 * L;
     pa.tie32 = (float)(0.5 * L * (1.0 - 1e-6));
     pa.N = (int)N;
-    pa.G = (int)((N + kOwn * kSubs - 1) / (kOwn * kSubs));
-    pa.Gp = pa.G + (pa.G & 1);
-    pa.round = 0;
-    const int nb = (int)((N + 255) / 256);
-    hipLaunchKernelGGL(lp_stage_kernel, dim3(nb), dim3(256), 0, stream, pos, mass, eps, (int)N, L, perm, rec);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = out_pot ? launch_learned_pairwise<true>(pa, stream) : launch_learned_pairwise<false>(pa, stream);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(lp_finish_kernel, dim3(nb), dim3(256), 0, stream, pa.acc, perm, (int)N, out_acc,
-                           out_acc + N, out_acc + 2 * N, out_pot);
-        e = hipGetLastError();
-    }
+    hipError_t e = launch_stage(pos, mass, eps, (int)N, L, perm, rec, box, stream);
+    if (e == hipSuccess)
+        e = each_launch(sch, (int)N, kOwn, [&](const Rounds &rd, unsigned blocks) {
+            pa.rd = rd;
+            if (out_pot)
+                hipLaunchKernelGGL((forces_learned_pairwise_kernel<true>), dim3(blocks), dim3(kBlock), 0, stream, pa);
+            else
+                hipLaunchKernelGGL((forces_learned_pairwise_kernel<false>), dim3(blocks), dim3(kBlock), 0, stream, pa);
+            return hipGetLastError();
+        });
+    if (e == hipSuccess) e = launch_finish(sch, pa.acc, kOwn, perm, (int)N, out_acc, out_pot, stream);
     return hip_status(e, "forces_learned_pairwise launch");
 }
 

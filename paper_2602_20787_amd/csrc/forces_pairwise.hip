@@ -10,26 +10,8 @@
 // pair once halves the arithmetic of the per-target kernels
 // (forces_exact.hip, table.hip).
 //
-// Layout.  The particles are put in spatial (Morton) order (above kSortMin;
-// fewer keep their own order) and staged as 32-byte records {x, y, z wrapped,
-// m, h}, with a bounding box per run of 64 records.  A part is 64 consecutive
-// records, a group S parts.  Each particle has M sets of S slots of FP64 sums
-// (x, y, z, potential).
-//
-// Schedule (bitwise deterministic, no atomics).  G groups meet in G' rounds
-// (G' = G rounded up to even): in round 0 every group meets itself, and
-// rounds 1 .. G'-1 are a round-robin tournament: in round r + 1 group G'-1
-// meets group r and, for k = 1 .. G'/2 - 1, group (r + k) mod (G'-1) meets
-// group (r - k) mod (G'-1), so every unordered pair of groups meets exactly
-// once and no group appears twice in a round.  A meeting of groups a and b
-// takes S^2 tiles: tile (i, j) holds part i of a in registers and streams
-// part j of b, adding a's sums into slot j of part i and b's reactions into
-// slot i of part j.  A group meets itself in the S (S + 1)/2 tiles i <= j;
-// tile (i, i) is one-sided and adds to slot i alone.  So within a round each
-// slot has one writer.  A launch runs up to M rounds, each in a slot set of
-// its own; the first launch writes its sets (zeros where a partner is
-// missing), later ones add to them in launch order.  A last pass adds the
-// slots in order and writes FP32 outputs at the particles' own positions.
+// Layout and schedule: pair_schedule.h, with parts of 64 records (kSortMin: few
+// particles keep their own order).
 //
 // What bounds a call is the number of waves in flight: a wave alone takes 37
 // us for its 64 steps at |n| <= 8 where five on its SIMD take 15 us each, and
@@ -56,6 +38,7 @@
 #include "common.h"
 #include "pair_f64.h"
 #include "pair_fp32.h"
+#include "pair_schedule.h"
 #include "table_pair.h"
 
 namespace steps {
@@ -64,7 +47,6 @@ namespace {
 
 constexpr int kThreads = 64;  // one wave
 constexpr int kPart = 64;     // particles per part, one per lane
-constexpr int kBox = 8;       // doubles per 64-record box
 // The one-launch form up to this many particles.  Per call (us, |n| <= 8 with
 // the potential), one launch against tiles: N = 500 13 and 50, 1000 13 and 38,
 // 2000 29 and 40, 2500 47 and 42.
@@ -90,11 +72,8 @@ struct PairwiseArgs {
     ImageConsts c;
     TableView tv;  // far-image table (table paths only)
     float invLf, invL2f;
-    int N, G, Gp;  // particles, groups, groups rounded up to even
-    int S, Q;      // parts per group, waves per tile (Q > 1: one group only)
-    int round;     // first round of this launch (0: the groups' own meetings)
-    int first;     // the slots are written, not added to
-    unsigned own;  // workgroups of round 0 in this launch
+    int N;
+    Rounds rd;  // this launch's meetings
 };
 
 // Exact band 2 <= |n| <= n_far of one pair in one lane (delta = d/L signed,
@@ -114,87 +93,6 @@ __device__ __noinline__ void band_serial(float delta, float r, int n_far, float 
     }
     fz = sz;
     fr = sr;
-}
-
-// Records in the order of `perm` (null: the particles' own) and the bounding
-// box {x_lo, x_hi, y_lo, y_hi, z_lo, z_hi, h_max, 0} of every aligned run of
-// 64; one wave per run.
-__global__ __launch_bounds__(256) void stage_kernel(const double *pos, const double *mass, const double *eps, int N,
-                                                    double L, const int *perm, SrcRec *rec, double *box) {
-    const int b = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const int64_t k = (int64_t)b * 64 + (threadIdx.x & 63);
-    if ((int64_t)b * 64 >= N) return;  // whole wave leaves together
-    double v[7];
-    if (k < N) {
-        const int64_t p = perm ? perm[k] : k;
-        SrcRec r;
-        r.x = pos[p];
-        r.y = pos[N + p];
-        r.z = wrap_z(pos[2 * (int64_t)N + p], L);
-        r.m = (float)mass[p];
-        r.h = (float)eps[p];
-        rec[k] = r;
-        v[0] = r.x;
-        v[1] = -r.x;
-        v[2] = r.y;
-        v[3] = -r.y;
-        v[4] = r.z;
-        v[5] = -r.z;
-        v[6] = (double)r.h;
-    } else {
-        for (int c = 0; c < 6; ++c) v[c] = HUGE_VAL;  // neutral for the minima
-        v[6] = 0.0;
-    }
-    // minima of (x, -x, y, -y, z, -z), maximum of h, over the wave
-    for (int off = 32; off >= 1; off >>= 1) {
-        for (int c = 0; c < 6; ++c) v[c] = fmin(v[c], __shfl_xor(v[c], off));
-        v[6] = fmax(v[6], __shfl_xor(v[6], off));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        double *o = box + (int64_t)b * kBox;
-        o[0] = v[0];
-        o[1] = -v[1];
-        o[2] = v[2];
-        o[3] = -v[3];
-        o[4] = v[4];
-        o[5] = -v[5];
-        o[6] = v[6];
-        o[7] = 0.0;
-    }
-}
-
-// One component of the 64 particles of a part per workgroup, whose waves take
-// equal runs of the slots (added in order, then the runs in order): few
-// particles have many slots, and what bounds the pass is the loads in flight
-// (N = 4096, 128 slots: 17 us with one thread per particle, 4.6 us in 16 runs).  With
-// Q > 1 waves per tile (one group) slot o Q + q is written for every q where
-// the particle's own part p <= o acted, and for q = 0 alone where it reacted.
-__global__ __launch_bounds__(1024) void finish_kernel(const double *sum, int slots, int Q, const int *perm, int N,
-                                                      float *ax, float *ay, float *az, float *pot) {
-    __shared__ double run[16][kPart];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    const int part = blockIdx.x, c = blockIdx.y;
-    const int k = part * kPart + lane;
-    double s = 0.0;
-    if (k < N) {
-        const double *p = sum + (int64_t)c * N + k;
-        const int64_t stride = 4 * (int64_t)N;
-        const int skip = Q > 1 ? part : 0;  // parts that hold one slot
-        const int total = skip + (slots - skip) * Q;
-        const int each = (total + waves - 1) / waves;
-        const int end = min(total, (wave + 1) * each);
-#pragma unroll 8
-        for (int e = wave * each; e < end; ++e) s += p[(e < skip ? e * Q : skip * Q + (e - skip)) * stride];
-    }
-    run[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && k < N) {
-        for (int w = 1; w < waves; ++w) s += run[w][lane];
-        const int64_t i = perm ? perm[k] : k;
-        // attraction: a = -sum m_j S (x_i - x_j), potential = -sum m_j / r
-        float *out = c == 0 ? ax : c == 1 ? ay : c == 2 ? az : pot;
-        out[i] = (float)(-s);
-    }
 }
 
 // a wave's particle
@@ -508,47 +406,16 @@ template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairwise_kernel(PairwiseArgs a) {
     __shared__ Stage st;
     const int lane = threadIdx.x;
-    const int S = a.S, Q = a.Q;
-    int ga, gb, pi, pj, q = 0, set = 0;
-    const bool own = blockIdx.x < a.own;
-    if (own) {
-        const unsigned T = (unsigned)S * (S + 1) / 2;
-        const unsigned tile = blockIdx.x / Q;
-        q = (int)(blockIdx.x % Q);
-        ga = gb = (int)(tile / T);
-        const unsigned t = tile % T;  // column-wise: t = j (j + 1)/2 + i, i <= j
-        pj = (int)((__builtin_sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-        while ((unsigned)(pj + 1) * (pj + 2) / 2 <= t) ++pj;
-        while ((unsigned)pj * (pj + 1) / 2 > t) --pj;
-        pi = (int)(t - (unsigned)pj * (pj + 1) / 2);
-    } else {
-        const unsigned w = blockIdx.x - a.own;
-        const unsigned per = (unsigned)S * S, half = a.Gp / 2;
-        const unsigned meeting = w / per;
-        const int meet = (int)(meeting % half);
-        const int k = (int)(meeting / half);  // rounds of the launch, in order
-        set = k + (a.own ? 1 : 0);
-        const int round = a.round + set - 1;
-        const int M = a.Gp - 1;
-        if (meet == 0) {
-            ga = M;
-            gb = round;
-        } else {
-            ga = (round + meet) % M;
-            gb = (round - meet + M) % M;
-        }
-        pi = (int)((w % per) / S);
-        pj = (int)((w % per) % S);
-    }
-    const int n = kPart / Q;  // sources of the tile
-    const int64_t g0 = ga < a.G ? ((int64_t)ga * S + pi) * kPart : a.N;               // first owned record
-    const int64_t b0 = gb < a.G ? ((int64_t)gb * S + pj) * kPart + q * n : a.N;       // first source record
-    const int ocnt = (int)max((int64_t)0, min((int64_t)kPart, (int64_t)a.N - g0));    // owned records
-    const int cnt = (int)max((int64_t)0, min((int64_t)n, (int64_t)a.N - b0));         // sources
-    const bool react = !own || pi != pj;
+    const Tile t = tile_of_block(a.rd);
+    const int n = kPart / a.rd.Q;  // sources of the tile
+    const int64_t g0 = min((int64_t)a.N, (int64_t)t.pa * kPart);                // first owned record
+    const int64_t b0 = min((int64_t)a.N, (int64_t)t.pb * kPart + t.q * n);      // first source record
+    const int ocnt = (int)min((int64_t)kPart, (int64_t)a.N - g0);               // owned records
+    const int cnt = (int)min((int64_t)n, (int64_t)a.N - b0);                    // sources
+    const bool react = t.pa != t.pb;
     // the owned particles' slot and the sources'
-    double *pa = a.sum + ((int64_t)(set * S + pj) * Q + q) * 4 * a.N + g0;
-    double *pb = a.sum + (int64_t)(set * S + pi) * Q * 4 * a.N + b0;
+    double *pa = a.sum + (int64_t)t.slot_a * 4 * a.N + g0;
+    double *pb = a.sum + (int64_t)t.slot_b * 4 * a.N + b0;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     int out = lane;
     if (ocnt > 0 && cnt > 0) {
@@ -593,18 +460,18 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
                 for (int e = n; e < kPart; e += n) v += st.r[c][out + e];
                 if (c < 3) v = -v;
                 double *p = pb + (int64_t)c * a.N;
-                p[out] = a.first ? v : p[out] + v;
+                p[out] = a.rd.first ? v : p[out] + v;
             }
         }
-    } else if (a.first && react && lane < cnt) {
+    } else if (a.rd.first && react && lane < cnt) {
 #pragma unroll
         for (int c = 0; c < (POT ? 4 : 3); ++c) pb[(int64_t)c * a.N + lane] = 0.0;
     }
-    if (out < ocnt && (a.first || cnt > 0)) {
+    if (out < ocnt && (a.rd.first || cnt > 0)) {
 #pragma unroll
         for (int c = 0; c < (POT ? 4 : 3); ++c) {
             double *p = pa + (int64_t)c * a.N;
-            p[out] = a.first ? acc[c] : p[out] + acc[c];
+            p[out] = a.rd.first ? acc[c] : p[out] + acc[c];
         }
     }
 }
@@ -617,20 +484,13 @@ struct Launcher {
         return hipGetLastError();
     }
 
-    static hipError_t run(PairwiseArgs a, int sets, hipStream_t stream) {
-        const int rounds = a.G > 1 ? a.Gp : 1;
-        hipError_t e = hipSuccess;
-        for (int r = 0; e == hipSuccess && r < rounds; r += sets) {
-            const int k = std::min(sets, rounds - r);
-            a.round = r;
-            a.first = r == 0;
-            a.own = r == 0 ? (unsigned)a.G * a.S * (a.S + 1) / 2 * a.Q : 0;
-            const unsigned meet = (unsigned)(k - (r == 0)) * (a.Gp / 2) * a.S * a.S;
-            hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE>), dim3(a.own + meet),
-                               dim3(kThreads), 0, stream, a);
-            e = hipGetLastError();
-        }
-        return e;
+    static hipError_t run(PairwiseArgs a, const Schedule &s, hipStream_t stream) {
+        return each_launch(s, a.N, kPart, [&](const Rounds &rd, unsigned blocks) {
+            a.rd = rd;
+            hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE>), dim3(blocks), dim3(kThreads), 0,
+                               stream, a);
+            return hipGetLastError();
+        });
     }
 };
 
@@ -670,49 +530,15 @@ auto dispatch(int n_img, bool pot, int order, bool complete, F &&f) {
 
 namespace {
 
-// Below this many particles the parts are runs of the particles' own order:
-// what the order saves in near tiles is less than the 60 us that sorting costs
-// (us per call without and with it: N = 8000 167 and 200, 12000 339 and 352;
-// with a CIC table 148 and 171, 283 and 284).
-constexpr int64_t kSortMin = 10240;
-
-// Bytes of FP64 sum slots of a call.  Up to kScratchN particles the slots (and
-// what else a call takes) fit the 128 MiB array of steps_cyl_forces_noalloc,
-// which then runs the same schedule; above, twice as many rounds share a launch.
-constexpr int64_t kScratchN = 125000;
-constexpr size_t kSlotBytesScratch = (size_t)112 << 20, kSlotBytes = (size_t)256 << 20;
-constexpr size_t kSetBytes = 32;  // per particle and slot
-
-struct Schedule {
-    int S, M, Q;  // parts per group, slot sets, waves per tile
-};
-
 Schedule pairwise_schedule(int64_t N, size_t budget) {
-    Schedule s;
-    const int64_t P = (N + kPart - 1) / kPart;
-    if (budget == 0) budget = N <= kScratchN ? kSlotBytesScratch : kSlotBytes;
-    if (N <= kScratchN && (size_t)P * N * kSetBytes <= budget) {
-        // flat: one group, one launch; tiles split while they would not fill
-        // the device (us per call at Q = 1, 2, 4: N = 2800 49, 43, 43; 4096
-        // 78, 70, 68; 6000 114, 103, 110; 8000 166, 162, 168)
-        const int64_t tiles = P * (P + 1) / 2;
-        s.S = (int)P;
-        s.M = 1;
-        s.Q = tiles <= 1024 ? 4 : tiles <= 8192 ? 2 : 1;
-        return s;
-    }
-    // groups of 16 parts (8 above 2^21 particles, where a call has enough
-    // meetings and the slots would grow past 1 GiB), fewer only where a
-    // smaller budget asks for it; as many sets as fit
-    s.Q = 1;
-    s.S = N <= ((int64_t)1 << 21) ? 16 : 8;
-    const bool fixed = budget < kSlotBytes && N > kScratchN;  // the static array's
-    while (fixed && s.S > 1 && (size_t)s.S * N * kSetBytes > budget) s.S >>= 1;
-    s.M = (int)std::max<int64_t>(1, (int64_t)(budget / ((size_t)s.S * N * kSetBytes)));
-    const int64_t G = (P + s.S - 1) / s.S;
-    const int rounds = G > 1 ? (int)(G + (G & 1)) : 1;
-    const int launches = (rounds + s.M - 1) / s.M;
-    s.M = (rounds + launches - 1) / launches;  // launches of equal length, every set written by the first
+    // groups of 16 parts, 8 above 2^21 particles, where a call has enough
+    // meetings and the slots would grow past 1 GiB
+    Schedule s = make_schedule(N, kPart, N <= ((int64_t)1 << 21) ? 16 : 8, budget);
+    // flat: tiles split while they would not fill the device (us per call at
+    // Q = 1, 2, 4: N = 2800 49, 43, 43; 4096 78, 70, 68; 6000 114, 103, 110;
+    // 8000 166, 162, 168)
+    const int64_t tiles = (int64_t)s.S * (s.S + 1) / 2;
+    if (s.flat) s.Q = tiles <= 1024 ? 4 : tiles <= 8192 ? 2 : 1;
     return s;
 }
 
@@ -720,7 +546,7 @@ size_t schedule_bytes(int64_t N, const Schedule &s) {
     if (N <= kSmallMax) return 0;
     const int64_t nbox = (N + 63) / 64;
     return ws_total({N >= kSortMin ? order_targets_bytes(N) : 0, (size_t)N * sizeof(SrcRec),
-                     (size_t)nbox * kBox * sizeof(double), (size_t)s.S * s.M * s.Q * N * kSetBytes});
+                     (size_t)nbox * kBox * sizeof(double), slot_bytes(s, N)});
 }
 
 }  // namespace
@@ -737,7 +563,6 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     const Schedule sch = pairwise_schedule(N, slot_budget);
     int rc = check_workspace(ws, schedule_bytes(N, sch));
     if (rc) return rc;
-    const int group = kPart * sch.S;
     PairwiseArgs a;
     a.L = L;
     a.invL = 1.0 / L;
@@ -753,10 +578,6 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     a.invL2f = (float)(1.0 / (L * L));
     if (table) a.tv = table_view(table);
     a.N = (int)N;
-    a.G = (int)((N + group - 1) / group);
-    a.Gp = a.G + (a.G & 1);
-    a.S = sch.S;
-    a.Q = sch.Q;
     const int ord = table ? order : 0;
     const bool complete = table && table->complete != 0;
 
@@ -775,25 +596,17 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     const int *perm = nullptr;
     if (N >= kSortMin && (rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
     const int64_t nbox = (N + 63) / 64;
-    const size_t slots = (size_t)sch.S * sch.M;
     SrcRec *rec = (SrcRec *)ws.take((size_t)N * sizeof(SrcRec));
     double *box = (double *)ws.take((size_t)nbox * kBox * sizeof(double));
-    double *sum = (double *)ws.take(slots * sch.Q * N * kSetBytes);
+    double *sum = (double *)ws.take(slot_bytes(sch, N));
     if (!rec || !box || !sum) return fail(STEPS_EINVAL, "workspace too small for the pairwise path");
     a.rec = rec;
     a.box = box;
     a.sum = sum;
-    hipLaunchKernelGGL(stage_kernel, dim3((unsigned)((nbox + 3) / 4)), dim3(256), 0, stream, pos, mass, eps, (int)N, L,
-                       perm, rec, box);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_stage(pos, mass, eps, (int)N, L, perm, rec, box, stream);
     if (e == hipSuccess)
-        e = dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.run(a, sch.M, stream); });
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(finish_kernel, dim3((unsigned)nbox, out_pot ? 4 : 3), dim3(slots * sch.Q > 64 ? 1024 : 256),
-                           0, stream, a.sum, (int)slots, sch.Q, perm, (int)N, out_acc, out_acc + N, out_acc + 2 * N,
-                           out_pot);
-        e = hipGetLastError();
-    }
+        e = dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.run(a, sch, stream); });
+    if (e == hipSuccess) e = launch_finish(sch, a.sum, kPart, perm, (int)N, out_acc, out_pot, stream);
     return hip_status(e, "forces_pairwise launch");
 }
 

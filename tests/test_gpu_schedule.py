@@ -1,4 +1,4 @@
-"""The schedules of the pairwise exact and tabulated paths, at the sizes where
+"""The schedules of the pairwise exact, tabulated and learned paths, at the sizes where
 one gives way to the next: one wave per target, flat tiles split over four, two
 and one waves (parts and tiles full, ragged and nearly empty), sorted and
 unsorted parts, groups meeting over one or several launches with even and odd
@@ -136,6 +136,33 @@ def test_table_schedules(sc, N, order, complete):
     assert rel(acc, ref) <= 2e-5
     assert (torch.abs(pot - ref_pot) / torch.abs(ref_pot)).max().item() <= 2e-5
     tab.close()
+
+
+# tiles over 16, 8, 4, 2 workgroups (ragged parts and source runs), sorted,
+# flat / groups, several groups with one particle in the last
+@pytest.mark.parametrize("N", [1, 2, 129, 1000, 2900, 5000, 5700, 10240, 21632, 21633, 25601])
+def test_learned_schedules(sc, N):
+    print(f"[case] learned N={N}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    pos, m, e = to_dev(p)
+    net = sc.Mlp.create(synth.mlp_init(seed=21, out_gain=1.0))
+    acc, pot = sc.steps_cyl_forces_learned(pos, m, e, p.L, net)
+    nb = sc.steps_cyl_forces_workspace(sc.STEPS_PATH_LEARNED, N, 0, 0, sc.STEPS_SUM_PAIRWISE)
+    ws = torch.full((nb,), 255, dtype=torch.uint8, device="cuda:0")
+    again, pot_again = sc.steps_cyl_forces_learned_ws(pos, m, e, p.L, net, ws)
+    assert torch.equal(acc, again) and torch.equal(pot, pot_again)
+    only, _ = sc.steps_cyl_forces_learned(pos, m, e, p.L, net, potential=False)
+    # the per-target kernel sums the same terms in FP32, 32 at a time: 32
+    # roundings of 6e-8
+    ref, ref_pot = sc.steps_cyl_forces_learned_ex(pos, m, e, p.L, net)
+    if N == 1:
+        assert not acc.any() and not pot.any() and not only.any()
+    else:
+        size = term_sizes(pos, m, e, p.L, 1)
+        for a in (acc, only):
+            assert (torch.linalg.norm(a.double() - ref.double(), dim=0) / size).max().item() <= 2e-6
+        assert (torch.abs(pot - ref_pot) / torch.abs(ref_pot)).max().item() <= 2e-6
+    net.close()
 
 
 @pytest.mark.parametrize("N", [2304, 15296, 100001, 125000, 125001, 300000])
