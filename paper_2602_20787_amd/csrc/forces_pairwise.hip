@@ -34,6 +34,7 @@
 // which hides the latency of the transcendentals (17 reciprocal square
 // roots per pair) and of the LDS traffic behind the other waves' work.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "pair_f64.h"
@@ -97,8 +98,8 @@ __device__ __noinline__ void band_serial(float delta, float r, int n_far, float 
 
 // a wave's particle
 struct Owned {
-    double x, y, z;
-    float h, m;
+    double x, y, z, m;
+    float h;
     int t;  // record index, or N for an empty lane
 };
 
@@ -135,10 +136,17 @@ __device__ __forceinline__ bool far_boxes(const PairwiseArgs &a, const WaveBox &
 }
 
 // LDS of a workgroup: its tile's sources (SoA) and their FP64 reaction slots.
+// The masses are FP32 values; with a table they are held in FP64, which saves a
+// conversion and an address per pair (CIC, N = 131072: 20.6 -> 20.0 ms).  The
+// exact pair keeps them in FP32: 120.6 against 127.3 ms at 262144 particles in
+// clumps, |n| <= 8 with the potential (though 66.3 against 64.8 us at 4096).
+template <int TORDER>
 struct Stage {
+    using Mass = typename std::conditional<(TORDER > 0), double, float>::type;
     double x[64], y[64], z[64];
-    float m[64], h[64];
+    Mass m[64];
     double r[4][64];  // reactions, FP64
+    float h[64];
 };
 
 // Reaction on the source from an evaluated pair, in the owned sums'
@@ -160,13 +168,14 @@ __device__ __forceinline__ double tie_fz(const PairwiseArgs &a, double zi, doubl
 template <int TORDER, bool COMPLETE>
 __device__ __forceinline__ void table_far(const PairwiseArgs &a, float dx, float dy, float d, bool self, float &S,
                                           float &Fz) {
-    const float rho = __builtin_sqrtf(__builtin_fmaf(dx, dx, dy * dy));
+    float rho, rinv;
+    rho_of(__builtin_fmaf(dx, dx, dy * dy), rho, rinv);
     const float rr = rho * a.invLf;
     const float delta = __builtin_fabsf(d) * a.invLf;
     const bool inside = (rr <= a.tv.r_max) && !self;
     float tz, tr;
-    lookup<(TORDER > 0 ? TORDER : 1)>(a.tv, delta, inside ? rr : 0.f, tz, tr);
-    float Rz = (d > 0.f) ? tz : ((d < 0.f) ? -tz : 0.f);
+    lookup<(TORDER > 0 ? TORDER : 1)>(a.tv, delta, rr, tz, tr);
+    float Rz = signed_tz(tz, d);
     float Rr = tr;
     if (!inside) {
         Rz = 0.f;
@@ -192,7 +201,6 @@ __device__ __forceinline__ void table_far(const PairwiseArgs &a, float dx, float
             }
         }
     }
-    const float rinv = rho > 0.f ? __builtin_amdgcn_rcpf(rho) : 0.f;
     S = __builtin_fmaf(-Rr * a.invL2f, rinv, S);
     Fz = __builtin_fmaf(-Rz, a.invL2f, Fz);
 }
@@ -204,7 +212,7 @@ __device__ __forceinline__ void table_far(const PairwiseArgs &a, float dx, float
 // no per-pair floor).  No softening, no half-period screen.  FP32 pair terms,
 // FP64 sums and reactions as in near_pass.
 template <int NIMG, bool POT, int TORDER, bool COMPLETE>
-__device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, Stage &st, int n, double kL,
+__device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, Stage<TORDER> &st, int n, double kL,
                                          double *acc) {
     const int lane = threadIdx.x & 63;
     const double zs = o.z - kL;
@@ -305,7 +313,7 @@ __device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, double 
 // `base`, `cnt` of its sources are real) the self pair and the padding are
 // skipped.
 template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool REACT>
-__device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o, Stage &st, int n, int base, int cnt,
+__device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o, Stage<TORDER> &st, int n, int base, int cnt,
                                           float hmax, double *acc) {
     const int lane = threadIdx.x & 63;
     const float hb = o.h + hmax;  // >= h_i + h_j for every source of the tile
@@ -317,12 +325,11 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o,
         src.x = st.x[k];
         src.y = st.y[k];
         src.z = st.z[k];
-        src.m = st.m[k];
         src.h = st.h[k];
         const int ks = k & (n - 1);  // source of the tile
         const bool self = !REACT && (base + ks == o.t || ks >= cnt);
         const PairTerms t = general_pair<NIMG, POT, TORDER, COMPLETE>(a, o.x, o.y, o.z, o.h, src, thr2, wide, self);
-        const double ms = (double)src.m;
+        const double ms = (double)st.m[k];
         double jx = 0.0, jy = 0.0, jz = 0.0, jp = 0.0;
         if (REACT && step > 0) {
             // the slot as the previous lane left it
@@ -404,7 +411,7 @@ __global__ __launch_bounds__(256) void forces_small_kernel(SmallArgs p) {
 // each), then S^2 per meeting of the launch's other rounds.
 template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairwise_kernel(PairwiseArgs a) {
-    __shared__ Stage st;
+    __shared__ Stage<TORDER> st;
     const int lane = threadIdx.x;
     const Tile t = tile_of_block(a.rd);
     const int n = kPart / a.rd.Q;  // sources of the tile
@@ -429,7 +436,7 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
         o.y = rr.y;
         o.z = rr.z;
         o.h = rr.h;
-        o.m = real ? rr.m : 0.f;
+        o.m = real ? (double)rr.m : 0.0;
         // a partly filled tile is padded with massless copies of its first record
         const int ks = lane & (n - 1);
         const bool live = ks < cnt;

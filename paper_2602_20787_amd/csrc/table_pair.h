@@ -85,38 +85,75 @@ __device__ __forceinline__ void band_wave(float delta, float r, int n_far, float
     fr = sr;
 }
 
+// rho and 1/rho of a pair (both 0 on the axis) from one reciprocal square root:
+// the correctly rounded square root and the reciprocal of it took 18 VALU
+// instructions more, of the 107 of a CIC pair in the pairwise kernel.
+__device__ __forceinline__ void rho_of(float rho2, float &rho, float &rinv) {
+    rinv = rho2 >= 1.17549435e-38f ? __builtin_amdgcn_rsqf(rho2) : 0.f;
+    rho = rho2 * rinv;
+}
+
+// The correctly rounded square root: a Newton step on the hardware's reciprocal
+// square root gives it for every x >= 2^-64 (compared with the library's for
+// every such float), in 5 instructions against 19.
+__device__ __forceinline__ float sqrt_exact(float x) {
+    const float q = __builtin_amdgcn_rsqf(x);
+    const float s = x * q;
+    float r = __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * q, s);
+    if (__builtin_expect(!(x >= 0x1p-64f && x < __builtin_inff()), 0)) r = __builtin_sqrtf(x);
+    return r;
+}
+
+// T_z carries the sign of d (odd in d, 0 at d = 0)
+__device__ __forceinline__ float signed_tz(float tz, float d) {
+    const float v = __uint_as_float(__float_as_uint(tz) ^ (__float_as_uint(d) & 0x80000000u));
+    return d != 0.f ? v : 0.f;
+}
+
+// two neighbouring nodes of a row, one load
+struct __attribute__((packed, aligned(8))) NodePair {
+    float2 a, b;
+};
+
+// Byte offsets are 32-bit from uniform row pointers, so that a node costs one
+// multiply-add and its rows share the offset.
+template <class T>
+__device__ __forceinline__ T node_at(const float2 *row, unsigned off) {
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(row) + off);
+}
+
 template <int ORDER>
 __device__ __forceinline__ void lookup(const TableView &a, float delta, float r, float &tz, float &tr) {
     const float x = delta * a.inv_hd, y = r * a.inv_hr;
     tz = 0.f;
     tr = 0.f;
     if (ORDER == 1) {
-        // indices clamped into the table whatever the input (NaN included)
-        const int i0 = max(0, min((int)x, a.n_d - 1)), j0 = max(0, min((int)y, a.n_r - 1));
+        // indices clamped into the table whatever the input (the conversion
+        // saturates, NaN gives 0)
+        const unsigned i0 = min((unsigned)x, (unsigned)(a.n_d - 1)), j0 = min((unsigned)y, (unsigned)(a.n_r - 1));
         const float fx = x - (float)i0, fy = y - (float)j0;
-        const float2 *p = a.T + (j0 + 1) * a.w + (i0 + 1);
-        const float2 v00 = p[0], v10 = p[1], v01 = p[a.w], v11 = p[a.w + 1];
-        const float z0 = __builtin_fmaf(fx, v10.x - v00.x, v00.x), z1 = __builtin_fmaf(fx, v11.x - v01.x, v01.x);
-        const float r0 = __builtin_fmaf(fx, v10.y - v00.y, v00.y), r1 = __builtin_fmaf(fx, v11.y - v01.y, v01.y);
+        const unsigned off = (__umul24(j0, (unsigned)a.w) + i0) * (unsigned)sizeof(float2);
+        const float2 *row = a.T + a.w + 1;
+        const NodePair lo = node_at<NodePair>(row, off), hi = node_at<NodePair>(row + a.w, off);
+        const float z0 = __builtin_fmaf(fx, lo.b.x - lo.a.x, lo.a.x), z1 = __builtin_fmaf(fx, hi.b.x - hi.a.x, hi.a.x);
+        const float r0 = __builtin_fmaf(fx, lo.b.y - lo.a.y, lo.a.y), r1 = __builtin_fmaf(fx, hi.b.y - hi.a.y, hi.a.y);
         tz = __builtin_fmaf(fy, z1 - z0, z0);
         tr = __builtin_fmaf(fy, r1 - r0, r0);
     } else {
-        const int i0 = max(0, min((int)__builtin_rintf(x), a.n_d));
-        const int j0 = max(0, min((int)__builtin_rintf(y), a.n_r));
+        const unsigned i0 = min((unsigned)__builtin_rintf(x), (unsigned)a.n_d);
+        const unsigned j0 = min((unsigned)__builtin_rintf(y), (unsigned)a.n_r);
         const float fx = x - (float)i0, fy = y - (float)j0;
         const float ax0 = 0.5f - fx, ax2 = 0.5f + fx, ay0 = 0.5f - fy, ay2 = 0.5f + fy;
         const float wx[3] = {0.5f * ax0 * ax0, 0.75f - fx * fx, 0.5f * ax2 * ax2};
         const float wy[3] = {0.5f * ay0 * ay0, 0.75f - fy * fy, 0.5f * ay2 * ay2};
-        const float2 *p = a.T + j0 * a.w + i0;  // node (i0 - 1, j0 - 1)
+        const unsigned off = (__umul24(j0, (unsigned)a.w) + i0) * (unsigned)sizeof(float2);  // node (i0 - 1, j0 - 1)
 #pragma unroll
         for (int dj = 0; dj < 3; ++dj) {
-            float rz = 0.f, rr = 0.f;
-#pragma unroll
-            for (int di = 0; di < 3; ++di) {
-                const float2 v = p[dj * a.w + di];
-                rz = __builtin_fmaf(wx[di], v.x, rz);
-                rr = __builtin_fmaf(wx[di], v.y, rr);
-            }
+            const float2 *row = a.T + dj * a.w;
+            const NodePair p = node_at<NodePair>(row, off);
+            const float2 q = node_at<float2>(row + 2, off);
+            const float rz = __builtin_fmaf(wx[2], q.x, __builtin_fmaf(wx[1], p.b.x, wx[0] * p.a.x));
+            const float rr = __builtin_fmaf(wx[2], q.y, __builtin_fmaf(wx[1], p.b.y, wx[0] * p.a.y));
             tz = __builtin_fmaf(wy[dj], rz, tz);
             tr = __builtin_fmaf(wy[dj], rr, tr);
         }
@@ -155,13 +192,13 @@ __device__ __forceinline__ void table_pair(const TableView &a, const PeriodConst
             Pn = g.P;
         }
     }
-    const float rho = __builtin_sqrtf(rho2);
+    const float rho = sqrt_exact(rho2);
     const float r = rho * pc.invLf;
     const float delta = __builtin_fabsf(d) * pc.invLf;
     const bool inside = (r <= a.r_max) && !self;
     float tz, tr;
-    lookup<ORDER>(a, delta, inside ? r : 0.f, tz, tr);
-    float Rz = (d > 0.f) ? tz : ((d < 0.f) ? -tz : 0.f);
+    lookup<ORDER>(a, delta, r, tz, tr);
+    float Rz = signed_tz(tz, d);
     float Rr = tr;
     if (!inside) {
         Rz = 0.f;
