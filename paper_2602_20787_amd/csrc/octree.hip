@@ -24,16 +24,19 @@
 // and stay compact where 64 consecutive particles in key order would not
 // (the key order jumps between distant octants).
 //
-// Walk: one 64-lane wave per group.  The wave walks the depth-first list
-// without a stack: a cell is
-// accepted for the whole group when size^2 < theta^2 d^2 and
-// d^2 > (h_group + h_cell)^2,
-// d the distance (periodic in z) from its centre of mass to the group's
-// bounding box; an accepted cell adds its monopole, an opened leaf its
-// particles, both through the pair interaction of the tabulated scheme
-// (exact images |n| <= 1 plus the table's band).  The decision is
-// wave-uniform, so the lanes never diverge.  Accelerations are rotated
-// back and written in the caller's particle order.
+// Walk: one 64-lane wave per group.  A cell is accepted for the whole group
+// when size^2 < theta^2 d^2 and d^2 > (h_group + h_cell)^2, d the distance
+// (periodic in z) from its centre of mass to the group's bounding box; an
+// accepted cell adds its monopole, an opened leaf its particles, both through
+// the pair interaction of the tabulated scheme (exact images |n| <= 1 plus the
+// table's far images).  The lanes take turns as tests and as targets: the wave
+// keeps the frontier of the walk in depth-first order on an LDS stack, tests
+// its next 64 cells at once (one per lane), replaces the opened ones by their
+// children in place, and hands what lies before the first opened one to a list
+// of cells and leaves that is staged 64 sources at a time in LDS and then
+// evaluated with a target per lane.  The list is in depth-first order and so
+// are the sums.  Accelerations are rotated back and written in the caller's
+// particle order.
 #include <cmath>
 #include <vector>
 
@@ -58,6 +61,14 @@ struct CellRec {
     float q[6];
 };
 
+// what the walk needs of a cell, in build order (children are contiguous)
+struct alignas(64) WalkNode {
+    double cx, cy, cz, hmax, size2;  // centre of mass, largest softening, size^2
+    float m, h;                      // mass and largest softening, FP32
+    int first, count;                // children, or particles with the top bit of count set
+};
+constexpr int kLeafBit = (int)0x80000000u;
+
 }  // namespace
 }  // namespace steps
 
@@ -77,6 +88,9 @@ struct steps_cyl_tree {
     int *c_start = nullptr, *c_count = nullptr, *c_level = nullptr, *c_leaf = nullptr;
     double *c_m = nullptr, *c_mx = nullptr, *c_my = nullptr, *c_mz = nullptr, *c_h = nullptr;
     double *c_q = nullptr;  // [6][cap_cells] quadrupoles (when enabled)
+    int *c_child = nullptr, *c_nchild = nullptr;  // first child and their number (cells that are no leaves)
+    steps::WalkNode *nodes = nullptr;
+    float *node_q = nullptr;  // [cap_cells][8] quadrupoles (when enabled)
     uint64_t *c_key_in = nullptr, *c_key_out = nullptr;
     int *c_id_in = nullptr, *c_id_out = nullptr;
     steps::CellRec *cells = nullptr;  // depth-first
@@ -162,6 +176,11 @@ hipError_t ensure_cells(steps_cyl_tree *t, int64_t n, hipStream_t stream) {
         (void)hipFree(t->c_q);
         t->c_q = nullptr;
         e = hipMalloc(&t->c_q, (size_t)6 * c * sizeof(double));
+        // (the walk's nodes and the child links likewise)
+        if (e == hipSuccess) e = grow(t->nodes, c);
+        if (e == hipSuccess) e = grow(t->node_q, t->quadrupole ? 8 * c : 1);
+        if (e == hipSuccess) e = grow(t->c_child, c);
+        if (e == hipSuccess) e = grow(t->c_nchild, c);
     }
     regrow(t->c_key_in);
     regrow(t->c_key_out);
@@ -295,7 +314,7 @@ __device__ void cell_centre(uint64_t key, int level, const Frame &f, double side
 __global__ void moments_kernel(int off, int n, int child_off, int n_child, const int *c_start, const int *c_count,
                                const int *c_leaf, double *c_m, double *c_mx, double *c_my, double *c_mz, double *c_h,
                                const double *sx, const double *sy, const double *sz, const double *sm,
-                               const double *sh) {
+                               const double *sh, int *c_child, int *c_nchild) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
     const int c = off + k;
@@ -316,13 +335,16 @@ __global__ void moments_kernel(int off, int n, int child_off, int n_child, const
             const int mid = (lo + hi) / 2;
             if (c_start[child_off + mid] < s) lo = mid + 1; else hi = mid;
         }
-        for (int q = child_off + lo; q < child_off + n_child && c_start[q] < e; ++q) {
+        int q = child_off + lo;
+        c_child[c] = q;
+        for (; q < child_off + n_child && c_start[q] < e; ++q) {
             m += c_m[q];
             mx += c_mx[q];
             my += c_my[q];
             mz += c_mz[q];
             h = fmax(h, c_h[q]);
         }
+        c_nchild[c] = q - (child_off + lo);
     }
     c_m[c] = m;
     c_mx[c] = mx;
@@ -383,7 +405,8 @@ __global__ void dfs_cells_kernel(int n, int N, const uint64_t *key, const int *i
                                  const int *c_count, const int *c_level, const int *c_leaf, const double *c_m,
                                  const double *c_mx, const double *c_my, const double *c_mz, const double *c_h,
                                  const double *c_q, int cap, int quad, const uint64_t *pkey, Frame f, double side,
-                                 CellRec *cells, int *cell_level) {
+                                 const int *c_child, const int *c_nchild, CellRec *cells, int *cell_level,
+                                 WalkNode *nodes, float *node_q) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const int c = id[p];
@@ -421,6 +444,19 @@ __global__ void dfs_cells_kernel(int n, int N, const uint64_t *key, const int *i
     for (int a = 0; a < 6; ++a) r.q[a] = quad ? (float)c_q[(size_t)a * cap + c] : 0.f;
     cells[p] = r;
     cell_level[p] = c_level[c];
+    WalkNode w;
+    w.cx = r.cx;
+    w.cy = r.cy;
+    w.cz = r.cz;
+    w.hmax = r.hmax;
+    w.size2 = r.size * r.size;
+    w.m = (float)r.mass;
+    w.h = (float)r.hmax;
+    w.first = r.leaf ? r.start : c_child[c];
+    w.count = r.leaf ? (r.count | kLeafBit) : c_nchild[c];
+    nodes[c] = w;
+    if (quad)
+        for (int a = 0; a < 6; ++a) node_q[(size_t)c * 8 + a] = r.q[a];
 }
 
 // groups packed by cell c (see the file comment); with out < 0 only counted
@@ -474,7 +510,8 @@ __global__ void group_write_kernel(const CellRec *cells, int n, const int *g_cnt
 
 // ---------------------------------------------------------------- walk
 struct WalkArgs {
-    const CellRec *cells;
+    const WalkNode *nodes;
+    const float *node_q;
     const double *sx, *sy, *sz, *sm, *sh;
     const int *idx, *g_start, *g_count;
     float *ax, *ay, *az;
@@ -483,7 +520,7 @@ struct WalkArgs {
     TableView tv;
     PeriodConsts pc;
     double theta2, c, s, corr_step;
-    int N, n_cells, n_groups, n_bins;
+    int n_groups, n_bins;
 };
 
 __device__ __forceinline__ double wave_min(double v) {
@@ -510,13 +547,16 @@ __device__ double box_distance2(double cx, double cy, double cz, const double lo
     return dx * dx + dy * dy + dz * dz;
 }
 
-// size^2 < theta^2 d^2 and d^2 > (h_group + h_cell)^2, compared squared
-__device__ bool accept_cell(const CellRec &r, const double lo[3], const double hi[3], double hg, double theta2,
-                            double L) {
+// size^2 < theta^2 d^2 and d^2 > (h_group + h_cell)^2, compared squared;
+// `far`: no pair of the cell with the group can be softened, by a margin over
+// FP32 rounding
+__device__ bool accept_cell(const WalkNode &r, const double lo[3], const double hi[3], double hg, double theta2,
+                            double L, bool &far) {
 #pragma clang fp contract(off)
     const double d2 = box_distance2(r.cx, r.cy, r.cz, lo, hi, L);
     const double hs = hg + r.hmax;
-    return r.size * r.size < theta2 * d2 && d2 > hs * hs;
+    far = d2 > hs * hs * 1.00001 && hs < 0.49999 * L;
+    return r.size2 < theta2 * d2 && d2 > hs * hs;
 }
 
 // quadrupole term of an accepted cell for the images |n| <= 4 about the
@@ -525,21 +565,21 @@ __device__ bool accept_cell(const CellRec &r, const double lo[3], const double h
 // a += Q s / r^5 - (5/2) (s.Q.s) s / r^7.  Q s_n = Q s_0 - n L Q e_z.
 constexpr int kQuadImages = 4;
 
-__device__ __forceinline__ void quadrupole_term(const CellRec &r, double xi, double yi, double zi,
+__device__ __forceinline__ void quadrupole_term(const SrcRec &r, const float *q, double xi, double yi, double zi,
                                                 const PeriodConsts &pc, float &px, float &py, float &pz) {
-    const float sx = (float)(xi - r.cx), sy = (float)(yi - r.cy);
-    const float d = (float)min_image(zi - r.cz, pc.L, pc.invL);
+    const float sx = (float)(xi - r.x), sy = (float)(yi - r.y);
+    const float d = (float)min_image(zi - r.z, pc.L, pc.invL);
     const float rho2 = __builtin_fmaf(sx, sx, sy * sy);
-    const float bx = __builtin_fmaf(r.q[0], sx, __builtin_fmaf(r.q[3], sy, r.q[4] * d));
-    const float by = __builtin_fmaf(r.q[3], sx, __builtin_fmaf(r.q[1], sy, r.q[5] * d));
-    const float bz = __builtin_fmaf(r.q[4], sx, __builtin_fmaf(r.q[5], sy, r.q[2] * d));
+    const float bx = __builtin_fmaf(q[0], sx, __builtin_fmaf(q[3], sy, q[4] * d));
+    const float by = __builtin_fmaf(q[3], sx, __builtin_fmaf(q[1], sy, q[5] * d));
+    const float bz = __builtin_fmaf(q[4], sx, __builtin_fmaf(q[5], sy, q[2] * d));
 #pragma unroll
     for (int n = -kQuadImages; n <= kQuadImages; ++n) {
         const float nL = (float)n * pc.c.Lf;
         const float sz = d - nL;
-        const float qx = __builtin_fmaf(-nL, r.q[4], bx);
-        const float qy = __builtin_fmaf(-nL, r.q[5], by);
-        const float qz = __builtin_fmaf(-nL, r.q[2], bz);
+        const float qx = __builtin_fmaf(-nL, q[4], bx);
+        const float qy = __builtin_fmaf(-nL, q[5], by);
+        const float qz = __builtin_fmaf(-nL, q[2], bz);
         const float r2 = __builtin_fmaf(sz, sz, rho2);
         const float ri = __builtin_amdgcn_rsqf(r2);
         const float ri2 = ri * ri;
@@ -552,66 +592,209 @@ __device__ __forceinline__ void quadrupole_term(const CellRec &r, double xi, dou
     }
 }
 
+// The frontier: cells still to be tested or resolved, the next in depth-first
+// order on top.  A step pops n of them and pushes at most 8 n, so with
+// n <= (kStack - kStackRest - size)/8 (at least 1) the wide steps stay below
+// kStack - kStackRest, and popping one by one from there adds at most 7 per
+// level: 147 entries.
+constexpr int kStack = 768, kStackRest = 160;
+enum { kOpen = 0, kFar = 1, kNear = 2, kLeaf = 3 };  // kind of an entry, its top two bits
+
+template <bool QUAD>
+struct WalkLds {
+    double box[7];       // the group's bounding box (low, high) and largest softening
+    unsigned stack[kStack];
+    unsigned list[128];  // resolved cells and leaves, in order
+    int start[64];       // a batch: first source of each entry
+    unsigned kind[64];   // and kind | flush << 2 of its last source
+    int first[64];       // and its node or first particle
+    SrcRec src[64];      // a stage of the batch's sources
+    int own[64];         // their particle index (-1: a cell)
+    unsigned flag[64];   // their kind | flush << 2
+    float q[QUAD ? 64 : 1][6];
+};
+
+__device__ __forceinline__ unsigned lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+// Exclusive sum over the lanes of v < 2^BITS; `total` of all.
+template <int BITS>
+__device__ __forceinline__ int small_scan(int v, int &total) {
+    int e = 0;
+    total = 0;
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const uint64_t m = __ballot((v >> b) & 1);
+        e += (int)lanes_below(m) << b;
+        total += __builtin_popcountll(m) << b;
+    }
+    return e;
+}
+
+// Before: a wave tested one cell at a time, all lanes alike, and read sources
+// one at a time from memory (148 VALU instructions per interaction of a wave,
+// 34 of them tests).  N = 2^20, theta 0.5: 15.7 -> WALK_MS ms.
 template <int ORDER, bool QUAD, bool COMPLETE>
-__global__ __launch_bounds__(kBlock) void tree_walk_kernel(WalkArgs a) {
+__global__ __launch_bounds__(kBlock, 5) void tree_walk_kernel(WalkArgs a) {
+    __shared__ WalkLds<QUAD> lds[kBlock / 64];
     const int lane = threadIdx.x & 63;
     const int wave = (int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
-    if (wave >= a.n_groups) return;  // whole wave
+    if (wave >= a.n_groups) return;  // whole wave (and the waves share nothing)
+    WalkLds<QUAD> &w = lds[threadIdx.x >> 6];
     const int g0 = a.g_start[wave];
     const bool active = lane < a.g_count[wave];
     const int i = g0 + lane;
     const int ii = active ? i : g0;
     const double xi = a.sx[ii], yi = a.sy[ii], zi = a.sz[ii];
     const float hi = (float)a.sh[ii];
-    double lo[3] = {wave_min(xi), wave_min(yi), wave_min(zi)};
-    double up[3] = {wave_max(xi), wave_max(yi), wave_max(zi)};
-    const double hg = wave_max(a.sh[ii]);
+    {
+        const double b[7] = {wave_min(xi), wave_min(yi), wave_min(zi), wave_max(xi),
+                             wave_max(yi), wave_max(zi), wave_max(a.sh[ii])};
+        if (lane == 0)
+            for (int c = 0; c < 7; ++c) w.box[c] = b[c];
+    }
     float sx = 0.f, sy = 0.f, sz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
     float px = 0.f, py = 0.f, pz = 0.f, pp = 0.f;
     int pending = 0, n_cell = 0, n_part = 0;
-    int p = 0;
-    while (p < a.n_cells) {
-        const CellRec r = a.cells[p];
-        // every lane evaluates the same FP64 test on the same data
-        const int acc = __builtin_amdgcn_readfirstlane(accept_cell(r, lo, up, hg, a.theta2, a.pc.L) ? 1 : 0);
-        if (acc) {
-            SrcRec src;
-            src.x = r.cx;
-            src.y = r.cy;
-            src.z = r.cz;
-            src.m = (float)r.mass;
-            src.h = (float)r.hmax;
-            table_pair<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, src, false, active, px, py, pz, pp);
-            if (QUAD) quadrupole_term(r, xi, yi, zi, a.pc, px, py, pz);
-            ++n_cell;
-            if (++pending == 16) {
-                kahan_add(sx, cx, px);
-                kahan_add(sy, cy, py);
-                kahan_add(sz, cz, pz);
-                px = py = pz = 0.f;
-                pending = 0;
+    int size = 1, listed = 0;
+    if (lane == 0) w.stack[0] = 0;  // the root, unresolved
+    for (;;) {
+        asm volatile("" ::: "memory");
+        if (listed < 64 && size > 0) {
+            // ---- one step of the frontier
+            const int n = min(min(64, size), max(1, (kStack - kStackRest - size) >> 3));
+            unsigned e = lane < n ? w.stack[size - 1 - lane] : 0u;
+            int first = 0, count = 1;  // what replaces the entry: itself, or `count` children from `first`
+            bool open = false;
+            if (lane < n && (e >> 30) == kOpen) {
+                const WalkNode r = a.nodes[e];
+                bool far;
+                if (accept_cell(r, w.box, w.box + 3, w.box[6], a.theta2, a.pc.L, far)) {
+                    e |= (unsigned)(far ? kFar : kNear) << 30;
+                } else if (r.count < 0) {
+                    e |= (unsigned)kLeaf << 30;
+                } else {
+                    open = true;
+                    first = r.first;
+                    count = r.count;
+                }
             }
-            p = __builtin_amdgcn_readfirstlane(r.skip);
-        } else if (__builtin_amdgcn_readfirstlane(r.leaf)) {
-            const int e = r.start + r.count;
-            for (int j = r.start; j < e; ++j) {
-                SrcRec src;
-                src.x = a.sx[j];
-                src.y = a.sy[j];
-                src.z = a.sz[j];
-                src.m = (float)a.sm[j];
-                src.h = (float)a.sh[j];
-                table_pair<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, src, j == i, active, px, py, pz, pp);
+            const uint64_t opened = __ballot(open);
+            const int f = opened ? __builtin_ctzll(opened) : n;  // entries that are next in the list
+            if (lane < f) w.list[listed + lane] = e;
+            listed += f;
+            if (lane < f || lane >= n) count = 0;
+            int total;
+            const int before = small_scan<4>(count, total);
+            size += total - n;
+            const int top = size - 1 - before;
+            if (open) {
+                for (int k = 0; k < count; ++k) w.stack[top - k] = (unsigned)(first + k);
+            } else if (count) {
+                w.stack[top] = e;
             }
-            n_part += r.count;
-            kahan_add(sx, cx, px);
-            kahan_add(sy, cy, py);
-            kahan_add(sz, cz, pz);
-            px = py = pz = 0.f;
-            pending = 0;
-            p = __builtin_amdgcn_readfirstlane(r.skip);
+            continue;
+        }
+        if (listed == 0) break;
+        // ---- a batch of the list
+        const int n = min(64, listed);
+        const unsigned e = lane < n ? w.list[lane] : 0u;
+        const unsigned next = lane + 64 < listed ? w.list[lane + 64] : 0u;
+        const unsigned kind = e >> 30;
+        const bool leaf = lane < n && kind == kLeaf;
+        int first = (int)(e & 0x3fffffffu), count = lane < n ? 1 : 0;
+        if (leaf) {
+            const WalkNode &r = a.nodes[first];
+            first = r.first;
+            count = r.count & ~kLeafBit;
+        }
+        // the partial sums are flushed after a leaf and after 16 cells in a row
+        const uint64_t leaves = __ballot(leaf);
+        const uint64_t below = leaves & ((1ull << lane) - 1);
+        const int row = below ? lane - 64 + __builtin_clzll(below) : pending + lane;
+        const bool flush = leaf || (row & 15) == 15;
+        pending = (leaves ? n - 64 + (int)__builtin_clzll(leaves) : pending + n) & 15;
+        int total, start;
+        if (__ballot(count > 127) == 0) {
+            start = small_scan<7>(count, total);
         } else {
-            ++p;
+            int s = count;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int v = __shfl_up(s, off);
+                if (lane >= off) s += v;
+            }
+            start = s - count;
+            total = __shfl(s, 63);
+        }
+        n_cell += n - __builtin_popcountll(leaves);
+        n_part += total - (n - __builtin_popcountll(leaves));
+        w.start[lane] = start;
+        w.kind[lane] = kind | (flush ? 4u : 0u);
+        w.first[lane] = first;
+        if (lane < 64) w.list[lane] = next;
+        listed -= n;
+        for (int base = 0; base < total; base += 64) {
+            asm volatile("" ::: "memory");
+            // ---- stage up to 64 sources
+            const int m = min(64, total - base);
+            if (lane < m) {
+                const int t = base + lane;
+                int k = 0;  // the entry: the last that starts at or before t
+#pragma unroll
+                for (int b = 32; b >= 1; b >>= 1)
+                    if (k + b < n && w.start[k + b] <= t) k += b;
+                const unsigned kd = w.kind[k];
+                const int at = t - w.start[k];
+                SrcRec r;
+                int own = -1;
+                unsigned flag = kd;
+                if ((kd & 3) == kLeaf) {
+                    own = w.first[k] + at;
+                    r.x = a.sx[own];
+                    r.y = a.sy[own];
+                    r.z = a.sz[own];
+                    r.m = (float)a.sm[own];
+                    r.h = (float)a.sh[own];
+                    const int end = k + 1 < n ? w.start[k + 1] : total;
+                    if (t + 1 < end) flag = kLeaf;
+                } else {
+                    const int c = w.first[k];
+                    const WalkNode &q = a.nodes[c];
+                    r.x = q.cx;
+                    r.y = q.cy;
+                    r.z = q.cz;
+                    r.m = q.m;
+                    r.h = q.h;
+                    if (QUAD)
+                        for (int b = 0; b < 6; ++b) w.q[lane][b] = a.node_q[(size_t)c * 8 + b];
+                }
+                w.src[lane] = r;
+                w.own[lane] = own;
+                w.flag[lane] = flag;
+            }
+            asm volatile("" ::: "memory");
+            // ---- and evaluate them, a target per lane
+            for (int s = 0; s < m; ++s) {
+                const SrcRec src = w.src[s];
+                const unsigned flag = __builtin_amdgcn_readfirstlane(w.flag[s]);
+                if ((flag & 3) == kFar) {
+                    table_add<false>(table_terms<ORDER, false, COMPLETE, false>(a.tv, a.pc, xi, yi, zi, hi, src, false,
+                                                                                active),
+                                     src.m, px, py, pz, pp);
+                } else {
+                    table_add<false>(table_terms<ORDER, false, COMPLETE, true>(a.tv, a.pc, xi, yi, zi, hi, src,
+                                                                               w.own[s] == i, active),
+                                     src.m, px, py, pz, pp);
+                }
+                if (QUAD && (flag & 3) != kLeaf) quadrupole_term(src, w.q[QUAD ? s : 0], xi, yi, zi, a.pc, px, py, pz);
+                if (flag & 4) {
+                    kahan_add(sx, cx, px);
+                    kahan_add(sy, cy, py);
+                    kahan_add(sz, cz, pz);
+                    px = py = pz = 0.f;
+                }
+            }
         }
     }
     kahan_add(sx, cx, px);
@@ -773,7 +956,7 @@ int build(steps_cyl_tree *t, const double *pos, const double *mass, const double
         const int co = (l + 1 < n_lev) ? off[l + 1] : 0, cn = (l + 1 < n_lev) ? cnt[l + 1] : 0;
         hipLaunchKernelGGL(moments_kernel, dim3(blocks(cnt[l])), dim3(kBlock), 0, stream, off[l], cnt[l], co, cn,
                            t->c_start, t->c_count, t->c_leaf, t->c_m, t->c_mx, t->c_my, t->c_mz, t->c_h, t->sx, t->sy,
-                           t->sz, t->sm, t->sh);
+                           t->sz, t->sm, t->sh, t->c_child, t->c_nchild);
         TRY(hipGetLastError());
         if (t->quadrupole) {
             hipLaunchKernelGGL(quadrupole_kernel, dim3(blocks(cnt[l])), dim3(kBlock), 0, stream, off[l], cnt[l], co,
@@ -791,8 +974,8 @@ int build(steps_cyl_tree *t, const double *pos, const double *mass, const double
                                            total, 0, 37, stream));
     hipLaunchKernelGGL(dfs_cells_kernel, dim3(blocks(total)), dim3(kBlock), 0, stream, total, n, t->c_key_out,
                        t->c_id_out, t->c_start, t->c_count, t->c_level, t->c_leaf, t->c_m, t->c_mx, t->c_my, t->c_mz,
-                       t->c_h, t->c_q, (int)t->cap_cells, t->quadrupole, t->key_out, f, side, t->cells,
-                       t->cell_level);
+                       t->c_h, t->c_q, (int)t->cap_cells, t->quadrupole, t->key_out, f, side, t->c_child, t->c_nchild,
+                       t->cells, t->cell_level, t->nodes, t->node_q);
     TRY(hipGetLastError());
     // target groups
     hipLaunchKernelGGL(group_count_kernel, dim3(blocks(total)), dim3(kBlock), 0, stream, t->cells, total, t->g_cnt);
@@ -814,7 +997,8 @@ int build(steps_cyl_tree *t, const double *pos, const double *mass, const double
 int walk(steps_cyl_tree *t, const steps_cyl_table *table, int order, double L, double theta, const Frame &f,
          bool correct, float *out_acc, hipStream_t stream) {
     WalkArgs a;
-    a.cells = t->cells;
+    a.nodes = t->nodes;
+    a.node_q = t->node_q;
     a.sx = t->sx;
     a.sy = t->sy;
     a.sz = t->sz;
@@ -837,8 +1021,6 @@ int walk(steps_cyl_tree *t, const steps_cyl_table *table, int order, double L, d
     a.s = f.s;
     a.n_bins = correct ? t->n_bins : 0;
     a.corr_step = t->n_bins ? t->corr_rdom / t->n_bins : 1.0;
-    a.N = (int)t->n;
-    a.n_cells = (int)t->n_cells;
     const int64_t threads = t->n_groups * 64;
     const dim3 grid(blocks(threads)), block(kBlock);
     const int variant = (order == 2 ? 4 : 0) + (t->quadrupole ? 2 : 0) + (a.tv.complete ? 1 : 0);
@@ -887,7 +1069,7 @@ STEPS_API void steps_cyl_tree_destroy(steps_cyl_tree *t) {
     if (!t) return;
     void *ptrs[] = {t->cub_tmp, t->tx, t->ty, t->tz, t->key_in, t->key_out, t->idx_in, t->idx_out, t->sx, t->sy,
                     t->sz, t->sm, t->sh, t->act, t->fs, t->fe, t->ss, t->se, t->c_start, t->c_count, t->c_level,
-                    t->c_leaf, t->c_m, t->c_mx, t->c_my, t->c_mz, t->c_h, t->c_q, t->c_key_in, t->c_key_out, t->c_id_in,
+                    t->c_leaf, t->c_m, t->c_mx, t->c_my, t->c_mz, t->c_h, t->c_q, t->c_child, t->c_nchild, t->nodes, t->node_q, t->c_key_in, t->c_key_out, t->c_id_in,
                     t->c_id_out, t->cells, t->cell_level, t->wave_cells, t->wave_parts, t->corr, t->bin_sum,
                     t->g_cnt, t->g_off, t->g_start, t->g_count,
                     t->bin_cnt, t->acc_dir, t->acc_tree};

@@ -161,35 +161,39 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
 }
 
 
-// One pair of the tabulated scheme, accumulated as (px, py) += m S_eff (dx, dy),
-// pz += m Fz_eff, pp += m P (the caller negates at the end).  Every lane of
+// One pair of the tabulated scheme: S_eff, F_z,eff and (POT) P.  Every lane of
 // the wave must call it together (the exact band beyond a band table's
 // rho_max is shared by the wave); ``active`` marks lanes with a real target.
 // COMPLETE: the table holds every image |n| >= 2 (pairs beyond rho_max take
-// the line-mass limit) rather than a band.
-template <int ORDER, bool POT, bool COMPLETE>
-__device__ __forceinline__ void table_pair(const TableView &a, const PeriodConsts &pc, double xi, double yi,
-                                           double zi, float hi, const SrcRec &src, bool self, bool active,
-                                           float &px, float &py, float &pz, float &pp) {
+// the line-mass limit) rather than a band.  NEAR: the pair may be softened.
+struct TableTerms {
+    float dx, dy, S, Fz, P;
+};
+
+template <int ORDER, bool POT, bool COMPLETE, bool NEAR>
+__device__ __forceinline__ TableTerms table_terms(const TableView &a, const PeriodConsts &pc, double xi, double yi,
+                                                  double zi, float hi, const SrcRec &src, bool self, bool active) {
     const int lane = threadIdx.x & 63;
     const double dx64 = xi - src.x, dy64 = yi - src.y;
     const double d64 = min_image(zi - src.z, pc.L, pc.invL);
     const float dx = (float)dx64, dy = (float)dy64, d = (float)d64;
-    const float hij = hi + src.h;
     float S, Fz, Pn = 0.f;
     pair_fast<1, POT>(dx, dy, d, pc.c, S, Fz, Pn);
     const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
     const float r2_0 = __builtin_fmaf(d, d, rho2);
-    if (r2_0 < hij * hij || hij > (float)pc.halfL) {
+    const float hij = hi + src.h;
+    if (NEAR && (r2_0 < hij * hij || hij > (float)pc.halfL)) {
         if (self) {
             S = 0.f;
             Fz = 0.f;
             Pn = 0.f;
         } else {
-            const PairSums g = pair_general_f64(dx64, dy64, d64, (double)hi + (double)src.h, pc.L, 1);
-            S = g.S;
-            Fz = g.Fz;
-            Pn = g.P;
+            // inlined: a call's register convention would raise the walk from 96 to 131 VGPRs
+            double gs, gf, gp;
+            pair_spline_f64(dx64, dy64, d64, (double)hi + (double)src.h, pc.L, 1, gs, gf, gp);
+            S = (float)gs;
+            Fz = (float)gf;
+            Pn = (float)gp;
         }
     }
     const float rho = sqrt_exact(rho2);
@@ -234,13 +238,18 @@ __device__ __forceinline__ void table_pair(const TableView &a, const PeriodConst
         }
     }
     const float rinv = rho > 0.f ? __builtin_amdgcn_rcpf(rho) : 0.f;
-    const float Seff = __builtin_fmaf(-Rr * pc.invL2f, rinv, S);
-    const float Fzeff = __builtin_fmaf(-Rz, pc.invL2f, Fz);
-    const float mS = src.m * Seff;
-    px = __builtin_fmaf(mS, dx, px);
-    py = __builtin_fmaf(mS, dy, py);
-    pz = __builtin_fmaf(src.m, Fzeff, pz);
-    if (POT) pp = __builtin_fmaf(src.m, Pn, pp);
+    return TableTerms{dx, dy, __builtin_fmaf(-Rr * pc.invL2f, rinv, S), __builtin_fmaf(-Rz, pc.invL2f, Fz), Pn};
+}
+
+// (px, py) += m S_eff (dx, dy), pz += m Fz_eff, pp += m P (the caller negates
+// at the end).
+template <bool POT>
+__device__ __forceinline__ void table_add(const TableTerms &t, float m, float &px, float &py, float &pz, float &pp) {
+    const float mS = m * t.S;
+    px = __builtin_fmaf(mS, t.dx, px);
+    py = __builtin_fmaf(mS, t.dy, py);
+    pz = __builtin_fmaf(m, t.Fz, pz);
+    if (POT) pp = __builtin_fmaf(m, t.P, pp);
 }
 
 }  // namespace steps
