@@ -547,15 +547,20 @@ __device__ double box_distance2(double cx, double cy, double cz, const double lo
     return dx * dx + dy * dy + dz * dz;
 }
 
-// size^2 < theta^2 d^2 and d^2 > (h_group + h_cell)^2, compared squared;
-// `far`: no pair of the cell with the group can be softened, by a margin over
+// no pair at d^2 >= d2 with softening sum <= hs is softened, by a margin over
 // FP32 rounding
+__device__ __forceinline__ bool far_apart(double d2, double hs, double L) {
+    return d2 > hs * hs * 1.00001 && hs < 0.49999 * L;
+}
+
+// size^2 < theta^2 d^2 and d^2 > (h_group + h_cell)^2, compared squared; `far`
+// as above for the cell with the group
 __device__ bool accept_cell(const WalkNode &r, const double lo[3], const double hi[3], double hg, double theta2,
                             double L, bool &far) {
 #pragma clang fp contract(off)
     const double d2 = box_distance2(r.cx, r.cy, r.cz, lo, hi, L);
     const double hs = hg + r.hmax;
-    far = d2 > hs * hs * 1.00001 && hs < 0.49999 * L;
+    far = far_apart(d2, hs, L);
     return r.size2 < theta2 * d2 && d2 > hs * hs;
 }
 
@@ -600,17 +605,22 @@ __device__ __forceinline__ void quadrupole_term(const SrcRec &r, const float *q,
 constexpr int kStack = 768, kStackRest = 160;
 enum { kOpen = 0, kFar = 1, kNear = 2, kLeaf = 3 };  // kind of an entry, its top two bits
 
+struct alignas(16) WalkSrc {
+    SrcRec r;
+    int own;        // its particle index (-1: a cell)
+    unsigned flag;  // its entry's kind, | kFarSrc: no pair with the group is softened, | flush
+};
+constexpr unsigned kFarSrc = 4, kFlush = 8;
+
 template <bool QUAD>
 struct WalkLds {
     double box[7];       // the group's bounding box (low, high) and largest softening
     unsigned stack[kStack];
     unsigned list[128];  // resolved cells and leaves, in order
     int start[64];       // a batch: first source of each entry
-    unsigned kind[64];   // and kind | flush << 2 of its last source
+    unsigned kind[64];   // and the flags of its last source
     int first[64];       // and its node or first particle
-    SrcRec src[64];      // a stage of the batch's sources
-    int own[64];         // their particle index (-1: a cell)
-    unsigned flag[64];   // their kind | flush << 2
+    WalkSrc src[64];     // a stage of the batch's sources
     float q[QUAD ? 64 : 1][6];
 };
 
@@ -632,11 +642,16 @@ __device__ __forceinline__ int small_scan(int v, int &total) {
     return e;
 }
 
+// Waves per SIMD that the registers are bounded for.  CIC at 4 and 5: 12.55 and
+// 12.28 ms at N = 2^20; with quadrupoles at 4 and 3: 4.08 and 3.95 ms a step at
+// N = 100,003, where there are two waves per SIMD in any case.
+constexpr int walk_waves(int order, bool quad) { return quad ? 3 : order == 1 ? 5 : 4; }
+
 // Before: a wave tested one cell at a time, all lanes alike, and read sources
 // one at a time from memory (148 VALU instructions per interaction of a wave,
-// 34 of them tests).  N = 2^20, theta 0.5: 15.7 -> WALK_MS ms.
+// 34 of them tests).  N = 2^20, theta 0.5: 15.7 -> 11.7 ms.
 template <int ORDER, bool QUAD, bool COMPLETE>
-__global__ __launch_bounds__(kBlock, 5) void tree_walk_kernel(WalkArgs a) {
+__global__ __launch_bounds__(kBlock, walk_waves(ORDER, QUAD)) void tree_walk_kernel(WalkArgs a) {
     __shared__ WalkLds<QUAD> lds[kBlock / 64];
     const int lane = threadIdx.x & 63;
     const int wave = (int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
@@ -727,10 +742,11 @@ __global__ __launch_bounds__(kBlock, 5) void tree_walk_kernel(WalkArgs a) {
             start = s - count;
             total = __shfl(s, 63);
         }
+        total = __builtin_amdgcn_readfirstlane(total);
         n_cell += n - __builtin_popcountll(leaves);
         n_part += total - (n - __builtin_popcountll(leaves));
         w.start[lane] = start;
-        w.kind[lane] = kind | (flush ? 4u : 0u);
+        w.kind[lane] = kind | (kind == kFar ? kFarSrc : 0u) | (flush ? kFlush : 0u);
         w.first[lane] = first;
         if (lane < 64) w.list[lane] = next;
         listed -= n;
@@ -758,6 +774,8 @@ __global__ __launch_bounds__(kBlock, 5) void tree_walk_kernel(WalkArgs a) {
                     r.h = (float)a.sh[own];
                     const int end = k + 1 < n ? w.start[k + 1] : total;
                     if (t + 1 < end) flag = kLeaf;
+                    if (far_apart(box_distance2(r.x, r.y, r.z, w.box, w.box + 3, a.pc.L), w.box[6] + a.sh[own], a.pc.L))
+                        flag |= kFarSrc;
                 } else {
                     const int c = w.first[k];
                     const WalkNode &q = a.nodes[c];
@@ -769,31 +787,39 @@ __global__ __launch_bounds__(kBlock, 5) void tree_walk_kernel(WalkArgs a) {
                     if (QUAD)
                         for (int b = 0; b < 6; ++b) w.q[lane][b] = a.node_q[(size_t)c * 8 + b];
                 }
-                w.src[lane] = r;
-                w.own[lane] = own;
-                w.flag[lane] = flag;
+                w.src[lane] = WalkSrc{r, own, flag};
             }
             asm volatile("" ::: "memory");
-            // ---- and evaluate them, a target per lane
-            for (int s = 0; s < m; ++s) {
-                const SrcRec src = w.src[s];
-                const unsigned flag = __builtin_amdgcn_readfirstlane(w.flag[s]);
-                if ((flag & 3) == kFar) {
-                    table_add<false>(table_terms<ORDER, false, COMPLETE, false>(a.tv, a.pc, xi, yi, zi, hi, src, false,
-                                                                                active),
-                                     src.m, px, py, pz, pp);
-                } else {
-                    table_add<false>(table_terms<ORDER, false, COMPLETE, true>(a.tv, a.pc, xi, yi, zi, hi, src,
-                                                                               w.own[s] == i, active),
-                                     src.m, px, py, pz, pp);
-                }
-                if (QUAD && (flag & 3) != kLeaf) quadrupole_term(src, w.q[QUAD ? s : 0], xi, yi, zi, a.pc, px, py, pz);
-                if (flag & 4) {
+            // ---- and evaluate them, a target per lane: two at once where
+            // neither needs a branch, to hide the latency of the table's gathers
+            auto add = [&](const SrcRec &r, const TableTerms &t, unsigned flag, int s) {
+                table_add<false>(t, r.m, px, py, pz, pp);
+                if (QUAD && (flag & 3) != kLeaf) quadrupole_term(r, w.q[QUAD ? s : 0], xi, yi, zi, a.pc, px, py, pz);
+                if (flag & kFlush) {
                     kahan_add(sx, cx, px);
                     kahan_add(sy, cy, py);
                     kahan_add(sz, cz, pz);
                     px = py = pz = 0.f;
                 }
+            };
+            for (int s = 0; s < m;) {
+                const SrcRec r0 = w.src[s].r, r1 = w.src[min(s + 1, m - 1)].r;
+                const unsigned f0 = __builtin_amdgcn_readfirstlane(w.src[s].flag);
+                const unsigned f1 = s + 1 < m ? __builtin_amdgcn_readfirstlane(w.src[s + 1].flag) : 0u;
+                if (f0 & f1 & kFarSrc) {
+                    TableTerms t0, t1;
+                    const bool ok0 = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, r0, t0);
+                    const bool ok1 = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, r1, t1);
+                    if (__ballot(!(ok0 && ok1)) == 0) {
+                        add(r0, t0, f0, s);
+                        add(r1, t1, f1, s + 1);
+                        s += 2;
+                        continue;
+                    }
+                }
+                add(r0, table_terms<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, r0, w.src[s].own == i, active),
+                    f0, s);
+                ++s;
             }
         }
     }

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kBlock) void forces_table_kernel(TableArgs a) {
             for (int s = 0; s < e; ++s) {
                 const SrcRec src = tile[s0 + s];
                 const bool self = (int64_t)(base + s0 + s) == i;
-                table_add<POT>(table_terms<ORDER, POT, COMPLETE, true>(a.tv, a.pc, xi, yi, zi, hi, src, self, active),
+                table_add<POT>(table_terms<ORDER, POT, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, src, self, active),
                                src.m, px, py, pz, pp);
             }
             kahan_add(sx, cx, px);

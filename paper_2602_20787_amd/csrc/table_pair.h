@@ -94,13 +94,19 @@ __device__ __forceinline__ void rho_of(float rho2, float &rho, float &rinv) {
 }
 
 // The correctly rounded square root: a Newton step on the hardware's reciprocal
-// square root gives it for every x >= 2^-64 (compared with the library's for
-// every such float), in 5 instructions against 19.
-__device__ __forceinline__ float sqrt_exact(float x) {
+// square root gives it for every finite x >= 2^-64 (compared with the library's
+// for every such float), in 5 instructions against 19.
+constexpr float kSqrtMin = 0x1p-64f;
+
+__device__ __forceinline__ float sqrt_newton(float x) {
     const float q = __builtin_amdgcn_rsqf(x);
     const float s = x * q;
-    float r = __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * q, s);
-    if (__builtin_expect(!(x >= 0x1p-64f && x < __builtin_inff()), 0)) r = __builtin_sqrtf(x);
+    return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * q, s);
+}
+
+__device__ __forceinline__ float sqrt_exact(float x) {
+    float r = sqrt_newton(x);
+    if (__builtin_expect(!(x >= kSqrtMin && x < __builtin_inff()), 0)) r = __builtin_sqrtf(x);
     return r;
 }
 
@@ -124,6 +130,8 @@ __device__ __forceinline__ T node_at(const float2 *row, unsigned off) {
 
 template <int ORDER>
 __device__ __forceinline__ void lookup(const TableView &a, float delta, float r, float &tz, float &tr) {
+    // the positions in the cell by explicit fused operations: they do not depend
+    // on what the compiler can contract
     const float x = delta * a.inv_hd, y = r * a.inv_hr;
     tz = 0.f;
     tr = 0.f;
@@ -131,7 +139,7 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
         // indices clamped into the table whatever the input (the conversion
         // saturates, NaN gives 0)
         const unsigned i0 = min((unsigned)x, (unsigned)(a.n_d - 1)), j0 = min((unsigned)y, (unsigned)(a.n_r - 1));
-        const float fx = x - (float)i0, fy = y - (float)j0;
+        const float fx = __builtin_fmaf(delta, a.inv_hd, -(float)i0), fy = __builtin_fmaf(r, a.inv_hr, -(float)j0);
         const unsigned off = (__umul24(j0, (unsigned)a.w) + i0) * (unsigned)sizeof(float2);
         const float2 *row = a.T + a.w + 1;
         const NodePair lo = node_at<NodePair>(row, off), hi = node_at<NodePair>(row + a.w, off);
@@ -142,10 +150,10 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
     } else {
         const unsigned i0 = min((unsigned)__builtin_rintf(x), (unsigned)a.n_d);
         const unsigned j0 = min((unsigned)__builtin_rintf(y), (unsigned)a.n_r);
-        const float fx = x - (float)i0, fy = y - (float)j0;
+        const float fx = __builtin_fmaf(delta, a.inv_hd, -(float)i0), fy = __builtin_fmaf(r, a.inv_hr, -(float)j0);
         const float ax0 = 0.5f - fx, ax2 = 0.5f + fx, ay0 = 0.5f - fy, ay2 = 0.5f + fy;
-        const float wx[3] = {0.5f * ax0 * ax0, 0.75f - fx * fx, 0.5f * ax2 * ax2};
-        const float wy[3] = {0.5f * ay0 * ay0, 0.75f - fy * fy, 0.5f * ay2 * ay2};
+        const float wx[3] = {0.5f * ax0 * ax0, __builtin_fmaf(-fx, fx, 0.75f), 0.5f * ax2 * ax2};
+        const float wy[3] = {0.5f * ay0 * ay0, __builtin_fmaf(-fy, fy, 0.75f), 0.5f * ay2 * ay2};
         const unsigned off = (__umul24(j0, (unsigned)a.w) + i0) * (unsigned)sizeof(float2);  // node (i0 - 1, j0 - 1)
 #pragma unroll
         for (int dj = 0; dj < 3; ++dj) {
@@ -161,16 +169,46 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
 }
 
 
-// One pair of the tabulated scheme: S_eff, F_z,eff and (POT) P.  Every lane of
-// the wave must call it together (the exact band beyond a band table's
-// rho_max is shared by the wave); ``active`` marks lanes with a real target.
-// COMPLETE: the table holds every image |n| >= 2 (pairs beyond rho_max take
-// the line-mass limit) rather than a band.  NEAR: the pair may be softened.
 struct TableTerms {
-    float dx, dy, S, Fz, P;
+    float dx, dy, S, Fz, P;  // S_eff, F_z,eff and (POT) P
 };
 
-template <int ORDER, bool POT, bool COMPLETE, bool NEAR>
+// A pair of the tabulated scheme that is not softened, lies inside the table
+// and off the axis: table_terms without its branches, so that several pairs
+// can be in flight at once.  False where it is not such a pair (the terms are
+// then meaningless); the same values, bit for bit, where it is.
+template <int ORDER>
+__device__ __forceinline__ bool table_terms_inside(const TableView &a, const PeriodConsts &pc, double xi, double yi,
+                                                   double zi, const SrcRec &src, TableTerms &t) {
+    const double dx64 = xi - src.x, dy64 = yi - src.y;
+    const double d64 = min_image(zi - src.z, pc.L, pc.invL);
+    const float dx = (float)dx64, dy = (float)dy64, d = (float)d64;
+    const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
+    // pair_fast<1, false> with the contractions the compiler makes of it spelled out
+    const float ri0 = __builtin_amdgcn_rsqf(__builtin_fmaf(d, d, rho2));
+    const float dzp = d - pc.c.Lf, dzm = d + pc.c.Lf;
+    const float rip = __builtin_amdgcn_rsqf(__builtin_fmaf(dzp, dzp, rho2));
+    const float rim = __builtin_amdgcn_rsqf(__builtin_fmaf(dzm, dzm, rho2));
+    const float rip2 = rip * rip, rim3 = rim * rim * rim;
+    const float S = __builtin_fmaf(ri0 * ri0, ri0, __builtin_fmaf(rip2, rip, rim3));
+    const float Fz = __builtin_fmaf(d, S, -pc.c.Lf * __builtin_fmaf(rip2, rip, -rim3));
+    const float rho = sqrt_newton(rho2);
+    const float r = rho * pc.invLf;
+    const float delta = __builtin_fabsf(d) * pc.invLf;
+    float tz, Rr;
+    lookup<ORDER>(a, delta, r, tz, Rr);
+    const float Rz = signed_tz(tz, d);
+    const float rinv = __builtin_amdgcn_rcpf(rho);
+    t = TableTerms{dx, dy, __builtin_fmaf(-Rr * pc.invL2f, rinv, S), __builtin_fmaf(-Rz, pc.invL2f, Fz), 0.f};
+    return r <= a.r_max && rho2 >= kSqrtMin;
+}
+
+// One pair of the tabulated scheme.  Every lane of the wave must call it
+// together (the exact band beyond a band table's rho_max is shared by the
+// wave); ``active`` marks lanes with a real target.  COMPLETE: the table holds
+// every image |n| >= 2 (pairs beyond rho_max take the line-mass limit) rather
+// than a band.
+template <int ORDER, bool POT, bool COMPLETE>
 __device__ __forceinline__ TableTerms table_terms(const TableView &a, const PeriodConsts &pc, double xi, double yi,
                                                   double zi, float hi, const SrcRec &src, bool self, bool active) {
     const int lane = threadIdx.x & 63;
@@ -182,7 +220,7 @@ __device__ __forceinline__ TableTerms table_terms(const TableView &a, const Peri
     const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
     const float r2_0 = __builtin_fmaf(d, d, rho2);
     const float hij = hi + src.h;
-    if (NEAR && (r2_0 < hij * hij || hij > (float)pc.halfL)) {
+    if (r2_0 < hij * hij || hij > (float)pc.halfL) {
         if (self) {
             S = 0.f;
             Fz = 0.f;
