@@ -252,13 +252,13 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_kernel(LearnedArgs a
                 const mlp::Packed &Pl = *reinterpret_cast<const mlp::Packed *>(
                     reinterpret_cast<const char *>(&P) + poff);
                 float oa0, oa1, ob0, ob1;
-                mlp::forward32<false>(Pl, fa1, fa2, oa0, oa1, nullptr, nullptr);
+                mlp::forward32(Pl, fa1, fa2, oa0, oa1);
                 // the two tiles one after the other: one tile's registers
                 // let 3 waves share a SIMD, and the other waves hide the
                 // MFMA and transcendental latency that interleaving the
                 // tiles would
                 __builtin_amdgcn_sched_barrier(0);
-                mlp::forward32<false>(Pl, fb1, fb2, ob0, ob1, nullptr, nullptr);
+                mlp::forward32(Pl, fb1, fb2, ob0, ob1);
                 const float o0 = h ? ob0 : oa0, o1 = h ? ob1 : oa1;
                 const float mz = __builtin_fmaf(q.sc, o0, q.bz);
                 float Rz = (q.d > 0.f) ? mz : ((q.d < 0.f) ? -mz : 0.f);
@@ -579,10 +579,10 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(Pair
             const mlp::Packed &Pl = *reinterpret_cast<const mlp::Packed *>(
                 reinterpret_cast<const char *>(&P) + poff);
             float oa0, oa1, ob0, ob1;
-            mlp::forward32<false>(Pl, fa1, fa2, oa0, oa1, nullptr, nullptr);
+            mlp::forward32(Pl, fa1, fa2, oa0, oa1);
             // one tile after the other (3 waves per SIMD, as the per-target kernel)
             __builtin_amdgcn_sched_barrier(0);
-            mlp::forward32<false>(Pl, fb1, fb2, ob0, ob1, nullptr, nullptr);
+            mlp::forward32(Pl, fb1, fb2, ob0, ob1);
             const float o0 = h ? ob0 : oa0, o1 = h ? ob1 : oa1;
             const float mz = __builtin_fmaf(q.sc, o0, q.bz);
             float Rz = (q.d > 0.f) ? mz : ((q.d < 0.f) ? -mz : 0.f);

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void forward_kernel(const Packed *__restrict__
     const bool ok = s < B;
     const float f1 = ok ? in[s] : 0.f, f2 = ok ? in[B + s] : 0.f;
     float o0, o1;
-    forward32<false>(P, f1, f2, o0, o1, nullptr, nullptr);
+    forward32(P, f1, f2, o0, o1);
     if (ok && lane < 32) {
         out[s] = o0;
         out[B + s] = o1;
@@ -175,155 +175,212 @@ struct TrainArgs {
     int64_t count;          // samples in this batch
     int64_t base;           // first batch slot (for the permutation)
     uint64_t mul, add;      // permutation; mul = 0 selects identity (slot k -> sample k)
-    float *partial;         // [waves][kParams] gradient partials
-    float *loss_partial;    // [waves]
+    float *partial;         // [batches of 32][kParams] gradient partials
+    float *loss_partial;    // [batches of 32]
 };
 
+// One batch of 32 samples takes a workgroup of 4 waves.  As one wave's work the
+// step was a single chain of 5000 instructions, 22 us with a CU idle on three
+// SIMDs; the waves share it by the 64 features of a layer: wave w computes M
+// block w / 2 and keeps rows v = 8 (w mod 2) .. + 7 of it, which are K step w of
+// the next layer, so that a layer passes to the next through one 16-byte LDS
+// chunk per lane and one barrier (14 us).  Every sum runs in the order of
+// the one-wave form.
+constexpr int kTrainWaves = 4;
+
 struct TrainLDS {
-    float z[4][64][kZRow];
-    alignas(16) __bf16 x[3][64][kXRow];
-    float dzf[64][kZRow];
-    alignas(16) __bf16 dzb[64][kXRow];
+    bf16x8 chunk[2][4][64];              // B operand of the layer under way, by K step
+    alignas(16) __bf16 x[3][64][kXRow];  // inputs of layers 2..4, [feature][sample]
+    alignas(16) __bf16 dzb[2][64][kXRow];
+    float dzf[2][64][kZRow];
+    float a4[64][kZRow];
+    float2 w5[2][2][16];
     float dout[2][32];
     float feat[2][32];
 };
 
-__global__ __launch_bounds__(64) void train_kernel(TrainArgs A) {
+// entries 8 s .. 8 s + 7 of a D operand (s wave-uniform)
+__device__ __forceinline__ float part8(const f32x16 &acc, int s, int i) { return s ? acc[8 + i] : acc[i]; }
+
+__global__ __launch_bounds__(64 * kTrainWaves, 1) void train_kernel(TrainArgs A) {
     __shared__ TrainLDS S;
     const Packed &P = *A.P;
     const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int blk = w >> 1, sub = w & 1;  // M block and half of it
     const int h = lane >> 5, col = lane & 31;
-    const int64_t wave = blockIdx.x;
-    const int64_t slot = wave * 32 + col;
+    const int64_t batch = blockIdx.x;
+    const int64_t slot = batch * 32 + col;
     const bool ok = slot < A.count;
     int64_t s = 0;
     if (ok) s = A.mul ? batch_index(slot, A.base, A.mul, A.add, A.n) : slot;
     const float f1 = ok ? A.F[s] : 0.f, f2 = ok ? A.F[A.n + s] : 0.f;
     const float t0 = ok ? A.T[s] : 0.f, t1 = ok ? A.T[A.n + s] : 0.f;
+    // every weight is on its way before the first gradient store: loads and
+    // stores retire in order, so a load behind the stores would wait for them
+    const bf16x8 first = P.A1[blk][lane];
+    bf16x8 fwd[3][4], bwd[3][4];
+    f32x16 bias[4];
+    bias[0] = *reinterpret_cast<const f32x16 *>(&P.Bias1[h][blk][0]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        bias[k + 1] = *reinterpret_cast<const f32x16 *>(&P.Bias[h][k][blk][0]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            fwd[k][t] = P.A[k][blk][t][lane];
+            bwd[k][t] = A.PT->AT[k][blk][t][lane];
+        }
+    }
+    const float b50 = P.b5[0], b51 = P.b5[1];
+    if (threadIdx.x < 64) (&S.w5[0][0][0])[threadIdx.x] = (&P.W5[0][0][0])[threadIdx.x];
+
+    // forward: z of layers 1..4, this wave's rows
+    float z[4][8];
+    bf16x8 xb[4];
+    {
+        __bf16 p0, p1, p2, q0, q1, q2;
+        split3(f1, p0, p1, p2);
+        split3(f2, q0, q1, q2);
+        const __bf16 zero = (__bf16)0.f;
+        bf16x8 xin;
+        xin[0] = h ? zero : p0;
+        xin[1] = h ? zero : p1;
+        xin[2] = h ? zero : p2;
+        xin[3] = h ? zero : q0;
+        xin[4] = h ? zero : q1;
+        xin[5] = h ? zero : q2;
+        xin[6] = zero;
+        xin[7] = zero;
+        const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(first, xin, bias[0], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[0][i] = part8(acc, sub, i);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        bf16x8 mine;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            mine[i] = (__bf16)silu(z[k][i]);
+            S.x[k][drow(blk, 8 * sub + i, h)][col] = mine[i];
+        }
+        S.chunk[k & 1][w][lane] = mine;
+        __syncthreads();
+        f32x16 acc = bias[k + 1];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fwd[k][t], S.chunk[k & 1][t][lane], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[k + 1][i] = part8(acc, sub, i);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) S.a4[drow(blk, 8 * sub + i, h)][col] = silu(z[3][i]);
+    __syncthreads();
+    // layer 5, every wave: half-sums over the lane's 32 rows, then the halves
     float o0, o1;
-    forward32<true>(P, f1, f2, o0, o1, &S.z[0][0][0], &S.x[0][0][0]);
+    {
+        float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float2 c = S.w5[h][b][v];
+                const float a = S.a4[drow(b, v, h)][col];
+                p0 = __builtin_fmaf(c.x, a, p0);
+                p1 = __builtin_fmaf(c.y, a, p1);
+            }
+        const float q0 = __shfl_xor(p0, 32), q1 = __shfl_xor(p1, 32);
+        o0 = (h ? (q0 + p0) : (p0 + q0)) + b50;
+        o1 = (h ? (q1 + p1) : (p1 + q1)) + b51;
+    }
     // loss = mean of squared errors over both outputs and all samples
     const float inv_count = 1.0f / (float)A.count;
     const float e0 = ok ? (o0 - t0) : 0.f, e1 = ok ? (o1 - t1) : 0.f;
     const float d0 = e0 * inv_count, d1 = e1 * inv_count;  // d loss / d o
-    if (h == 0) {
-        S.dout[0][col] = d0;
-        S.dout[1][col] = d1;
-        S.feat[0][col] = f1;
-        S.feat[1][col] = f2;
-    }
-    // loss partial over this wave's samples (lanes of half 0)
-    float l = (h == 0) ? (e0 * e0 + e1 * e1) : 0.f;
-    for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off);
-    __syncthreads();
-    float *G = A.partial + wave * (int64_t)kParams;
-    if (lane == 0) A.loss_partial[wave] = l * 0.5f * inv_count;
-    // layer 5: dW5[c][r] = sum_j dout_c[j] a4[r][j], db5 = sum_j dout_c[j]
-    {
-        const int r = lane;
-        float g0 = 0.f, g1 = 0.f;
-        for (int j = 0; j < 32; ++j) {
-            const float a4 = silu(S.z[3][r][j]);
-            g0 = __builtin_fmaf(S.dout[0][j], a4, g0);
-            g1 = __builtin_fmaf(S.dout[1][j], a4, g1);
+    float *G = A.partial + batch * (int64_t)kParams;
+    if (w == 0) {
+        if (h == 0) {
+            S.dout[0][col] = d0;
+            S.dout[1][col] = d1;
+            S.feat[0][col] = f1;
+            S.feat[1][col] = f2;
         }
-        G[OFF_W5 + r] = g0;
-        G[OFF_W5 + 64 + r] = g1;
-        if (lane < 2) {
-            float b = 0.f;
-            for (int j = 0; j < 32; ++j) b += S.dout[lane][j];
-            G[OFF_B5 + lane] = b;
-        }
+        // loss partial over the samples (lanes of half 0)
+        float l = (h == 0) ? (e0 * e0 + e1 * e1) : 0.f;
+        for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off);
+        if (lane == 0) A.loss_partial[batch] = l * 0.5f * inv_count;
     }
-    // d loss / d z4 in the D layout
-    float dz[2][16];
-    {
-        const float dd0 = S.dout[0][col], dd1 = S.dout[1][col];
+    // d loss / d z4, this wave's rows
+    float dz[8];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = drow(b, v, h);
-                const float2 w5 = P.W5[h][b][v];
-                const float da = __builtin_fmaf(w5.y, dd1, w5.x * dd0);
-                dz[b][v] = da * silu_grad(S.z[3][r][col]);
-            }
+    for (int i = 0; i < 8; ++i) {
+        const float2 c = S.w5[h][blk][8 * sub + i];
+        const float da = __builtin_fmaf(c.y, d1, c.x * d0);
+        dz[i] = da * silu_grad(z[3][i]);
     }
+#pragma unroll
     for (int k = 2; k >= 0; --k) {  // MFMA layers 4, 3, 2
-        __syncthreads();
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = drow(b, v, h);
-                S.dzf[r][col] = dz[b][v];
-                S.dzb[r][col] = (__bf16)dz[b][v];
-            }
-        __syncthreads();
-        // bias gradient: row r = lane, FP32
+        const int buf = k & 1;
         {
-            float g = 0.f;
-            for (int j = 0; j < 32; ++j) g += S.dzf[lane][j];
-            G[OFF_B[k] + lane] = g;
-        }
-        // dW = bf16(dZ) X^T: M = out rows, N = in rows, K = 32 samples
+            bf16x8 mine;
 #pragma unroll
-        for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-            for (int bn = 0; bn < 2; ++bn) {
-                f32x16 acc = (f32x16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
-                                      0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&S.dzb[32 * bm + col][16 * ks + 8 * h]);
-                    const bf16x8 bb = *reinterpret_cast<const bf16x8 *>(&S.x[k][32 * bn + col][16 * ks + 8 * h]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, acc, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int o = drow(bm, v, h), i = 32 * bn + col;
-                    G[OFF_W[k] + o * 64 + i] = acc[v];
-                }
+            for (int i = 0; i < 8; ++i) {
+                const int r = drow(blk, 8 * sub + i, h);
+                mine[i] = (__bf16)dz[i];
+                S.dzf[buf][r][col] = dz[i];
+                S.dzb[buf][r][col] = mine[i];
             }
+            S.chunk[buf][w][lane] = mine;
+        }
+        __syncthreads();
         // dX = W^T bf16(dZ) in the D layout of the previous layer, then through SiLU
-        bf16x8 xb[4];
+        f32x16 dx = (f32x16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < 4; ++t)
+            dx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bwd[k][t], S.chunk[buf][t][lane], dx, 0, 0, 0);
+        // dW = bf16(dZ) X^T: M = out rows (block blk), N = in rows (block sub), K = 32 samples
+        f32x16 dw = (f32x16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) xb[t][e] = (__bf16)dz[t >> 1][8 * (t & 1) + e];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            f32x16 acc = (f32x16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
-                                  0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.PT->AT[k][b][t][lane], xb[t], acc, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = drow(b, v, h);
-                dz[b][v] = acc[v] * silu_grad(S.z[k][r][col]);
-            }
+        for (int ks = 0; ks < 2; ++ks) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&S.dzb[buf][32 * blk + col][16 * ks + 8 * h]);
+            const bf16x8 bb = *reinterpret_cast<const bf16x8 *>(&S.x[k][32 * sub + col][16 * ks + 8 * h]);
+            dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, dw, 0, 0, 0);
         }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dz[i] = part8(dx, sub, i) * silu_grad(z[k][i]);
+        // bias gradient: row r = lane, FP32 (the waves in turn)
+        if (w == k) {
+            float g = 0.f;
+#pragma unroll 8
+            for (int j = 0; j < 32; ++j) g += S.dzf[buf][lane][j];
+            G[OFF_B[k] + lane] = g;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) G[OFF_W[k] + drow(blk, v, h) * 64 + 32 * sub + col] = dw[v];
     }
-    // layer 1: dW1[r][c] = sum_j dz1[r][j] f_c[j], db1[r] = sum_j dz1[r][j]
-    __syncthreads();
+    // layer 1: dW1[r][c] = sum_j dz1[r][j] f_c[j], db1[r] = sum_j dz1[r][j], and
+    // layer 5: dW5[c][r] = sum_j dout_c[j] a4[r][j], db5 = sum_j dout_c[j]
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) S.dzf[drow(b, v, h)][col] = dz[b][v];
+    for (int i = 0; i < 8; ++i) S.dzf[1][drow(blk, 8 * sub + i, h)][col] = dz[i];
     __syncthreads();
-    {
-        const int r = lane;
-        float g0 = 0.f, g1 = 0.f, gb = 0.f;
+    if (w < 2) {
+        float g = 0.f, g5 = 0.f;
+#pragma unroll 8
         for (int j = 0; j < 32; ++j) {
-            const float d = S.dzf[r][j];
-            g0 = __builtin_fmaf(d, S.feat[0][j], g0);
-            g1 = __builtin_fmaf(d, S.feat[1][j], g1);
-            gb += d;
+            g = __builtin_fmaf(S.dzf[1][lane][j], S.feat[w][j], g);
+            g5 = __builtin_fmaf(S.dout[w][j], S.a4[lane][j], g5);
         }
-        G[OFF_W1 + 2 * r] = g0;
-        G[OFF_W1 + 2 * r + 1] = g1;
-        G[OFF_B1 + r] = gb;
+        G[OFF_W1 + 2 * lane + w] = g;
+        G[OFF_W5 + 64 * w + lane] = g5;
+    } else if (w == 2) {
+        float g = 0.f;
+#pragma unroll 8
+        for (int j = 0; j < 32; ++j) g += S.dzf[1][lane][j];
+        G[OFF_B1 + lane] = g;
+    } else if (lane < 2) {
+        float g = 0.f;
+#pragma unroll 8
+        for (int j = 0; j < 32; ++j) g += S.dout[lane][j];
+        G[OFF_B5 + lane] = g;
     }
 }
 
@@ -347,7 +404,7 @@ struct ReduceArgs {
 // is how many of its loads are in flight: 8 waves stage 256 partials of every
 // parameter in LDS, 32 independent loads a lane, and wave 0 then adds them in
 // order from there.  A thread that loads and adds one partial at a time took
-// 74 us for 256 waves (batch 8192), this form takes RED_US us.  The last
+// 74 us for 256 waves (batch 8192), this form takes 6 us.  The last
 // workgroup sums the loss partials alone, in the same order as ever.
 constexpr int kRedCols = 64, kRedWaves = 8, kRedRows = 256;
 
@@ -366,13 +423,10 @@ __global__ __launch_bounds__(64 * kRedWaves) void reduce_kernel(ReduceArgs R) {
         float v[kRedRows / kRedWaves];
 #pragma unroll
         for (int i = 0; i < kRedRows / kRedWaves; ++i) {
-            const int64_t r = w0 + wave + kRedWaves * i;
-            v[i] = 0.f;
-            if (loss) {
-                if (r * kRedCols + col < R.waves) v[i] = R.loss_partial[r * kRedCols + col];
-            } else if (ok && r < rows) {
-                v[i] = R.partial[r * (int64_t)kParams + p];
-            }
+            // past the end: some partial, not added (every load unconditional)
+            const int64_t r = min(w0 + wave + kRedWaves * i, rows - 1);
+            v[i] = *(loss ? R.loss_partial + min(r * kRedCols + col, R.waves - 1)
+                          : R.partial + r * (int64_t)kParams + min(p, kParams - 1));
         }
 #pragma unroll
         for (int i = 0; i < kRedRows / kRedWaves; ++i) tile[wave + kRedWaves * i][col] = v[i];
@@ -385,7 +439,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void reduce_kernel(ReduceArgs R) {
                 for (int q = 0; q < m; ++q) g += t[q];
             }
         } else if (wave == 0) {
-#pragma unroll 8
+#pragma unroll 32
             for (int q = 0; q < n; ++q) g += tile[q][col];
         }
     }
@@ -448,7 +502,7 @@ int launch_train(steps_cyl_mlp *net, const float *F, const float *T, int64_t n, 
     A.partial = partial;
     A.loss_partial = loss_partial;
     const int64_t waves = (count + 31) / 32;
-    hipLaunchKernelGGL(train_kernel, dim3((unsigned)waves), dim3(64), 0, stream, A);
+    hipLaunchKernelGGL(train_kernel, dim3((unsigned)waves), dim3(64 * kTrainWaves), 0, stream, A);
     return hip_status(hipGetLastError(), "mlp train kernel");
 }
 

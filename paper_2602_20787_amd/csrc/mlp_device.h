@@ -106,23 +106,18 @@ __device__ __forceinline__ void split3(float f, __bf16 &hi, __bf16 &mid, __bf16 
     lo = (__bf16)(r1 - (float)mid);
 }
 
-// LDS row lengths of the captured [feature][sample] arrays, 32 samples and
-// padding: the backward pass also reads them by feature (lane = row), where a
-// row of 32 would put all 64 lanes on one bank.  FP32 rows are one word longer;
-// BF16 rows stay multiples of 16 bytes for the MFMA operand loads, 16 rows of
-// which then cover the 64 banks once.
+// LDS row lengths of the training kernel's [feature][sample] arrays, 32 samples
+// and padding: they are also read by feature (lane = row), where a row of 32
+// would put all 64 lanes on one bank.  FP32 rows are one word longer; BF16 rows
+// stay multiples of 16 bytes for the MFMA operand loads, 16 rows of which then
+// cover the 64 banks once.
 constexpr int kZRow = 33, kXRow = 40;
 
 // Forward pass for the 32 samples of a wave.  Lanes l and l+32 both carry
 // the features (f1, f2) of sample l%32 and both return its outputs (o0, o1).
-// With CAPTURE, the pre-activations of layers 1..4 (zc, [4][64][kZRow] FP32)
-// and the BF16 inputs of layers 2..4 (xc, [3][64][kXRow]) are stored in
-// [feature][sample] layout (sample = column l%32) for the backward pass.
-template <bool CAPTURE>
-__device__ __forceinline__ void forward32(const Packed &P, float f1, float f2, float &o0, float &o1,
-                                          float *zc, __bf16 *xc) {
+__device__ __forceinline__ void forward32(const Packed &P, float f1, float f2, float &o0, float &o1) {
     const int lane = threadIdx.x & 63;
-    const int h = lane >> 5, col = lane & 31;
+    const int h = lane >> 5;
     bf16x8 xb[4];
     const float(*Bias)[2][16] = P.Bias[h];
     const float2(*W5)[16] = P.W5[h];
@@ -153,13 +148,7 @@ __device__ __forceinline__ void forward32(const Packed &P, float f1, float f2, f
         for (int b = 0; b < 2; ++b) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int r = drow(b, v, h);
-                const float z = acc1[b][v];
-                xb[2 * b + (v >> 3)][v & 7] = (__bf16)silu(z);
-                if (CAPTURE) {
-                    zc[r * kZRow + col] = z;
-                    xc[r * kXRow + col] = xb[2 * b + (v >> 3)][v & 7];
-                }
+                xb[2 * b + (v >> 3)][v & 7] = (__bf16)silu(acc1[b][v]);
             }
         }
     }
@@ -179,13 +168,9 @@ __device__ __forceinline__ void forward32(const Packed &P, float f1, float f2, f
         for (int b = 0; b < 2; ++b) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int r = drow(b, v, h);
-                const float z = acc[b][v];
-                const float a = silu(z);
-                if (CAPTURE) zc[((k + 1) * 64 + r) * kZRow + col] = z;
+                const float a = silu(acc[b][v]);
                 if (k < 2) {
                     xb[2 * b + (v >> 3)][v & 7] = (__bf16)a;
-                    if (CAPTURE) xc[((k + 1) * 64 + r) * kXRow + col] = xb[2 * b + (v >> 3)][v & 7];
                 } else {
                     a4[b][v] = a;
                 }
