@@ -45,12 +45,13 @@
  *    the workspace.
  *  - Short target lists: when a per-target call's target blocks alone would
  *    not fill the device, the sources are split into C chunks of at least
- *    4096 (C = min(ceil(2048 / target blocks), ceil(N / 4096)), target blocks
- *    of 256 targets, 128 with a network); each chunk's compensated totals go
- *    to the workspace in FP64 (32 C bytes per target) and are added in chunk
- *    order.  Results are deterministic, and two calls on the same particles
- *    give a target bit for bit the same result whenever they take the same
- *    C (always for N <= 4096); otherwise they agree to FP32 rounding.
+ *    m (C = min(ceil(8192 / target blocks), ceil(N / m)), m = 256 sources and
+ *    target blocks of 256 targets, with a network 1024 and 128); each chunk's
+ *    compensated totals go to the workspace in FP64 (32 C bytes per target)
+ *    and are added in a fixed order.  Results are deterministic, and two calls
+ *    on the same particles give a target bit for bit the same result whenever
+ *    they take the same C (always for N <= 4096 and lists of up to 131,072
+ *    targets); otherwise they agree to FP32 rounding.
  *  - Every call is asynchronous on `stream` (0 = the null stream); results
  *    are valid after the stream is synchronised.  Argument errors are found
  *    on the host before any device work and return a negative status; the

@@ -33,7 +33,7 @@
 // Short target lists.  When the target blocks alone would leave the device
 // idle, the sources are split into chunks too (a grid of target blocks x
 // source chunks): each workgroup writes its compensated totals in FP64 to
-// the workspace and a second pass adds the chunks in order.  The chunking
+// the workspace and a second pass adds the chunks in a fixed order.  The chunking
 // depends only on the list's length and N, so results stay deterministic;
 // lists long enough to fill the device take one chunk and the direct write.
 #include <algorithm>
@@ -41,6 +41,7 @@
 #include "common.h"
 #include "pair_f64.h"
 #include "pair_fp32.h"
+#include "pair_schedule.h"
 
 namespace steps {
 
@@ -100,7 +101,8 @@ __global__ __launch_bounds__(kBlock) void forces_exact_kernel(ExactArgs a) {
         const float hb = hi + hmax;        // >= h_i + h_j for every source in the tile
         const float thr2 = hb * hb;        // rounding is monotonic: >= (h_i + h_j)^2
         const bool wide = hb > (float)a.halfL;
-        const int cnt = min(kBlock, j1 - base);
+        // a wave without targets only stages
+        const int cnt = (k - (tid & 63)) < a.n_tgt ? min(kBlock, j1 - base) : 0;
         for (int s0 = 0; s0 < cnt; s0 += kSub) {
             const int e = min(kSub, cnt - s0);
             float px = 0.f, py = 0.f, pz = 0.f, pp = 0.f;
@@ -169,21 +171,6 @@ __global__ __launch_bounds__(kBlock) void forces_exact_kernel(ExactArgs a) {
     }
 }
 
-// Chunk totals of a short target list added in chunk order (FP64), negated
-// and written as FP32.
-__global__ void exact_chunks_kernel(const double *part, int chunks, int n_tgt, float *ax, float *ay, float *az,
-                                    float *pot) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_tgt) return;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int c = 0; c < chunks; ++c)
-        for (int q = 0; q < 4; ++q) v[q] += part[((int64_t)c * 4 + q) * n_tgt + k];
-    ax[k] = (float)(-v[0]);
-    ay[k] = (float)(-v[1]);
-    az[k] = (float)(-v[2]);
-    if (pot) pot[k] = (float)(-v[3]);
-}
-
 template <int NIMG, bool POT, bool COMP>
 hipError_t launch_t(const ExactArgs &a, hipStream_t stream) {
     const int grid = (a.n_tgt + kBlock - 1) / kBlock;
@@ -207,19 +194,23 @@ hipError_t launch_nimg(const ExactArgs &a, hipStream_t stream) {
 }  // namespace
 
 // Source chunks of the per-target kernels for n_tgt targets of N sources:
-// enough (target block, chunk) pairs for 2048 workgroups, chunks of at least
-// 4096 sources; one chunk once the targets fill the device.
-int per_target_chunks(int64_t N, int64_t n_tgt, int block) {
+// enough (target block, chunk) pairs for 8192 workgroups (eight to a CU's
+// four resident ones, so that the last to finish cost little), chunks of at
+// least min_chunk sources; one chunk once the targets fill the device.  The
+// exact kernel's us per call with 2048 workgroups and 4096 sources, and now:
+// 256 of 262144 particles 1428 -> 321, 4096 of them 4215 -> 3945, 1000 of
+// 50000 1365 -> 282, 300 of 10000 484 -> 50.
+int per_target_chunks(int64_t N, int64_t n_tgt, int block, int min_chunk) {
     const int64_t tblocks = (n_tgt + block - 1) / block;
-    int64_t c = (2048 + tblocks - 1) / tblocks;
-    c = std::min<int64_t>(c, (N + 4095) / 4096);
+    int64_t c = (8192 + tblocks - 1) / tblocks;
+    c = std::min<int64_t>(c, (N + min_chunk - 1) / min_chunk);
     return (int)std::max<int64_t>(1, c);
 }
 
 // Workspace of the per-target exact kernel: the spatial order of a long
 // list, and the chunk totals of a short one.
 size_t exact_per_target_bytes(int64_t N, int64_t n_tgt) {
-    const int chunks = per_target_chunks(N, n_tgt, kBlock);
+    const int chunks = per_target_chunks(N, n_tgt, kBlock, kBlock);
     return ws_total({per_target_bytes(n_tgt), chunks > 1 ? (size_t)chunks * 4 * n_tgt * sizeof(double) : 0});
 }
 
@@ -253,7 +244,7 @@ int launch_forces_exact(const double *pos, const double *mass, const double *eps
     if (rc) return rc;
     if (n_tgt >= kOrderTargetsMin && (rc = order_targets(pos, N, L, targets, n_tgt, stream, ws, &a.perm)))
         return rc;
-    const int chunks = per_target_chunks(N, n_tgt, kBlock);
+    const int chunks = per_target_chunks(N, n_tgt, kBlock, kBlock);
     a.chunk = (int)N;
     a.part = nullptr;
     if (chunks > 1) {
@@ -268,10 +259,8 @@ int launch_forces_exact(const double *pos, const double *mass, const double *eps
     else
         e = comp ? launch_nimg<false, true>(a, stream) : launch_nimg<false, false>(a, stream);
     if (e == hipSuccess && a.part) {
-        const int nch = (int)((N + a.chunk - 1) / a.chunk);
-        hipLaunchKernelGGL(exact_chunks_kernel, dim3((unsigned)((n_tgt + 255) / 256)), dim3(256), 0, stream, a.part,
-                           nch, (int)n_tgt, out_acc, out_acc + n_tgt, out_acc + 2 * n_tgt, out_pot);
-        e = hipGetLastError();
+        const Schedule sch = {(int)((N + a.chunk - 1) / a.chunk), 1, 1, true};  // a slot per chunk
+        e = launch_finish(sch, a.part, kBlock, nullptr, (int)n_tgt, out_acc, out_pot, stream);
     }
     return hip_status(e, "forces_exact launch");
 }

@@ -35,6 +35,7 @@ constexpr int kBlock = 256;     // 4 waves
 constexpr int kTargets = 128;   // targets per workgroup (32 per wave)
 constexpr int kTile = 256;      // sources per LDS tile
 constexpr int kSub = 32;        // sources per compensated flush
+constexpr int kMinChunk = 1024;  // sources per chunk of a short list (a workgroup also loads the network)
 
 // The band 2 <= |n| <= 1024 of a pair near the axis (rho < 0.05 L), where the
 // network is not defined, as a convergent series rather than 2046 image
@@ -313,21 +314,6 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_kernel(LearnedArgs a
     }
 }
 
-// Chunk totals of a short target list added in chunk order (FP64), negated
-// and written as FP32.
-__global__ void learned_chunks_kernel(const double *part, int chunks, int n_tgt, float *ax, float *ay, float *az,
-                                      float *pot) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_tgt) return;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int c = 0; c < chunks; ++c)
-        for (int q = 0; q < 4; ++q) v[q] += part[((int64_t)c * 4 + q) * n_tgt + k];
-    ax[k] = (float)(-v[0]);
-    ay[k] = (float)(-v[1]);
-    az[k] = (float)(-v[2]);
-    if (pot) pot[k] = (float)(-v[3]);
-}
-
 template <bool POT, bool COMP>
 hipError_t launch_t(const LearnedArgs &a, hipStream_t stream) {
     const int grid = (a.n_tgt + kTargets - 1) / kTargets;
@@ -342,13 +328,13 @@ namespace mlp {
 const Packed *packed_of(const steps_cyl_mlp *net);
 }
 
-int per_target_chunks(int64_t N, int64_t n_tgt, int block);
+int per_target_chunks(int64_t N, int64_t n_tgt, int block, int min_chunk);
 
 // Workspace of the per-target learned kernel: the spatial order of a long
 // list and the chunk totals of a short one (sources split into chunks when
 // the target blocks alone would leave the device idle; see forces_exact.hip).
 size_t learned_per_target_bytes(int64_t N, int64_t n_tgt) {
-    const int chunks = per_target_chunks(N, n_tgt, kTargets);
+    const int chunks = per_target_chunks(N, n_tgt, kTargets, kMinChunk);
     return ws_total({per_target_bytes(n_tgt), chunks > 1 ? (size_t)chunks * 4 * n_tgt * sizeof(double) : 0});
 }
 
@@ -441,7 +427,7 @@ int launch_forces_learned(const double *pos, const double *mass, const double *e
     if (rc) return rc;
     if (n_tgt >= kOrderTargetsMin && (rc = order_targets(pos, N, L, targets, n_tgt, stream, ws, &a.perm)))
         return rc;
-    const int chunks = per_target_chunks(N, n_tgt, kTargets);
+    const int chunks = per_target_chunks(N, n_tgt, kTargets, kMinChunk);
     a.chunk = (int)N;
     a.part = nullptr;
     if (chunks > 1) {
@@ -456,10 +442,8 @@ int launch_forces_learned(const double *pos, const double *mass, const double *e
     else
         e = comp ? launch_t<false, true>(a, stream) : launch_t<false, false>(a, stream);
     if (e == hipSuccess && a.part) {
-        const int nch = (int)((N + a.chunk - 1) / a.chunk);
-        hipLaunchKernelGGL(learned_chunks_kernel, dim3((unsigned)((n_tgt + 255) / 256)), dim3(256), 0, stream,
-                           a.part, nch, (int)n_tgt, out_acc, out_acc + n_tgt, out_acc + 2 * n_tgt, out_pot);
-        e = hipGetLastError();
+        const Schedule sch = {(int)((N + a.chunk - 1) / a.chunk), 1, 1, true};  // a slot per chunk
+        e = launch_finish(sch, a.part, kTargets, nullptr, (int)n_tgt, out_acc, out_pot, stream);
     }
     return hip_status(e, "forces_learned launch");
 }

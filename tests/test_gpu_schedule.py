@@ -165,6 +165,31 @@ def test_learned_schedules(sc, N):
     net.close()
 
 
+# target blocks and source chunks: full, ragged and nearly empty, one and many
+@pytest.mark.parametrize("N,T", [(1, 1), (255, 1), (256, 64), (257, 65), (1000, 255), (1025, 257), (20011, 300),
+                                 (40000, 4097)])
+def test_short_target_lists(sc, N, T):
+    print(f"[case] N={N} T={T}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    pos, m, e = to_dev(p)
+    t = torch.from_numpy(np.random.default_rng(T).choice(N, size=T, replace=False).astype(np.int64)).cuda()
+    net = sc.Mlp.create(synth.mlp_init(seed=21, out_gain=1.0))
+    acc, pot = sc.steps_cyl_forces_ex(pos, m, e, p.L, 2, targets=t)
+    far, far_pot = sc.steps_cyl_forces_learned_ex(pos, m, e, p.L, net, targets=t)
+    ref, ref_pot = sc.steps_cyl_forces_f64(pos, m, e, p.L, 2, targets=t)
+    full, full_pot = sc.steps_cyl_forces_learned(pos, m, e, p.L, net)
+    if N == 1:
+        assert not acc.any() and not pot.any() and not far.any() and not far_pot.any()
+    else:
+        # FP32 sums of 32 terms: 32 roundings of 6e-8, and the terms' own 5e-7
+        size, pairs = term_sizes(pos, m, e, p.L, 2)[t], ((acc, ref, pot, ref_pot),
+                                                         (far, full[:, t], far_pot, full_pot[t]))
+        for a, r, q, rq in pairs:
+            assert (torch.linalg.norm(a.double() - r.double(), dim=0) / size).max().item() <= 2.5e-6
+            assert (torch.abs(q.double() - rq.double()) / torch.abs(rq.double())).max().item() <= 2.5e-6
+    net.close()
+
+
 @pytest.mark.parametrize("N", [2304, 15296, 100001, 125000, 125001, 300000])
 def test_static_scratch_runs_the_same_schedule(sc, N):
     # bit for bit up to 125,000 particles; above, other sums of the same terms
