@@ -45,6 +45,7 @@
 // are the sums.  Accelerations are rotated back and written in the caller's
 // particle order.
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include <rocprim/device/device_radix_sort.hpp>
@@ -59,6 +60,9 @@ constexpr int kLevels = 21;
 constexpr int kBlock = 256;
 constexpr int kMaxBins = 256;
 constexpr int kGroup = 64;
+// The walk's waves share nothing: workgroups of one are dealt out evenly (N =
+// 2^20 11.3 -> 10.8 ms, with quadrupoles 22.6 -> 21.0, against workgroups of four).
+constexpr int kWalkBlock = 64;
 
 // one cell in depth-first order (88 B): monopole, and the traceless
 // quadrupole about the centre of mass (xx, yy, zz, xy, xz, yz) when enabled
@@ -582,6 +586,29 @@ __device__ __forceinline__ void quadrupole_term(const SrcRec &r, const float *q,
     }
 }
 
+// v of the lanes' F groups of 64 / F, in every lane: out[k] is the value that
+// lane k (64 / F) + lane mod (64 / F) holds.
+template <int F>
+__device__ __forceinline__ void spread(float v, float *out) {
+    if (F == 1) {
+        out[0] = v;
+    } else {
+        const unsigned u = __float_as_uint(v);
+        const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        if (F == 2) {
+            out[0] = __uint_as_float(h[0]);
+            out[1] = __uint_as_float(h[1]);
+        } else {
+            const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+            const auto up = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+            out[0] = __uint_as_float(lo[0]);
+            out[1 % F] = __uint_as_float(lo[1]);
+            out[2 % F] = __uint_as_float(up[0]);
+            out[3 % F] = __uint_as_float(up[1]);
+        }
+    }
+}
+
 // The frontier: cells still to be tested or resolved, the next in depth-first
 // order on top.  A step pops n of them and pushes at most 8 n, so with
 // n <= (kStack - kStackRest - size)/8 (at least 1) the wide steps stay below
@@ -630,32 +657,47 @@ __device__ __forceinline__ int small_scan(int v, int &total) {
 // Waves per SIMD that the registers are bounded for.  CIC at 4 and 5: 12.55 and
 // 12.28 ms at N = 2^20; with quadrupoles at 4 and 3: 4.08 and 3.95 ms a step at
 // N = 100,003, where there are two waves per SIMD in any case.
-constexpr int walk_waves(int order, bool quad) { return quad ? 3 : order == 1 ? 5 : 4; }
+constexpr int walk_waves(int order, bool quad, int split) {
+    return split > 1 ? 2 : quad ? 3 : order == 1 ? 5 : 4;
+}
 
-// Before: a wave tested one cell at a time, all lanes alike, and read sources
-// one at a time from memory (148 VALU instructions per interaction of a wave,
-// 34 of them tests).  N = 2^20, theta 0.5: 15.7 -> 11.7 ms.
-template <int ORDER, bool QUAD, bool COMPLETE>
-__global__ __launch_bounds__(kBlock, walk_waves(ORDER, QUAD)) void tree_walk_kernel(WalkArgs a) {
-    __shared__ WalkLds<QUAD> lds[kBlock / 64];
+// A wave tested one cell at a time, all lanes alike, and read sources one at a
+// time from memory (148 VALU instructions per interaction of a wave, 34 of them
+// tests; N = 2^20, theta 0.5: 15.7 -> 11.0 ms).
+//
+// SPLIT waves per group, each for 64 / SPLIT of its targets: the lanes then hold
+// them SPLIT times over, take one of SPLIT sources each and hand each other the
+// terms, which every lane adds in order.  A source costs a wave less and a group
+// more: this is for trees of few groups, which leave SIMDs idle (see walk()).  Not
+// with quadrupoles, whose 36 terms per cell cost more to hand over than to repeat.
+template <int ORDER, bool QUAD, bool COMPLETE, int SPLIT>
+__global__ __launch_bounds__(kWalkBlock, walk_waves(ORDER, QUAD, SPLIT)) void tree_walk_kernel(WalkArgs a) {
+    static_assert(SPLIT == 1 || !QUAD, "quadrupoles take whole groups");
+    __shared__ WalkLds<QUAD> lds[kWalkBlock / 64];
+    constexpr int kOwned = 64 / SPLIT;  // targets of a wave
     const int lane = threadIdx.x & 63;
-    const int wave = (int)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
-    if (wave >= a.n_groups) return;  // whole wave (and the waves share nothing)
+    const int64_t wave = ((int64_t)blockIdx.x * kWalkBlock + threadIdx.x) >> 6;
+    const int group = (int)(wave / SPLIT), slice = (int)(wave % SPLIT);
+    if (group >= a.n_groups) return;  // whole wave (and the waves share nothing)
     WalkLds<QUAD> &w = lds[threadIdx.x >> 6];
-    const int g0 = a.g_start[wave];
-    const bool active = lane < a.g_count[wave];
-    const int i = g0 + lane;
-    const int ii = active ? i : g0;
-    const double xi = a.sx[ii], yi = a.sy[ii], zi = a.sz[ii];
-    const float hi = (float)a.sh[ii];
+    const int g0 = a.g_start[group], g_n = a.g_count[group];
+    if (slice * kOwned >= g_n) return;
     {
-        const double b[7] = {wave_min(xi), wave_min(yi), wave_min(zi), wave_max(xi),
-                             wave_max(yi), wave_max(zi), wave_max(a.sh[ii])};
+        const int j = g0 + min(lane, g_n - 1);
+        const double x = a.sx[j], y = a.sy[j], z = a.sz[j];
+        const double b[7] = {wave_min(x), wave_min(y), wave_min(z), wave_max(x),
+                             wave_max(y), wave_max(z), wave_max(a.sh[j])};
         if (lane == 0)
             for (int c = 0; c < 7; ++c) w.box[c] = b[c];
     }
+    const int own = slice * kOwned + lane % kOwned;
+    const bool active = own < g_n;
+    const int i = g0 + own;
+    const int ii = active ? i : g0;
+    const double xi = a.sx[ii], yi = a.sy[ii], zi = a.sz[ii];
+    const float hi = (float)a.sh[ii];
     float sx = 0.f, sy = 0.f, sz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
-    float px = 0.f, py = 0.f, pz = 0.f, pp = 0.f;
+    float px = 0.f, py = 0.f, pz = 0.f;
     int pending = 0, n_cell = 0, n_part = 0;
     int size = 1, listed = 0;
     if (lane == 0) w.stack[0] = 0;  // the root, unresolved
@@ -775,11 +817,13 @@ __global__ __launch_bounds__(kBlock, walk_waves(ORDER, QUAD)) void tree_walk_ker
                 w.src[lane] = WalkSrc{r, own, flag};
             }
             asm volatile("" ::: "memory");
-            // ---- and evaluate them, a target per lane: two at once where
-            // neither needs a branch, to hide the latency of the table's gathers
-            auto add = [&](const SrcRec &r, const TableTerms &t, unsigned flag, int s) {
-                table_add<false>(t, r.m, px, py, pz, pp);
-                if (QUAD && (flag & 3) != kLeaf) quadrupole_term(r, w.q[QUAD ? s : 0], xi, yi, zi, a.pc, px, py, pz);
+            // ---- and evaluate them
+            auto add = [&](float mS, float m, float dx, float dy, float Fz) {
+                px = __builtin_fmaf(mS, dx, px);
+                py = __builtin_fmaf(mS, dy, py);
+                pz = __builtin_fmaf(m, Fz, pz);
+            };
+            auto flush = [&](unsigned flag) {
                 if (flag & kFlush) {
                     kahan_add(sx, cx, px);
                     kahan_add(sy, cy, py);
@@ -787,35 +831,68 @@ __global__ __launch_bounds__(kBlock, walk_waves(ORDER, QUAD)) void tree_walk_ker
                     px = py = pz = 0.f;
                 }
             };
-            for (int s = 0; s < m;) {
-                const SrcRec r0 = w.src[s].r, r1 = w.src[min(s + 1, m - 1)].r;
-                const unsigned f0 = __builtin_amdgcn_readfirstlane(w.src[s].flag);
-                const unsigned f1 = s + 1 < m ? __builtin_amdgcn_readfirstlane(w.src[s + 1].flag) : 0u;
-                if (f0 & f1 & kFarSrc) {
-                    TableTerms t0, t1;
-                    const bool ok0 = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, r0, t0);
-                    const bool ok1 = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, r1, t1);
-                    if (__ballot(!(ok0 && ok1)) == 0) {
-                        add(r0, t0, f0, s);
-                        add(r1, t1, f1, s + 1);
-                        s += 2;
-                        continue;
+            if (SPLIT == 1) {
+                // a target per lane: two sources at once where neither needs a
+                // branch, to hide the latency of the table's gathers
+                auto one = [&](const SrcRec &r, const TableTerms &t, unsigned flag, int s) {
+                    add(r.m * t.S, r.m, t.dx, t.dy, t.Fz);
+                    if (QUAD && (flag & 3) != kLeaf) quadrupole_term(r, w.q[QUAD ? s : 0], xi, yi, zi, a.pc, px, py, pz);
+                    flush(flag);
+                };
+                for (int s = 0; s < m;) {
+                    const SrcRec r0 = w.src[s].r, r1 = w.src[min(s + 1, m - 1)].r;
+                    const unsigned f0 = __builtin_amdgcn_readfirstlane(w.src[s].flag);
+                    const unsigned f1 = s + 1 < m ? __builtin_amdgcn_readfirstlane(w.src[s + 1].flag) : 0u;
+                    if (f0 & f1 & kFarSrc) {
+                        TableTerms t0, t1;
+                        const bool ok0 = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, r0, t0);
+                        const bool ok1 = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, r1, t1);
+                        if (__ballot(!(ok0 && ok1)) == 0) {
+                            one(r0, t0, f0, s);
+                            one(r1, t1, f1, s + 1);
+                            s += 2;
+                            continue;
+                        }
+                    }
+                    one(r0, table_terms<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, r0, w.src[s].own == i,
+                                                                active),
+                        f0, s);
+                    ++s;
+                }
+            } else {
+                // this lane's source of each SPLIT, the terms added in order
+                for (int s = 0; s < m; s += SPLIT) {
+                    const int mine = min(s + lane / kOwned, m - 1);
+                    const WalkSrc src = w.src[mine];
+                    TableTerms t;
+                    bool ok = (src.flag & kFarSrc) != 0;
+                    if (__ballot(!ok) == 0) ok = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, src.r, t);
+                    if (__ballot(!ok) != 0)
+                        t = table_terms<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, src.r, src.own == i, active);
+                    float mS[SPLIT], mm[SPLIT], dx[SPLIT], dy[SPLIT], Fz[SPLIT];
+                    spread<SPLIT>(src.r.m * t.S, mS);
+                    spread<SPLIT>(src.r.m, mm);
+                    spread<SPLIT>(t.dx, dx);
+                    spread<SPLIT>(t.dy, dy);
+                    spread<SPLIT>(t.Fz, Fz);
+#pragma unroll
+                    for (int k = 0; k < SPLIT; ++k) {
+                        if (s + k >= m) break;
+                        add(mS[k], mm[k], dx[k], dy[k], Fz[k]);
+                        flush(__builtin_amdgcn_readfirstlane(w.src[s + k].flag));
                     }
                 }
-                add(r0, table_terms<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, r0, w.src[s].own == i, active),
-                    f0, s);
-                ++s;
             }
         }
     }
     kahan_add(sx, cx, px);
     kahan_add(sy, cy, py);
     kahan_add(sz, cz, pz);
-    if (lane == 0) {
-        a.wave_cells[wave] = n_cell;
-        a.wave_parts[wave] = n_part;
+    if (wave % SPLIT == 0 && lane == 0) {
+        a.wave_cells[group] = n_cell;
+        a.wave_parts[group] = n_part;
     }
-    if (!active) return;
+    if (!active || lane >= kOwned) return;
     // acceleration in the rotated frame (the sums carry the opposite sign)
     double gx = -(double)(sx - cx), gy = -(double)(sy - cy);
     const float gz = -(sz - cz);
@@ -990,19 +1067,41 @@ int walk(steps_cyl_tree *t, const steps_cyl_table *table, int order, double L, d
     a.s = f.s;
     a.n_bins = correct ? t->n_bins : 0;
     a.corr_step = t->n_bins ? t->corr_rdom / t->n_bins : 1.0;
-    const int64_t threads = t->n_groups * 64;
-    const dim3 grid(blocks(threads)), block(kBlock);
-    const int variant = (order == 2 ? 4 : 0) + (t->quadrupole ? 2 : 0) + (a.tv.complete ? 1 : 0);
-    switch (variant) {
-        case 0: hipLaunchKernelGGL((tree_walk_kernel<1, false, false>), grid, block, 0, stream, a); break;
-        case 1: hipLaunchKernelGGL((tree_walk_kernel<1, false, true>), grid, block, 0, stream, a); break;
-        case 2: hipLaunchKernelGGL((tree_walk_kernel<1, true, false>), grid, block, 0, stream, a); break;
-        case 3: hipLaunchKernelGGL((tree_walk_kernel<1, true, true>), grid, block, 0, stream, a); break;
-        case 4: hipLaunchKernelGGL((tree_walk_kernel<2, false, false>), grid, block, 0, stream, a); break;
-        case 5: hipLaunchKernelGGL((tree_walk_kernel<2, false, true>), grid, block, 0, stream, a); break;
-        case 6: hipLaunchKernelGGL((tree_walk_kernel<2, true, false>), grid, block, 0, stream, a); break;
-        default: hipLaunchKernelGGL((tree_walk_kernel<2, true, true>), grid, block, 0, stream, a); break;
-    }
+    // Waves per group, by the number of groups (about N / 45; there are 1024
+    // SIMDs) and what a source costs.  ms per call at SPLIT 1, 2, 4: CIC N =
+    // 20000 1.41, 1.07, 0.91, 50000 1.66, 1.32, 1.30, 100003 2.08, 1.85, 2.08,
+    // 200000 2.90, 3.01, 3.54; TSC 50000 1.82, 1.20, 1.16, 100003 2.21, 1.84,
+    // 1.87, 400000 5.38, 4.97, 5.77, 2^20 12.3, 12.2, 15.1.
+    const int64_t g = t->n_groups;
+    const int split = t->quadrupole ? 1 : order == 1 ? (g <= 1100 ? 4 : g <= 3300 ? 2 : 1) : (g <= 1600 ? 4 : g <= 16384 ? 2 : 1);
+    const int64_t threads = t->n_groups * 64 * split;
+    const dim3 grid((unsigned)((threads + kWalkBlock - 1) / kWalkBlock)), block(kWalkBlock);
+    auto launch = [&](auto order_c, auto quad_c, auto complete_c) {
+        constexpr int O = decltype(order_c)::value;
+        constexpr bool Q = decltype(quad_c)::value, C = decltype(complete_c)::value;
+        if (Q || split == 1)
+            hipLaunchKernelGGL((tree_walk_kernel<O, Q, C, 1>), grid, block, 0, stream, a);
+        else if (split == 2)
+            hipLaunchKernelGGL((tree_walk_kernel<O, false, C, 2>), grid, block, 0, stream, a);
+        else
+            hipLaunchKernelGGL((tree_walk_kernel<O, false, C, 4>), grid, block, 0, stream, a);
+    };
+    auto with_table = [&](auto order_c, auto quad_c) {
+        if (a.tv.complete)
+            launch(order_c, quad_c, std::true_type{});
+        else
+            launch(order_c, quad_c, std::false_type{});
+    };
+    auto with_quad = [&](auto order_c) {
+        if (t->quadrupole)
+            with_table(order_c, std::true_type{});
+        else
+            with_table(order_c, std::false_type{});
+    };
+    if (order == 2)
+        with_quad(std::integral_constant<int, 2>{});
+    else
+        with_quad(std::integral_constant<int, 1>{});
     return hip_status(hipGetLastError(), "tree walk");
 }
 
