@@ -496,7 +496,7 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_pairwise_kernel(Pair
     __shared__ double jpart[kBlock / 64][4][kOwn];  // per wave, component, entry
     __shared__ BandSeries bands;
     const LearnedArgs &a = pa.la;
-    const Tile tl = tile_of_block(pa.rd);
+    const Tile tl = tile_of(pa.rd, blockIdx.x);
     const int n = kOwn / pa.rd.Q;                                            // sources of the tile
     const int64_t g0 = min((int64_t)pa.N, tl.pa * kOwn);                     // first target
     const int base = (int)min((int64_t)pa.N, tl.pb * kOwn + tl.q * n);       // first source

@@ -107,16 +107,19 @@ struct WaveBox {
     double x0, x1, y0, y1, z0, z1, h;
 };
 
-// True when no pair between the wave's particles (box w) and the records of
-// box b needs the softening or the half-period screen: the boxes are apart by
-// more than the sum of their largest softenings (with that sum below L/2, so
-// that no image n != 0 is softened either) and no axial separation comes
-// near L/2.  Then every axial separation t = z_i - z_j of the two boxes has
-// the same minimum image t - kL, returned as kL.  Evaluated alike by every
-// lane.
-__device__ __forceinline__ bool far_boxes(const PairwiseArgs &a, const WaveBox &w, const double *b, double &kL) {
+// How the pairs between the wave's particles (box w) and the records of box b
+// are evaluated.  kNear: a pair may be softened.  The others: the boxes are
+// apart by more than the sum of their largest softenings (with that sum below
+// L/2, so that no image n != 0 is softened either); kWrap: some axial separation
+// may come near L/2, each pair takes its own minimum image and the half-period
+// screen; kFar: none does, and every axial separation t = z_i - z_j of the two
+// boxes has the same minimum image t - kL, returned as kL.  Evaluated alike by
+// every lane.
+enum { kNear = 0, kWrap = 1, kFar = 2 };
+
+__device__ __forceinline__ int tile_kind(const PairwiseArgs &a, const WaveBox &w, const double *b, double &kL) {
     const double hs = w.h + b[6];
-    if (hs > a.far_h) return false;
+    if (hs > a.far_h) return kNear;
     const double gx = fmax(0.0, fmax(w.x0 - b[1], b[0] - w.x1));
     const double gy = fmax(0.0, fmax(w.y0 - b[3], b[2] - w.y1));
     // axial separations t = z_i - z_j lie in [tl, th], inside (-L, L)
@@ -128,11 +131,12 @@ __device__ __forceinline__ bool far_boxes(const PairwiseArgs &a, const WaveBox &
         const double el = fabs(tl - a.L * rint(tl * a.invL)), eh = fabs(th - a.L * rint(th * a.invL));
         gz = fmin(el, eh);
     }
-    // no separation within 1e-5 L of a half period (the screen is 5e-7 L)
+    if (!(gx * gx + gy * gy + gz * gz > hs * hs * (1.0 + 1e-4) + 1e-300)) return kNear;
+    // a separation within 1e-5 L of a half period (the screen is 5e-7 L)
     const double m = 1e-5 * a.L;
-    if (ceil((tl - m) * a.invL - 0.5) <= floor((th + m) * a.invL - 0.5)) return false;
+    if (ceil((tl - m) * a.invL - 0.5) <= floor((th + m) * a.invL - 0.5)) return kWrap;
     kL = a.L * floor(tl * a.invL + 0.5);
-    return gx * gx + gy * gy + gz * gz > hs * hs * (1.0 + 1e-4) + 1e-300;
+    return kFar;
 }
 
 // LDS of a workgroup: its tile's sources (SoA) and their FP64 reaction slots.
@@ -165,16 +169,16 @@ __device__ __forceinline__ double tie_fz(const PairwiseArgs &a, double zi, doubl
 // added to (S, Fz): R_z is odd in d and R_rho even, so the corrected pair
 // keeps the symmetry of the exact one.  `self`: the pair of a particle with
 // itself (no correction).
-template <int TORDER, bool COMPLETE>
-__device__ __forceinline__ void table_far(const PairwiseArgs &a, float dx, float dy, float d, bool self, float &S,
-                                          float &Fz) {
+template <int TORDER, bool COMPLETE, class Nodes>
+__device__ __forceinline__ void table_far(const PairwiseArgs &a, const Nodes &nodes, float dx, float dy, float d,
+                                          bool self, float &S, float &Fz) {
     float rho, rinv;
     rho_of(__builtin_fmaf(dx, dx, dy * dy), rho, rinv);
     const float rr = rho * a.invLf;
     const float delta = __builtin_fabsf(d) * a.invLf;
     const bool inside = (rr <= a.tv.r_max) && !self;
     float tz, tr;
-    lookup<(TORDER > 0 ? TORDER : 1)>(a.tv, delta, rr, tz, tr);
+    lookup<(TORDER > 0 ? TORDER : 1)>(a.tv, nodes, delta, rr, tz, tr);
     float Rz = signed_tz(tz, d);
     float Rr = tr;
     if (!inside) {
@@ -205,13 +209,14 @@ __device__ __forceinline__ void table_far(const PairwiseArgs &a, float dx, float
     Fz = __builtin_fmaf(-Rz, a.invL2f, Fz);
 }
 
-// One wave's passage over a tile's sources when far_boxes holds (image shift
-// kL): n steps, lane l taking source l xor step.  The separation is the FP64
-// difference of the positions, with the minimum image's shift kL taken off
-// the owned z once per tile, rounded to FP32 (as exact as in near_pass, with
-// no per-pair floor).  No softening, no half-period screen.  FP32 pair terms,
-// FP64 sums and reactions as in near_pass.
-template <int NIMG, bool POT, int TORDER, bool COMPLETE>
+// One wave's passage over a tile's sources where none is softened: n steps, lane
+// l taking source l xor step.  kFar: the separation is the FP64 difference of
+// the positions, with the minimum image's shift kL taken off the owned z once
+// per tile, rounded to FP32 (as exact as in near_pass, with no per-pair floor);
+// no half-period screen.  kWrap: both per pair (a near_pass without its screens
+// for softening: N = 30011 with 4 images 1107 -> 1071 us, 200000 with 8 70.9 ->
+// 69.6 ms).  FP32 pair terms, FP64 sums and reactions as in near_pass.
+template <int NIMG, bool POT, int TORDER, bool COMPLETE, int KIND>
 __device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, Stage<TORDER> &st, int n, double kL,
                                          double *acc) {
     const int lane = threadIdx.x & 63;
@@ -229,10 +234,11 @@ __device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, 
             if (POT) jp = st.r[3][k];
         }
         const double dx64 = o.x - sxj, dy64 = o.y - syj;
-        const float dx = (float)dx64, dy = (float)dy64, d = (float)(zs - szj);
+        const float dx = (float)dx64, dy = (float)dy64;
+        const float d = (float)(KIND == kFar ? zs - szj : min_image(o.z - szj, a.L, a.invL));
         float S, Fz, P = 0.f;
         pair_fast<NIMG, POT>(dx, dy, d, a.c, S, Fz, P);
-        if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, false, S, Fz);
+        if (TORDER > 0) table_far<TORDER, COMPLETE>(a, GlobalNodes{a.tv.T, a.tv.w}, dx, dy, d, false, S, Fz);
         const double S64 = (double)S, Fz64 = (double)Fz;
         const double mS = ms * S64;
         acc[0] = __builtin_fma(mS, dx64, acc[0]);
@@ -242,7 +248,8 @@ __device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, 
         const double miS = o.m * S64;
         st.r[0][k] = __builtin_fma(miS, dx64, jx);
         st.r[1][k] = __builtin_fma(miS, dy64, jy);
-        st.r[2][k] = __builtin_fma(o.m, Fz64, jz);
+        const double fz = KIND == kWrap && __builtin_fabsf(d) >= a.tie32 ? tie_fz(a, o.z, szj, Fz64) : Fz64;
+        st.r[2][k] = __builtin_fma(o.m, fz, jz);
         if (POT) st.r[3][k] = __builtin_fma(o.m, (double)P, jp);
     }
 }
@@ -258,8 +265,8 @@ struct PairTerms {
     float d, S, Fz, P;
 };
 
-template <int NIMG, bool POT, int TORDER, bool COMPLETE>
-__device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, double xi, double yi, double zi, float hi,
+template <int NIMG, bool POT, int TORDER, bool COMPLETE, class Nodes>
+__device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, const Nodes &nodes, double xi, double yi, double zi, float hi,
                                                   const SrcRec &src, float thr2, bool wide, bool self) {
     PairTerms t;
     t.dx = xi - src.x;
@@ -301,7 +308,7 @@ __device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, double 
         t.Fz = (float)gf;
         t.P = (float)gp;
     }
-    if (TORDER > 0) table_far<TORDER, COMPLETE>(a, dx, dy, d, self, t.S, t.Fz);
+    if (TORDER > 0) table_far<TORDER, COMPLETE>(a, nodes, dx, dy, d, self, t.S, t.Fz);
     return t;
 }
 
@@ -328,7 +335,8 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o,
         src.h = st.h[k];
         const int ks = k & (n - 1);  // source of the tile
         const bool self = !REACT && (base + ks == o.t || ks >= cnt);
-        const PairTerms t = general_pair<NIMG, POT, TORDER, COMPLETE>(a, o.x, o.y, o.z, o.h, src, thr2, wide, self);
+        const PairTerms t =
+            general_pair<NIMG, POT, TORDER, COMPLETE>(a, GlobalNodes{a.tv.T, a.tv.w}, o.x, o.y, o.z, o.h, src, thr2, wide, self);
         const double ms = (double)st.m[k];
         double jx = 0.0, jy = 0.0, jz = 0.0, jp = 0.0;
         if (REACT && step > 0) {
@@ -390,7 +398,8 @@ __global__ __launch_bounds__(256) void forces_small_kernel(SmallArgs p) {
         src.m = (float)p.mass[js];
         src.h = (float)p.eps[js];
         const PairTerms t =
-            general_pair<NIMG, POT, TORDER, COMPLETE>(a, xi, yi, zi, hi, src, 0.f, true, !live || j == i);
+            general_pair<NIMG, POT, TORDER, COMPLETE>(a, GlobalNodes{a.tv.T, a.tv.w}, xi, yi, zi, hi, src, 0.f, true,
+                                                      !live || j == i);
         const double ms = (double)src.m, mS = ms * (double)t.S;
         acc[0] = __builtin_fma(mS, t.dx, acc[0]);
         acc[1] = __builtin_fma(mS, t.dy, acc[1]);
@@ -413,7 +422,7 @@ template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairwise_kernel(PairwiseArgs a) {
     __shared__ Stage<TORDER> st;
     const int lane = threadIdx.x;
-    const Tile t = tile_of_block(a.rd);
+    const Tile t = tile_of(a.rd, blockIdx.x);
     const int n = kPart / a.rd.Q;  // sources of the tile
     const int64_t g0 = min((int64_t)a.N, (int64_t)t.pa * kPart);                // first owned record
     const int64_t b0 = min((int64_t)a.N, (int64_t)t.pb * kPart + t.q * n);      // first source record
@@ -450,10 +459,13 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
         const WaveBox wb = {w[0], w[1], w[2], w[3], w[4], w[5], w[6]};
         __syncthreads();
         double kL = 0.0;
+        const int kind = react ? __builtin_amdgcn_readfirstlane(tile_kind(a, wb, b, kL)) : kNear;
         if (!react)
             near_pass<NIMG, POT, TORDER, COMPLETE, false>(a, o, st, n, (int)b0, cnt, (float)b[6], acc);
-        else if (__builtin_amdgcn_readfirstlane((int)far_boxes(a, wb, b, kL)))
-            far_pass<NIMG, POT, TORDER, COMPLETE>(a, o, st, n, kL, acc);
+        else if (kind == kFar)
+            far_pass<NIMG, POT, TORDER, COMPLETE, kFar>(a, o, st, n, kL, acc);
+        else if (kind == kWrap)
+            far_pass<NIMG, POT, TORDER, COMPLETE, kWrap>(a, o, st, n, kL, acc);
         else
             near_pass<NIMG, POT, TORDER, COMPLETE, true>(a, o, st, n, (int)b0, cnt, (float)b[6], acc);
         __syncthreads();
@@ -483,6 +495,208 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
     }
 }
 
+// ---------------------------------------------------------------------------
+// TSC tables that fit the LDS.  A TSC pair gathers nine nodes in six loads, 56
+// cache accesses each, and what bounds it is the rate of those (address units
+// 77% busy, VALU 56%, 930 cycles a step where the VALU work takes 430), so here
+// the whole table sits in the LDS of a workgroup of 16 waves, one to a CU, each
+// walking its share of the launch's tiles.  That leaves no room for staged
+// sources: a lane holds one source and its reaction sums in registers, and after
+// each step they move to another lane, by a Gray code of exchanges (DPP for two
+// out of three, a permute for each fourth step), so that every lane meets every
+// source.  us per call: N = 10000 393 -> 269, 20011 (with the potential) 1272 ->
+// 1024, 40000 4342 -> 3332, 100000 23800 -> 19100; what bounds it then is bank
+// conflicts of the gathers and the VALU (124 instructions) about alike.
+constexpr int kLdsWaves = 16;
+constexpr int kLdsNodes = 20480;  // 160 KiB
+constexpr int kLdsGroups = 256;   // one per CU
+// From this many particles on: 4096 waves with 55 us a tile (us per call from L2
+// and from LDS: N = 4000 80 and 86, 5000 121 and 83, 6000 153 and 141).
+constexpr int kLdsMin = 4500;
+
+inline bool lds_table(const TableView &tv, int64_t N) {
+    return N >= kLdsMin && tv.w * (tv.n_r + 3) <= kLdsNodes;
+}
+
+struct LdsNodes {
+    const float2 *T;
+    int w;
+    __device__ NodePair pair(int row, int col, unsigned off) const {
+        const float2 *p = T + row * w + col + off / (unsigned)sizeof(float2);
+        return NodePair{p[0], p[1]};
+    }
+    __device__ float2 one(int row, int col, unsigned off) const {
+        return T[row * w + col + off / (unsigned)sizeof(float2)];
+    }
+};
+
+struct MovingSource {
+    double x, y, z, m;
+    double r[4];  // reactions
+    float h;
+};
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t u) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)u, CTRL, 0xf, 0xf, true);
+}
+
+template <class F>
+__device__ __forceinline__ void each_dword(double &v, F &&f) {
+    const uint64_t u = __double_as_longlong(v);
+    v = __longlong_as_double((long long)((uint64_t)f((uint32_t)u) | (uint64_t)f((uint32_t)(u >> 32)) << 32));
+}
+
+template <bool POT, bool NEAR, class F>
+__device__ __forceinline__ void move_source(MovingSource &s, F &&f) {
+    each_dword(s.x, f);
+    each_dword(s.y, f);
+    each_dword(s.z, f);
+    each_dword(s.m, f);
+#pragma unroll
+    for (int c = 0; c < (POT ? 4 : 3); ++c) each_dword(s.r[c], f);
+    if (NEAR) s.h = __uint_as_float(f(__float_as_uint(s.h)));
+}
+
+// One wave's passage over the 64 sources of a tile of a kind (kFar: image shift
+// kL); the tile's first record is `base`, `cnt` of its sources are real.
+// Returns the source that the lane ends with.
+template <bool POT, bool COMPLETE, int KIND>
+__device__ __forceinline__ int lds_pass(const PairwiseArgs &a, const LdsNodes &nodes, const Owned &o, MovingSource &s,
+                                         double kL, bool react, int base, int cnt, double *acc) {
+    const int lane = threadIdx.x & 63;
+    const double zs = o.z - kL;
+    int at = lane;  // the source that this lane holds
+    auto step = [&] {
+        double dx, dy;
+        float S, Fz, P = 0.f, d;
+        if (KIND != kNear) {
+            dx = o.x - s.x;
+            dy = o.y - s.y;
+            d = (float)(KIND == kFar ? zs - s.z : min_image(o.z - s.z, a.L, a.invL));
+            pair_fast<1, POT>((float)dx, (float)dy, d, a.c, S, Fz, P);
+            table_far<2, COMPLETE>(a, nodes, (float)dx, (float)dy, d, false, S, Fz);
+        } else {
+            const SrcRec src = {s.x, s.y, s.z, 0.f, s.h};
+            const bool self = !react && (base + at == o.t || at >= cnt);
+            const PairTerms t =
+                general_pair<1, POT, 2, COMPLETE>(a, nodes, o.x, o.y, o.z, o.h, src, 0.f, true, self);
+            dx = t.dx;
+            dy = t.dy;
+            d = t.d;
+            S = t.S;
+            Fz = t.Fz;
+            P = t.P;
+        }
+        const double S64 = (double)S, Fz64 = (double)Fz;
+        const double mS = s.m * S64;
+        acc[0] = __builtin_fma(mS, dx, acc[0]);
+        acc[1] = __builtin_fma(mS, dy, acc[1]);
+        acc[2] = __builtin_fma(s.m, Fz64, acc[2]);
+        if (POT) acc[3] = __builtin_fma(s.m, (double)P, acc[3]);
+        const double fz = KIND != kFar && react && __builtin_fabsf(d) >= a.tie32 ? tie_fz(a, o.z, s.z, Fz64) : Fz64;
+        const double miS = o.m * S64;
+        s.r[0] = __builtin_fma(miS, dx, s.r[0]);
+        s.r[1] = __builtin_fma(miS, dy, s.r[1]);
+        s.r[2] = __builtin_fma(o.m, fz, s.r[2]);
+        if (POT) s.r[3] = __builtin_fma(o.m, (double)P, s.r[3]);
+    };
+    auto permute = [&](int mask) {
+        const int from = (lane ^ mask) * 4;
+        move_source<POT, KIND == kNear>(s, [&](uint32_t u) { return (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)u); });
+        at ^= mask;
+    };
+    auto by1 = [&] {  // lane xor 1
+        move_source<POT, KIND == kNear>(s, [](uint32_t u) { return dpp_move<0xB1>(u); });
+        at ^= 1;
+    };
+    auto by2 = [&] {  // lane xor 2
+        move_source<POT, KIND == kNear>(s, [](uint32_t u) { return dpp_move<0x4E>(u); });
+        at ^= 2;
+    };
+    for (int k = 1;; ++k) {
+        step();
+        by1();
+        step();
+        by2();
+        step();
+        by1();
+        step();
+        if (k == 16) break;
+        permute(4 << __builtin_ctz(k));  // lane xor 4, 8, 4, 16, 4, 8, 4, 32, ...
+    }
+    return at;
+}
+
+template <bool POT, bool COMPLETE>
+__global__ __launch_bounds__(64 * kLdsWaves) void forces_pairwise_lds_kernel(PairwiseArgs a, unsigned tiles) {
+    __shared__ float2 T[kLdsNodes];
+    const int nodes = a.tv.w * (a.tv.n_r + 3);
+    for (int i = threadIdx.x; i < nodes; i += 64 * kLdsWaves) T[i] = a.tv.T[i];
+    __syncthreads();
+    const LdsNodes table = {T, a.tv.w};
+    const int lane = threadIdx.x & 63;
+    const unsigned wave = __builtin_amdgcn_readfirstlane(blockIdx.x * kLdsWaves + (threadIdx.x >> 6));
+    for (unsigned at = wave; at < tiles; at += gridDim.x * kLdsWaves) {
+        const Tile t = tile_of(a.rd, at);
+        const int64_t g0 = min((int64_t)a.N, (int64_t)t.pa * kPart);   // first owned record
+        const int64_t b0 = min((int64_t)a.N, (int64_t)t.pb * kPart);   // first source record
+        const int ocnt = (int)min((int64_t)kPart, (int64_t)a.N - g0);  // owned records
+        const int cnt = (int)min((int64_t)kPart, (int64_t)a.N - b0);   // sources
+        const bool react = t.pa != t.pb;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        double *pa = a.sum + (int64_t)t.slot_a * 4 * a.N + g0;
+        double *pb = a.sum + (int64_t)t.slot_b * 4 * a.N + b0;
+        int source = lane;  // the source whose reaction this lane ends with
+        MovingSource s;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s.r[c] = 0.0;
+        if (ocnt > 0 && cnt > 0) {
+            // empty lanes as in forces_pairwise_kernel
+            Owned o;
+            const bool real = lane < ocnt, live = lane < cnt;
+            const SrcRec rr = a.rec[real ? g0 + lane : g0], sr = a.rec[live ? b0 + lane : b0];
+            o.t = real ? (int)g0 + lane : a.N;
+            o.x = rr.x;
+            o.y = rr.y;
+            o.z = rr.z;
+            o.h = rr.h;
+            o.m = real ? (double)rr.m : 0.0;
+            s.x = sr.x;
+            s.y = sr.y;
+            s.z = sr.z;
+            s.h = sr.h;
+            s.m = live ? (double)sr.m : 0.0;
+            const double *w = a.box + (g0 >> 6) * kBox;
+            const WaveBox wb = {w[0], w[1], w[2], w[3], w[4], w[5], w[6]};
+            double kL = 0.0;
+            const int kind =
+                react ? __builtin_amdgcn_readfirstlane(tile_kind(a, wb, a.box + (b0 >> 6) * kBox, kL)) : kNear;
+            if (kind == kFar)
+                source = lds_pass<POT, COMPLETE, kFar>(a, table, o, s, kL, true, (int)b0, cnt, acc);
+            else if (kind == kWrap)
+                source = lds_pass<POT, COMPLETE, kWrap>(a, table, o, s, 0.0, true, (int)b0, cnt, acc);
+            else
+                source = lds_pass<POT, COMPLETE, kNear>(a, table, o, s, 0.0, react, (int)b0, cnt, acc);
+        }
+        if (react && source < cnt && (a.rd.first || ocnt > 0)) {
+#pragma unroll
+            for (int c = 0; c < (POT ? 4 : 3); ++c) {
+                const double v = c < 3 ? -s.r[c] : s.r[c];
+                double *p = pb + (int64_t)c * a.N + source;
+                *p = a.rd.first ? v : *p + v;
+            }
+        }
+        if (lane < ocnt && (a.rd.first || cnt > 0)) {
+#pragma unroll
+            for (int c = 0; c < (POT ? 4 : 3); ++c) {
+                double *p = pa + (int64_t)c * a.N + lane;
+                *p = a.rd.first ? acc[c] : *p + acc[c];
+            }
+        }
+    }
+}
+
 template <int NIMG, bool POT, int TORDER, bool COMPLETE>
 struct Launcher {
     static hipError_t small(const SmallArgs &p, hipStream_t stream) {
@@ -492,6 +706,15 @@ struct Launcher {
     }
 
     static hipError_t run(PairwiseArgs a, const Schedule &s, hipStream_t stream) {
+        if constexpr (TORDER == 2) {
+            if (lds_table(a.tv, a.N))
+                return each_launch(s, a.N, kPart, [&](const Rounds &rd, unsigned tiles) {
+                    a.rd = rd;
+                    hipLaunchKernelGGL((forces_pairwise_lds_kernel<POT, COMPLETE>), dim3(kLdsGroups),
+                                       dim3(64 * kLdsWaves), 0, stream, a, tiles);
+                    return hipGetLastError();
+                });
+        }
         return each_launch(s, a.N, kPart, [&](const Rounds &rd, unsigned blocks) {
             a.rd = rd;
             hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE>), dim3(blocks), dim3(kThreads), 0,
@@ -567,9 +790,10 @@ size_t pairwise_bytes(int64_t N, size_t slot_budget) { return schedule_bytes(N, 
 int launch_forces_pairwise(const double *pos, const double *mass, const double *eps, int64_t N, double L,
                            int n_img, const steps_cyl_table *table, int order, float *out_acc, float *out_pot,
                            Workspace &ws, hipStream_t stream, size_t slot_budget) {
-    const Schedule sch = pairwise_schedule(N, slot_budget);
+    Schedule sch = pairwise_schedule(N, slot_budget);
     int rc = check_workspace(ws, schedule_bytes(N, sch));
     if (rc) return rc;
+    if (table && order == 2 && lds_table(table_view(table), N)) sch.Q = 1;  // fewer slots than there is room for
     PairwiseArgs a;
     a.L = L;
     a.invL = 1.0 / L;

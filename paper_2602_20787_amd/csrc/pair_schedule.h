@@ -91,17 +91,17 @@ struct Tile {
     int slot_a, slot_b;  // slot of the owned sums, of the reactions
 };
 
-// The workgroup's tile: round 0's first (tiles i <= j of every group, Q
+// Tile `at` of a launch: round 0's first (tiles i <= j of every group, Q
 // workgroups each), then S^2 per meeting of the launch's other rounds.
-__device__ __forceinline__ Tile tile_of_block(const Rounds &r) {
+__device__ __forceinline__ Tile tile_of(const Rounds &r, unsigned at) {
     Tile t;
     const int S = r.S, Q = r.Q;
     int ga, gb, pi, pj, set = 0;
     t.q = 0;
-    if (blockIdx.x < r.own) {
+    if (at < r.own) {
         const unsigned T = (unsigned)S * (S + 1) / 2;
-        const unsigned tile = blockIdx.x / Q;
-        t.q = (int)(blockIdx.x % Q);
+        const unsigned tile = at / Q;
+        t.q = (int)(at % Q);
         ga = gb = (int)(tile / T);
         const unsigned c = tile % T;  // by columns: c = j (j + 1)/2 + i, i <= j
         pj = (int)((__builtin_sqrtf(8.f * (float)c + 1.f) - 1.f) * 0.5f);
@@ -109,7 +109,7 @@ __device__ __forceinline__ Tile tile_of_block(const Rounds &r) {
         while ((unsigned)pj * (pj + 1) / 2 > c) --pj;
         pi = (int)(c - (unsigned)pj * (pj + 1) / 2);
     } else {
-        const unsigned w = blockIdx.x - r.own;
+        const unsigned w = at - r.own;
         const unsigned per = (unsigned)S * S, half = r.Gp / 2;
         const unsigned meeting = w / per;
         const int meet = (int)(meeting % half);

@@ -128,8 +128,18 @@ __device__ __forceinline__ T node_at(const float2 *row, unsigned off) {
     return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(row) + off);
 }
 
-template <int ORDER>
-__device__ __forceinline__ void lookup(const TableView &a, float delta, float r, float &tz, float &tr) {
+// Where a lookup reads the nodes: two neighbours, or one, of row `row` and the
+// columns from `col` on, at byte offset `off`.
+struct GlobalNodes {
+    const float2 *T;
+    int w;
+    __device__ NodePair pair(int row, int col, unsigned off) const { return node_at<NodePair>(T + row * w + col, off); }
+    __device__ float2 one(int row, int col, unsigned off) const { return node_at<float2>(T + row * w + col, off); }
+};
+
+template <int ORDER, class Nodes>
+__device__ __forceinline__ void lookup(const TableView &a, const Nodes &nodes, float delta, float r, float &tz,
+                                       float &tr) {
     // the positions in the cell by explicit fused operations: they do not depend
     // on what the compiler can contract
     const float x = delta * a.inv_hd, y = r * a.inv_hr;
@@ -141,8 +151,7 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
         const unsigned i0 = min((unsigned)x, (unsigned)(a.n_d - 1)), j0 = min((unsigned)y, (unsigned)(a.n_r - 1));
         const float fx = __builtin_fmaf(delta, a.inv_hd, -(float)i0), fy = __builtin_fmaf(r, a.inv_hr, -(float)j0);
         const unsigned off = (__umul24(j0, (unsigned)a.w) + i0) * (unsigned)sizeof(float2);
-        const float2 *row = a.T + a.w + 1;
-        const NodePair lo = node_at<NodePair>(row, off), hi = node_at<NodePair>(row + a.w, off);
+        const NodePair lo = nodes.pair(1, 1, off), hi = nodes.pair(2, 1, off);
         const float z0 = __builtin_fmaf(fx, lo.b.x - lo.a.x, lo.a.x), z1 = __builtin_fmaf(fx, hi.b.x - hi.a.x, hi.a.x);
         const float r0 = __builtin_fmaf(fx, lo.b.y - lo.a.y, lo.a.y), r1 = __builtin_fmaf(fx, hi.b.y - hi.a.y, hi.a.y);
         tz = __builtin_fmaf(fy, z1 - z0, z0);
@@ -157,9 +166,8 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
         const unsigned off = (__umul24(j0, (unsigned)a.w) + i0) * (unsigned)sizeof(float2);  // node (i0 - 1, j0 - 1)
 #pragma unroll
         for (int dj = 0; dj < 3; ++dj) {
-            const float2 *row = a.T + dj * a.w;
-            const NodePair p = node_at<NodePair>(row, off);
-            const float2 q = node_at<float2>(row + 2, off);
+            const NodePair p = nodes.pair(dj, 0, off);
+            const float2 q = nodes.one(dj, 2, off);
             const float rz = __builtin_fmaf(wx[2], q.x, __builtin_fmaf(wx[1], p.b.x, wx[0] * p.a.x));
             const float rr = __builtin_fmaf(wx[2], q.y, __builtin_fmaf(wx[1], p.b.y, wx[0] * p.a.y));
             tz = __builtin_fmaf(wy[dj], rz, tz);
@@ -167,7 +175,6 @@ __device__ __forceinline__ void lookup(const TableView &a, float delta, float r,
         }
     }
 }
-
 
 struct TableTerms {
     float dx, dy, S, Fz, P;  // S_eff, F_z,eff and (POT) P
@@ -196,7 +203,7 @@ __device__ __forceinline__ bool table_terms_inside(const TableView &a, const Per
     const float r = rho * pc.invLf;
     const float delta = __builtin_fabsf(d) * pc.invLf;
     float tz, Rr;
-    lookup<ORDER>(a, delta, r, tz, Rr);
+    lookup<ORDER>(a, GlobalNodes{a.T, a.w}, delta, r, tz, Rr);
     const float Rz = signed_tz(tz, d);
     const float rinv = __builtin_amdgcn_rcpf(rho);
     t = TableTerms{dx, dy, __builtin_fmaf(-Rr * pc.invL2f, rinv, S), __builtin_fmaf(-Rz, pc.invL2f, Fz), 0.f};
@@ -239,7 +246,7 @@ __device__ __forceinline__ TableTerms table_terms(const TableView &a, const Peri
     const float delta = __builtin_fabsf(d) * pc.invLf;
     const bool inside = (r <= a.r_max) && !self;
     float tz, tr;
-    lookup<ORDER>(a, delta, r, tz, tr);
+    lookup<ORDER>(a, GlobalNodes{a.T, a.w}, delta, r, tz, tr);
     float Rz = signed_tz(tz, d);
     float Rr = tr;
     if (!inside) {

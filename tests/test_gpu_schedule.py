@@ -138,6 +138,34 @@ def test_table_schedules(sc, N, order, complete):
     tab.close()
 
 
+# TSC from LDS: from 4500 particles on, and tables of up to 20480 nodes (140 and
+# 141 a side hold 20449 and 20736 with their ghosts)
+@pytest.mark.parametrize("N", [4499, 4500, 4544, 4545, 9001, 16000])
+@pytest.mark.parametrize("n_grid,complete,pot", [(140, True, True), (141, True, False), (32, False, True),
+                                                 (32, False, False)])
+def test_tsc_tables_in_and_out_of_lds(sc, N, n_grid, complete, pot):
+    print(f"[case] TSC N={N} grid={n_grid} complete={complete} pot={pot}", flush=True)
+    p = synth.clustered_load(N, n_clumps=8, clump_frac=0.02, seed=N)
+    pos = p.pos.copy()
+    pos[2, : N // 8] = np.floor(pos[2, : N // 8] * 4.0) / 4.0  # separations of exactly L/2
+    d = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (pos, p.mass, p.eps)]
+    tab = (sc.CorrectionTable.ewald(n_grid, n_grid, 4.5, 2.0, 5, 12) if complete
+           else sc.CorrectionTable(n_grid, n_grid, 4.5, 64))
+    t = torch.arange(N, dtype=torch.int64, device="cuda:0")
+    acc, q = sc.steps_cyl_forces_table(*d, p.L, tab, order=2, potential=pot)
+    nb = sc.steps_cyl_forces_workspace(sc.STEPS_PATH_TABLE, N, 0, 0, 0, table=tab, order=2, potential=pot)
+    ws = torch.full((nb,), 255, dtype=torch.uint8, device="cuda:0")
+    again, _ = sc.steps_cyl_forces_table_ws(*d, p.L, tab, ws, order=2, potential=pot)
+    assert torch.equal(acc, again)
+    ref, rq = sc.steps_cyl_forces_table(*d, p.L, tab, order=2, targets=t, potential=pot)
+    # the per-target kernel sums the same terms in FP32, 32 at a time
+    size = term_sizes(*d, p.L, 1)
+    assert (torch.linalg.norm(acc.double() - ref.double(), dim=0) / size).max().item() <= 2e-6
+    if pot:
+        assert (torch.abs(q - rq) / torch.abs(rq)).max().item() <= 2e-6
+    tab.close()
+
+
 # tiles over 16, 8, 4, 2 workgroups (ragged parts and source runs), sorted,
 # flat / groups, several groups with one particle in the last
 @pytest.mark.parametrize("N", [1, 2, 129, 1000, 2900, 5000, 5700, 10240, 21632, 21633, 25601])
