@@ -518,18 +518,6 @@ inline bool lds_table(const TableView &tv, int64_t N) {
     return N >= kLdsMin && tv.w * (tv.n_r + 3) <= kLdsNodes;
 }
 
-struct LdsNodes {
-    const float2 *T;
-    int w;
-    __device__ NodePair pair(int row, int col, unsigned off) const {
-        const float2 *p = T + row * w + col + off / (unsigned)sizeof(float2);
-        return NodePair{p[0], p[1]};
-    }
-    __device__ float2 one(int row, int col, unsigned off) const {
-        return T[row * w + col + off / (unsigned)sizeof(float2)];
-    }
-};
-
 struct MovingSource {
     double x, y, z, m;
     double r[4];  // reactions

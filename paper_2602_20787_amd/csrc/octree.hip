@@ -696,6 +696,7 @@ __global__ __launch_bounds__(kWalkBlock, walk_waves(ORDER, QUAD, SPLIT)) void tr
     const int ii = active ? i : g0;
     const double xi = a.sx[ii], yi = a.sy[ii], zi = a.sz[ii];
     const float hi = (float)a.sh[ii];
+    const GlobalNodes nodes = {a.tv.T, a.tv.w};
     float sx = 0.f, sy = 0.f, sz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
     float px = 0.f, py = 0.f, pz = 0.f;
     int pending = 0, n_cell = 0, n_part = 0;
@@ -854,8 +855,8 @@ __global__ __launch_bounds__(kWalkBlock, walk_waves(ORDER, QUAD, SPLIT)) void tr
                             continue;
                         }
                     }
-                    one(r0, table_terms<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, r0, w.src[s].own == i,
-                                                                active),
+                    one(r0, table_terms<ORDER, false, COMPLETE>(a.tv, nodes, a.pc, xi, yi, zi, hi, r0,
+                                                                w.src[s].own == i, active),
                         f0, s);
                     ++s;
                 }
@@ -868,7 +869,8 @@ __global__ __launch_bounds__(kWalkBlock, walk_waves(ORDER, QUAD, SPLIT)) void tr
                     bool ok = (src.flag & kFarSrc) != 0;
                     if (__ballot(!ok) == 0) ok = table_terms_inside<ORDER>(a.tv, a.pc, xi, yi, zi, src.r, t);
                     if (__ballot(!ok) != 0)
-                        t = table_terms<ORDER, false, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, src.r, src.own == i, active);
+                        t = table_terms<ORDER, false, COMPLETE>(a.tv, nodes, a.pc, xi, yi, zi, hi, src.r, src.own == i,
+                                                                  active);
                     float mS[SPLIT], mm[SPLIT], dx[SPLIT], dy[SPLIT], Fz[SPLIT];
                     spread<SPLIT>(src.r.m * t.S, mS);
                     spread<SPLIT>(src.r.m, mm);

@@ -31,8 +31,11 @@
 // kernel; at 146 x 131 nodes (the paper's 144 x 128 grid plus ghosts) the
 // FP32 table is 153 KB and stays in L2.  The force kernel maps one target
 // per thread like the exact kernel; sources come through LDS tiles, the
-// table through the vector caches.  Pairs of a band table beyond r_max take
+// table through the vector caches or, with TSC, from LDS.  Pairs of a band table beyond r_max take
 // the exact band, shared by the 64 lanes of the wave.
+#include <algorithm>
+#include <type_traits>
+
 #include "table_pair.h"
 
 namespace steps {
@@ -197,6 +200,11 @@ __global__ __launch_bounds__(64) void build_ewald_kernel(float2 *nodes, double2 
     store_node(nodes, nodes64, k, tz, rs < 0.0 ? -tr : tr);
 }
 
+constexpr int kCus = 256;
+constexpr int kLdsBlock = 1024;  // most targets of a workgroup with the table in LDS
+constexpr int kL1Nodes = 32 * 1024 / (int)sizeof(float2);
+constexpr int kLdsNodes = (160 * 1024 - kBlock * (int)sizeof(SrcRec)) / (int)sizeof(float2);  // 19456
+
 struct TableArgs {
     const double *x, *y, *z, *m, *h;
     const int64_t *targets;
@@ -207,12 +215,22 @@ struct TableArgs {
     int N, n_tgt;
 };
 
-template <int ORDER, bool POT, bool COMPLETE>
-__global__ __launch_bounds__(kBlock) void forces_table_kernel(TableArgs a) {
+// One thread per target.  With CIC (two loads of two nodes per pair) the VALU bounds
+// it.  With TSC six gathers per pair go to the vector L1, which does not hold what
+// the waves on a CU look up together (2^19 targets take 1350 ms at 7 waves per SIMD
+// and 1050 at 3); so a table that fits is held in LDS (LDS), one workgroup per CU.  ms per call from the L1 and from LDS, 146 x 131 nodes: 4096
+// of 262144 particles 125 and 121, 131072 of them 181 and 140, all 325 and 208,
+// 300000 392 and 373, 2^19 1348 and 814.
+template <int ORDER, bool POT, bool COMPLETE, bool LDS>
+__global__ __launch_bounds__(LDS ? kLdsBlock : kBlock) void forces_table_kernel(TableArgs a) {
     __shared__ SrcRec tile[kBlock];
+    __shared__ float2 T[LDS ? kLdsNodes : 1];
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int k = blockIdx.x * kBlock + tid;
+    if (LDS)  // the sources' first barrier makes it visible
+        for (int n = tid; n < a.tv.w * (a.tv.n_r + 3); n += (int)blockDim.x) T[n] = a.tv.T[n];
+    const std::conditional_t<LDS, LdsNodes, GlobalNodes> nodes = {LDS ? T : a.tv.T, a.tv.w};
+    const int threads = ORDER == 2 ? (int)blockDim.x : kBlock;
+    const int k = blockIdx.x * threads + tid;
     const bool active = k < a.n_tgt;
     const int64_t kk = active ? (a.perm ? (int64_t)a.perm[k] : (int64_t)k) : 0;  // position in the list
     const int64_t i = a.targets ? a.targets[kk] : kk;
@@ -222,15 +240,14 @@ __global__ __launch_bounds__(kBlock) void forces_table_kernel(TableArgs a) {
     float cx = 0.f, cy = 0.f, cz = 0.f, cp = 0.f;
     for (int base = 0; base < a.N; base += kBlock) {
         __syncthreads();
-        const int j = base + tid;
-        if (j < a.N) {
+        for (int q = tid, j = base + tid; q < kBlock && j < a.N; q += threads, j += threads) {
             SrcRec r;
             r.x = a.x[j];
             r.y = a.y[j];
             r.z = wrap_z(a.z[j], a.pc.L);
             r.m = (float)a.m[j];
             r.h = (float)a.h[j];
-            tile[tid] = r;
+            tile[q] = r;
         }
         __syncthreads();
         const int cnt = min(kBlock, a.N - base);
@@ -240,7 +257,8 @@ __global__ __launch_bounds__(kBlock) void forces_table_kernel(TableArgs a) {
             for (int s = 0; s < e; ++s) {
                 const SrcRec src = tile[s0 + s];
                 const bool self = (int64_t)(base + s0 + s) == i;
-                table_add<POT>(table_terms<ORDER, POT, COMPLETE>(a.tv, a.pc, xi, yi, zi, hi, src, self, active),
+                table_add<POT>(table_terms<ORDER, POT, COMPLETE>(a.tv, nodes, a.pc, xi, yi, zi, hi, src, self,
+                                                                 active),
                                src.m, px, py, pz, pp);
             }
             kahan_add(sx, cx, px);
@@ -258,15 +276,37 @@ __global__ __launch_bounds__(kBlock) void forces_table_kernel(TableArgs a) {
     }
 }
 
+template <int ORDER, bool POT, bool COMPLETE>
+hipError_t launch_c(const TableArgs &a, hipStream_t stream) {
+    if constexpr (ORDER == 2) {
+        // A workgroup per CU and round, rounds of equal size.  A table that fits the L1
+        // stays there where the last round would be nearly empty (43 x 43 nodes, ms from
+        // the L1 and from LDS: 262144 targets 260 and 193, 270000 303 and 320, 300000 349
+        // and 362, 350000 432 and 421).
+        constexpr int round = kCus * kLdsBlock;
+        const int nodes = a.tv.w * (a.tv.n_r + 3);
+        const int rounds = (a.n_tgt + round - 1) / round;
+        const bool empty = rounds > 1 && a.n_tgt - (rounds - 1) * round <= round / 4;
+        if (nodes <= kLdsNodes && !(empty && nodes <= kL1Nodes)) {
+            const int per = (a.n_tgt + kCus * rounds - 1) / (kCus * rounds);
+            const int block = std::max(kBlock, (per + 63) / 64 * 64);
+            hipLaunchKernelGGL((forces_table_kernel<ORDER, POT, COMPLETE, true>), dim3((a.n_tgt + block - 1) / block),
+                               dim3(block), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
+    // TSC from the L1, once every CU has work: smaller workgroups look up less at
+    // once (160 x 160 nodes, ms per call with 256, 128 and 64 threads: 65536 of 262144
+    // particles 125, 142, 139, 200000 309, 283, 270, 2^19 1244, 1142, 1187)
+    const int block = ORDER == 2 && a.n_tgt > kCus * kBlock ? 128 : kBlock;
+    hipLaunchKernelGGL((forces_table_kernel<ORDER, POT, COMPLETE, false>), dim3((a.n_tgt + block - 1) / block),
+                       dim3(block), 0, stream, a);
+    return hipGetLastError();
+}
 
 template <int ORDER, bool POT>
 hipError_t launch_t(const TableArgs &a, hipStream_t stream) {
-    const int grid = (a.n_tgt + kBlock - 1) / kBlock;
-    if (a.tv.complete)
-        hipLaunchKernelGGL((forces_table_kernel<ORDER, POT, true>), dim3(grid), dim3(kBlock), 0, stream, a);
-    else
-        hipLaunchKernelGGL((forces_table_kernel<ORDER, POT, false>), dim3(grid), dim3(kBlock), 0, stream, a);
-    return hipGetLastError();
+    return a.tv.complete ? launch_c<ORDER, POT, true>(a, stream) : launch_c<ORDER, POT, false>(a, stream);
 }
 
 }  // namespace

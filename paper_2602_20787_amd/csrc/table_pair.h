@@ -137,6 +137,18 @@ struct GlobalNodes {
     __device__ float2 one(int row, int col, unsigned off) const { return node_at<float2>(T + row * w + col, off); }
 };
 
+struct LdsNodes {
+    const float2 *T;
+    int w;
+    __device__ NodePair pair(int row, int col, unsigned off) const {
+        const float2 *p = T + row * w + col + off / (unsigned)sizeof(float2);
+        return NodePair{p[0], p[1]};
+    }
+    __device__ float2 one(int row, int col, unsigned off) const {
+        return T[row * w + col + off / (unsigned)sizeof(float2)];
+    }
+};
+
 template <int ORDER, class Nodes>
 __device__ __forceinline__ void lookup(const TableView &a, const Nodes &nodes, float delta, float r, float &tz,
                                        float &tr) {
@@ -215,9 +227,10 @@ __device__ __forceinline__ bool table_terms_inside(const TableView &a, const Per
 // wave); ``active`` marks lanes with a real target.  COMPLETE: the table holds
 // every image |n| >= 2 (pairs beyond rho_max take the line-mass limit) rather
 // than a band.
-template <int ORDER, bool POT, bool COMPLETE>
-__device__ __forceinline__ TableTerms table_terms(const TableView &a, const PeriodConsts &pc, double xi, double yi,
-                                                  double zi, float hi, const SrcRec &src, bool self, bool active) {
+template <int ORDER, bool POT, bool COMPLETE, class Nodes>
+__device__ __forceinline__ TableTerms table_terms(const TableView &a, const Nodes &nodes, const PeriodConsts &pc,
+                                                  double xi, double yi, double zi, float hi, const SrcRec &src,
+                                                  bool self, bool active) {
     const int lane = threadIdx.x & 63;
     const double dx64 = xi - src.x, dy64 = yi - src.y;
     const double d64 = min_image(zi - src.z, pc.L, pc.invL);
@@ -246,7 +259,7 @@ __device__ __forceinline__ TableTerms table_terms(const TableView &a, const Peri
     const float delta = __builtin_fabsf(d) * pc.invLf;
     const bool inside = (r <= a.r_max) && !self;
     float tz, tr;
-    lookup<ORDER>(a, GlobalNodes{a.T, a.w}, delta, r, tz, tr);
+    lookup<ORDER>(a, nodes, delta, r, tz, tr);
     float Rz = signed_tz(tz, d);
     float Rr = tr;
     if (!inside) {
