@@ -54,9 +54,9 @@ PEAK_FP32_UNPACKED = 78.6e12     # 256 CU x 4 SIMD x 16 lanes x 2 FLOP x 2.4 GHz
 # what the counter reads for a 256 MiB copy
 # (profiles/forces_pairwise_N1M_nimg8_counters.md).  Valid only for the
 # kernel sources they were measured on (hash below); None until measured.
-TRAFFIC_EXACT_N1M = {"bytes": 1.3253e12, "fetch_scale": 1.99974, "write_scale": 1.0,
-                     "sources_sha256_16": "c13a2cf9e317bbd3"}
-TRAFFIC_SOURCES = ["forces_pairwise.hip", "pair_fp32.h", "pair_f64.h", "target_order.hip"]
+TRAFFIC_EXACT_N1M = {"bytes": 1.2608e12, "fetch_scale": 1.99974, "write_scale": 1.0,
+                     "sources_sha256_16": "00888d9b52d917b0"}
+TRAFFIC_SOURCES = ["forces_pairwise.hip", "pair_schedule.h", "pair_fp32.h", "pair_f64.h", "target_order.hip"]
 
 
 def exact_sources_hash():
@@ -77,27 +77,30 @@ def flops_per_pair(n_img, potential=True):
 REACTION_FLOPS = 9
 
 
-def pairwise_group(N):
-    """Particles per group of the exact pairwise path: 16 parts of 64 (one
-    particle per lane of a one-wave workgroup) up to 2^21 particles, else 8."""
-    return 64 * (16 if N <= (1 << 21) else 8)
-
-
 def pairwise_evaluations(N):
-    """Pair terms the pairwise kernels evaluate: every ordered pair inside a
-    group, every pair across groups once."""
-    g = pairwise_group(N)
-    full, tail = divmod(N, g)
-    inner = full * g ** 2 + tail ** 2
-    return (N * N + inner) // 2
+    """Pair terms a call evaluates: every ordered pair inside a part of 64
+    particles (a one-wave workgroup), every pair across parts once; up to 2304
+    particles every ordered pair."""
+    if N <= 2304:
+        return N * N
+    full, tail = divmod(N, 64)
+    return (N * N + full * 64 ** 2 + tail ** 2) // 2
 
 
-def meeting_launches(N):
-    """Launches of the meeting kernel per call: G' - 1 tournament rounds,
-    G' the group count rounded up to even."""
-    g = pairwise_group(N)
-    G = (N + g - 1) // g
-    return G + (G & 1) - 1
+def pair_launches(N):
+    """Launches of the pair kernel per call: groups of 16 parts of 64 (8 above
+    2^21 particles) meet in G' rounds (the group count rounded up to even), as
+    many rounds to a launch as 256 MiB of sums hold (112 MiB up to 125,000
+    particles, there in one launch where all parts' sums fit)."""
+    parts = (N + 63) // 64
+    budget = (112 if N <= 125000 else 256) << 20
+    if N <= 2304 or (N <= 125000 and parts * N * 32 <= budget):
+        return 1
+    S = 16 if N <= (1 << 21) else 8
+    G = (parts + S - 1) // S
+    rounds = G + (G & 1) if G > 1 else 1
+    M = max(1, budget // (S * N * 32))
+    return (rounds + M - 1) // M
 
 
 def timed(fn, runs, stream):
@@ -165,10 +168,10 @@ def exact_leg(args, dev):
     ms = float(np.mean(step_ms))
     pairs = float(N) * float(N)
     value = pairs / (ms * 1e-3) / 1e9
-    # the kernels evaluate each unordered pair once (groups of pairwise_group(N)
-    # particles: all ordered pairs inside a group, each cross pair once) and
-    # apply it to both particles; the whole call (ordering, staging, the self
-    # launch, the tournament's launches and the final pass) is the time base
+    # the kernel evaluates each unordered pair once (all ordered pairs inside a
+    # part of 64, each cross pair once) and applies it to both particles; the
+    # whole call (ordering, staging, the pair launches and the final pass) is
+    # the time base
     evals = pairwise_evaluations(N)
     achieved = evals * (flops_per_pair(n_img) + REACTION_FLOPS) / (ms * 1e-3)
     print(f"[bench] per-step ms {['%.1f' % x for x in step_ms]} wall {wall:.2f}s",
@@ -214,10 +217,9 @@ def exact_leg(args, dev):
             "flops_per_evaluation": flops_per_pair(n_img) + REACTION_FLOPS,
             "evaluations": evals,
             "time_base": "whole steps_cyl_forces call",
-            "meeting_launches_per_call": meeting_launches(N),
+            "pair_launches_per_call": pair_launches(N),
             "frac_of_unpacked_fp32_peak": round(achieved / PEAK_FP32_UNPACKED, 4),
-            "kernel": f"forces_pairwise_kernel<{n_img},true,0,false,true> (tournament meetings, one-wave "
-                      f"workgroups; plus one self launch <{n_img},true,0,false,false>)",
+            "kernel": f"forces_pairwise_kernel<{n_img},true,0,false> (tournament meetings, one-wave workgroups)",
         },
         # the metric's N^2 count (F_pair for every ordered pair, including the
         # half that symmetry skips): a dense-equivalent figure

@@ -448,8 +448,8 @@ int steps_cyl_table_info(const steps_cyl_table *table, int *n_delta, int *n_rho,
  * and even in d across, so the tabulated pair is antisymmetric like the
  * exact one.  targets NULL (every particle a target): each unordered pair is
  * evaluated once and applied to both particles, with the arithmetic, the
- * fixed schedule (bitwise reproducible) and the workspace of steps_cyl_forces
- * (groups of 512).  An explicit target list: one thread per target with
+ * fixed schedule (bitwise reproducible) and the workspace of
+ * steps_cyl_forces.  An explicit target list: one thread per target with
  * Kahan-compensated FP32 sums, bitwise deterministic.  Other arguments as
  * steps_cyl_forces_ex. */
 int steps_cyl_forces_table(const double *pos, const double *mass, const double *eps,
