@@ -55,7 +55,7 @@ PEAK_FP32_UNPACKED = 78.6e12     # 256 CU x 4 SIMD x 16 lanes x 2 FLOP x 2.4 GHz
 # (profiles/forces_pairwise_N1M_nimg8_counters.md).  Valid only for the
 # kernel sources they were measured on (hash below); None until measured.
 TRAFFIC_EXACT_N1M = {"bytes": 1.2608e12, "fetch_scale": 1.99974, "write_scale": 1.0,
-                     "sources_sha256_16": "00888d9b52d917b0"}
+                     "sources_sha256_16": "557f82eb946cd22b"}
 TRAFFIC_SOURCES = ["forces_pairwise.hip", "pair_schedule.h", "pair_fp32.h", "pair_f64.h", "target_order.hip"]
 
 

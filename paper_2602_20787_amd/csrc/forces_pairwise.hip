@@ -58,9 +58,10 @@ constexpr int kSmallMax = 2304;
 // lane at 2 waves (256 VGPRs) 2182.  The extra VALU work of one particle per
 // lane (139 instructions per pair in the far loop against 134.5 with four, for
 // the reaction's LDS update and the loop) costs less than the latency the
-// extra waves hide.  With a table a bound of 4 waves (80-83 VGPRs, so 5-6
-// waves fit): CIC 1436 and TSC 2042 ms, against 1473 and 2200 with 2 per lane
-// at 3 waves and 1441 and 2075 with the bound at 6 waves.
+// extra waves hide.  With a table a bound of 4 waves (78 VGPRs, 6 waves; 98
+// with the potential, where a bound of 5 changed CIC by -2 to +1.5 %): before the
+// lookup was trimmed CIC 1436 and TSC 2042 ms, against 1473 and 2200 with 2 per
+// lane at 3 waves and 1441 and 2075 with the bound at 6 waves; CIC now 1192.
 constexpr int waves_per_simd(int torder) { return torder > 0 ? 4 : 5; }
 
 struct PairwiseArgs {
