@@ -252,6 +252,7 @@ __device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, 
         const double fz = KIND == kWrap && __builtin_fabsf(d) >= a.tie32 ? tie_fz(a, o.z, szj, Fz64) : Fz64;
         st.r[2][k] = __builtin_fma(o.m, fz, jz);
         if (POT) st.r[3][k] = __builtin_fma(o.m, (double)P, jp);
+        hand_over();
     }
 }
 
@@ -360,6 +361,7 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o,
             st.r[1][k] = __builtin_fma(miS, t.dy, jy);
             st.r[2][k] = __builtin_fma(o.m, fz, jz);
             if (POT) st.r[3][k] = __builtin_fma(o.m, (double)t.P, jp);
+            hand_over();
         }
     }
 }

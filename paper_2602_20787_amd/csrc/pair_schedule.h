@@ -155,6 +155,12 @@ hipError_t each_launch(const Schedule &s, int N, int part, F &&launch) {
     return e;
 }
 
+// Ends a step of a wave that hands LDS slots from lane to lane: what the next
+// step reads another lane has written in this one, which the compiler, following
+// one lane, cannot see.  It must keep the steps' LDS accesses in program order
+// (the wave's LDS operations then complete in issue order); no instruction.
+__device__ __forceinline__ void hand_over() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 constexpr int kBox = 8;  // doubles per 64-record box
 
 // Records in the order of `perm` (null: the particles' own) and the bounding
