@@ -521,10 +521,12 @@ inline bool lds_table(const TableView &tv, int64_t N) {
     return N >= kLdsMin && tv.w * (tv.n_r + 3) <= kLdsNodes;
 }
 
+// The mass moves in FP32, which leaves the form with the potential a register more
+// (32 x 32 nodes, N = 6000: 154 us, with an FP64 mass 155 to 185 by what else spills).
 struct MovingSource {
-    double x, y, z, m;
+    double x, y, z;
     double r[4];  // reactions
-    float h;
+    float m, h;
 };
 
 template <int CTRL>
@@ -543,7 +545,7 @@ __device__ __forceinline__ void move_source(MovingSource &s, F &&f) {
     each_dword(s.x, f);
     each_dword(s.y, f);
     each_dword(s.z, f);
-    each_dword(s.m, f);
+    s.m = __uint_as_float(f(__float_as_uint(s.m)));
 #pragma unroll
     for (int c = 0; c < (POT ? 4 : 3); ++c) each_dword(s.r[c], f);
     if (NEAR) s.h = __uint_as_float(f(__float_as_uint(s.h)));
@@ -580,11 +582,11 @@ __device__ __forceinline__ int lds_pass(const PairwiseArgs &a, const LdsNodes &n
             P = t.P;
         }
         const double S64 = (double)S, Fz64 = (double)Fz;
-        const double mS = s.m * S64;
+        const double ms = (double)s.m, mS = ms * S64;
         acc[0] = __builtin_fma(mS, dx, acc[0]);
         acc[1] = __builtin_fma(mS, dy, acc[1]);
-        acc[2] = __builtin_fma(s.m, Fz64, acc[2]);
-        if (POT) acc[3] = __builtin_fma(s.m, (double)P, acc[3]);
+        acc[2] = __builtin_fma(ms, Fz64, acc[2]);
+        if (POT) acc[3] = __builtin_fma(ms, (double)P, acc[3]);
         const double fz = KIND != kFar && react && __builtin_fabsf(d) >= a.tie32 ? tie_fz(a, o.z, s.z, Fz64) : Fz64;
         const double miS = o.m * S64;
         s.r[0] = __builtin_fma(miS, dx, s.r[0]);
@@ -657,7 +659,7 @@ __global__ __launch_bounds__(64 * kLdsWaves) void forces_pairwise_lds_kernel(Pai
             s.y = sr.y;
             s.z = sr.z;
             s.h = sr.h;
-            s.m = live ? (double)sr.m : 0.0;
+            s.m = live ? sr.m : 0.f;
             const double *w = a.box + (g0 >> 6) * kBox;
             const WaveBox wb = {w[0], w[1], w[2], w[3], w[4], w[5], w[6]};
             double kL = 0.0;

@@ -32,3 +32,14 @@ def test_steps_that_hand_lds_slots_on_are_ordered(tmp_path):
     assert len(passes) >= 30
     for n in passes:
         assert any("@" + f + "(" in fns[n] for f in fence), n
+
+
+def test_table_positions_take_the_saturating_conversion(tmp_path):
+    # a position far outside the table, or NaN, has no conversion in the language: what the
+    # compiler makes of it may index anywhere
+    fns = device_functions(os.path.join(CSRC, "table.hip"), tmp_path)
+    lookups = [n for n in fns if "6lookupILi" in n]
+    assert len(lookups) >= 3  # CIC, TSC, TSC from LDS
+    for n in lookups:
+        assert "fptoui" not in fns[n] and "fptosi" not in fns[n], n
+        assert any("@" + f + "(" in fns[n] for f in fns if "v_cvt_u32_f32" in fns[f]), n
