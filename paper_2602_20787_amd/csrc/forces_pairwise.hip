@@ -260,20 +260,24 @@ __device__ __forceinline__ void far_pass(const PairwiseArgs &a, const Owned &o, 
 // The n = 0 image of a pair inside its softening length takes the spline in
 // FP32 (selected per pair; the separation is the FP64 one cast); with a
 // softening sum above L/2 the images n != 0 may be softened too and the pair
-// is evaluated in FP64 with the spline on every image (rare).  `maybe`: the
-// pair may be softened, from a bound; `self`: no term at all, images included.
+// is evaluated in FP64 with the spline on every image (rare).  `wide`, `thr2`:
+// the pair may be softened, from a bound; `self`: no term at all, images
+// included.  MIRROR: evaluated at |d|, F_z then given the sign of d (0 at d = 0),
+// so that a pair has the same terms bit for bit from either side (as written, sums
+// over +n and -n and the compiler's contractions in them round differently at -d).
 struct PairTerms {
     double dx, dy;
     float d, S, Fz, P;
 };
 
-template <int NIMG, bool POT, int TORDER, bool COMPLETE, class Nodes>
+template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool MIRROR = false, class Nodes>
 __device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, const Nodes &nodes, double xi, double yi, double zi, float hi,
                                                   const SrcRec &src, float thr2, bool wide, bool self) {
     PairTerms t;
     t.dx = xi - src.x;
     t.dy = yi - src.y;
-    const double d64 = min_image(zi - src.z, a.L, a.invL);
+    const double signed_d = min_image(zi - src.z, a.L, a.invL);
+    const double d64 = MIRROR ? __builtin_fabs(signed_d) : signed_d;
     const float dx = (float)t.dx, dy = (float)t.dy, d = (float)d64;
     t.d = d;
     const float rho2 = __builtin_fmaf(dx, dx, dy * dy);
@@ -311,6 +315,7 @@ __device__ __forceinline__ PairTerms general_pair(const PairwiseArgs &a, const N
         t.P = (float)gp;
     }
     if (TORDER > 0) table_far<TORDER, COMPLETE>(a, nodes, dx, dy, d, self, t.S, t.Fz);
+    if (MIRROR) t.Fz = signed_tz(t.Fz, (float)signed_d);
     return t;
 }
 
@@ -372,8 +377,8 @@ __device__ __forceinline__ void near_pass(const PairwiseArgs &a, const Owned &o,
 // around it (N = 500, |n| <= 2: 66 us in ten launches), so this form has one
 // launch and no workspace (13 us, most of it the host's).  Two targets per
 // wave took 33 us against 29 at N = 2000.  The pair term of (j, i) is that of
-// (i, j) with the signs turned, bit for bit, so momentum is conserved as in
-// the pairwise form.  The lanes' FP64 sums are added in a fixed tree.
+// (i, j) with the signs turned, bit for bit (MIRROR), so momentum is conserved as
+// in the pairwise form.  The lanes' FP64 sums are added in a fixed tree.
 struct SmallArgs {
     PairwiseArgs a;
     const double *pos, *mass, *eps;
@@ -401,8 +406,8 @@ __global__ __launch_bounds__(256) void forces_small_kernel(SmallArgs p) {
         src.m = (float)p.mass[js];
         src.h = (float)p.eps[js];
         const PairTerms t =
-            general_pair<NIMG, POT, TORDER, COMPLETE>(a, GlobalNodes{a.tv.T, a.tv.w}, xi, yi, zi, hi, src, 0.f, true,
-                                                      !live || j == i);
+            general_pair<NIMG, POT, TORDER, COMPLETE, true>(a, GlobalNodes{a.tv.T, a.tv.w}, xi, yi, zi, hi, src, 0.f,
+                                                            true, !live || j == i);
         const double ms = (double)src.m, mS = ms * (double)t.S;
         acc[0] = __builtin_fma(mS, t.dx, acc[0]);
         acc[1] = __builtin_fma(mS, t.dy, acc[1]);
