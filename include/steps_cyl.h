@@ -29,7 +29,10 @@
  *    order, staged records, partial sums) come in two forms.  The *_ws form
  *    takes a caller-owned device workspace (workspace, workspace_bytes) and
  *    allocates nothing; steps_cyl_forces_workspace() returns the bytes it
- *    needs on the current device (STEPS_EINVAL if the workspace is smaller).
+ *    takes on the current device.  The pairwise paths also run in less, down to
+ *    2 sets of S sum slots per particle (1 with a table): more launches, the
+ *    same sums in another fixed order, results that agree to FP32 rounding.  A
+ *    workspace smaller than a call can run in is STEPS_EINVAL.
  *    Its contents are undefined after the call; calls that share one
  *    workspace must be ordered on one stream.  The plain form takes the same
  *    amount as stream-ordered memory (hipMallocAsync on `stream`, released

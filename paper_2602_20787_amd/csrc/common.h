@@ -80,7 +80,8 @@ int check_workspace(const Workspace &ws, size_t need);
 // The pairwise path (forces_pairwise.hip) for all N particles: every
 // unordered pair once, exact images |n| <= n_img, or with a table (non-null)
 // images |n| <= 1 plus its far images (order 1 CIC, 2 TSC).  Arguments are
-// validated by the caller; pairwise_bytes() is the workspace it takes.
+// validated by the caller; pairwise_bytes() is the workspace it takes (a smaller
+// one, down to two sets of slots, one with a table, takes more launches).
 // slot_budget > 0 bounds the bytes of its FP64 sum slots.
 size_t pairwise_bytes(int64_t N, size_t slot_budget = 0);
 int launch_forces_pairwise(const double *pos, const double *mass, const double *eps, int64_t N, double L,

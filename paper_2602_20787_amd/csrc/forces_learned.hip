@@ -652,26 +652,38 @@ Schedule learned_schedule(int64_t N) {
 
 }  // namespace
 
-size_t learned_pairwise_bytes(int64_t N) {
-    const int64_t nbox = (N + 63) / 64;
-    return ws_total({N >= kSortMin ? order_targets_bytes(N) : 0, (size_t)N * sizeof(SrcRec),
-                     (size_t)nbox * kBox * sizeof(double), slot_bytes(learned_schedule(N), N)});
+namespace {
+
+// The schedule in a workspace too small for the default one: two sets of slots, 512
+// bytes per particle (us per call, default and this one: N = 4096 523 and 885,
+// 15000 6337 and 8238, 30000 25,300 and 29,000).
+Schedule learned_lean_schedule(int64_t N) { return make_schedule(N, kOwn, kSubs, 2 * kSubs * N * kSetBytes); }
+
+size_t learned_schedule_bytes(int64_t N, const Schedule &s) {
+    return ws_total({N >= kSortMin ? order_targets_bytes(N) : 0, (size_t)N * sizeof(SrcRec), slot_bytes(s, N)});
 }
+
+}  // namespace
+
+size_t learned_pairwise_bytes(int64_t N) { return learned_schedule_bytes(N, learned_schedule(N)); }
 
 // Pairwise learned forces of all N particles (see above); arguments already
 // validated.  Scratch (spatial order, records, FP64 sums) comes from `ws`.
 int launch_forces_learned_pairwise(const double *pos, const double *mass, const double *eps, int64_t N, double L,
                                    const steps_cyl_mlp *net, float *out_acc, float *out_pot, Workspace &ws,
                                    hipStream_t stream) {
-    int rc = check_workspace(ws, learned_pairwise_bytes(N));
+    Schedule sch = learned_schedule(N);
+    if (ws.size < learned_schedule_bytes(N, sch)) {
+        const Schedule lean = learned_lean_schedule(N);
+        if (learned_schedule_bytes(N, lean) < learned_schedule_bytes(N, sch)) sch = lean;
+    }
+    int rc = check_workspace(ws, learned_schedule_bytes(N, sch));
     if (rc) return rc;
     const int *perm = nullptr;
     if (N >= kSortMin && (rc = order_targets(pos, N, L, nullptr, N, stream, ws, &perm))) return rc;
-    const Schedule sch = learned_schedule(N);
     SrcRec *rec = (SrcRec *)ws.take((size_t)N * sizeof(SrcRec));
-    double *box = (double *)ws.take((size_t)((N + 63) / 64) * kBox * sizeof(double));
     double *acc = (double *)ws.take(slot_bytes(sch, N));
-    if (!rec || !box || !acc) return fail(STEPS_EINVAL, "workspace too small for the pairwise learned path");
+    if (!rec || !acc) return fail(STEPS_EINVAL, "workspace too small for the pairwise learned path");
     PairwiseLearnedArgs pa;
     LearnedArgs &a = pa.la;
     a.x = a.y = a.z = a.m = a.h = nullptr;
@@ -696,7 +708,7 @@ int launch_forces_learned_pairwise(const double *pos, const double *mass, const 
     pa.tie = 1e-12 * L;
     pa.tie32 = (float)(0.5 * L * (1.0 - 1e-6));
     pa.N = (int)N;
-    hipError_t e = launch_stage(pos, mass, eps, (int)N, L, perm, rec, box, stream);
+    hipError_t e = launch_stage(pos, mass, eps, (int)N, L, perm, rec, nullptr, stream);
     if (e == hipSuccess)
         e = each_launch(sch, (int)N, kOwn, [&](const Rounds &rd, unsigned blocks) {
             pa.rd = rd;

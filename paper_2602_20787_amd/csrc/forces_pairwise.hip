@@ -18,19 +18,21 @@
 // every launch ends in a tail of half-empty SIMDs.  So as many rounds share a
 // launch as the slots' memory allows (kSlotBytes), up to one launch of one
 // group of all parts (flat: S = P, every slot written once), and where even
-// that has too few tiles each is split over Q waves of 64/Q sources.
+// that has too few tiles each is split over the two or four waves of a workgroup.
 //
 // Workgroup.  One wave owns its part, one particle per lane, in registers;
 // the tile's sources come through LDS: at step s lane l takes source l xor s,
 // so no two lanes meet the same source at once.  The reaction on a source is
 // summed in FP64 in an LDS slot that the lanes update in turn (64 steps visit
-// every lane).  A tile of n = 64/Q sources holds them Q times over and takes n
-// steps; the Q reactions on a source are added at the end.  A
+// every lane).  Of Q waves each takes n = 64/Q of the sources, held Q times over,
+// in n steps; the Q reactions on a source are added at the end, and wave 0 adds
+// the waves' sums of the part (in slots of their own they would take Q times the
+// workspace).  A
 // tile whose sources' box is far from the wave's (no pair closer than
 // the sum of the largest softenings, no axial separation near L/2) skips the
 // softening and half-period screens and the per-pair minimum image; the pair
-// arithmetic is the same either way.  One-wave workgroups need no barrier
-// between waves.  Small register sets let several of them share a SIMD,
+// arithmetic is the same either way.  Waves share nothing up to that last sum, so
+// their steps need no barrier.  Small register sets let several of them share a SIMD,
 // which hides the latency of the transcendentals (17 reciprocal square
 // roots per pair) and of the LDS traffic behind the other waves' work.
 #include <algorithm>
@@ -46,8 +48,8 @@ namespace steps {
 
 namespace {
 
-constexpr int kThreads = 64;  // one wave
-constexpr int kPart = 64;     // particles per part, one per lane
+constexpr int kPart = 64;  // particles per part, one per lane
+constexpr int kSplit = 4;  // most waves of a split tile
 // The one-launch form up to this many particles.  Per call (us, |n| <= 8 with
 // the potential), one launch against tiles: N = 500 13 and 50, 1000 13 and 38,
 // 2000 29 and 40, 2500 47 and 42.
@@ -67,7 +69,7 @@ constexpr int waves_per_simd(int torder) { return torder > 0 ? 4 : 5; }
 struct PairwiseArgs {
     const SrcRec *rec;   // [N] records in spatial order
     const double *box;   // [ceil(N/64)][8] bounding boxes of aligned runs of 64 records
-    double *sum;         // [M S Q][4][N] FP64 sums in spatial order (x, y, z, potential)
+    double *sum;         // [M S][4][N] FP64 sums in spatial order (x, y, z, potential)
     double L, invL, halfL, tie;  // tie: |d| within this of L/2 takes the check
     double far_h;                // largest softening sum for which the fast path is allowed
     float tie32;                 // FP32 screen for it: 0.5 L (1 - 1e-6), below every such |d|
@@ -424,16 +426,25 @@ __global__ __launch_bounds__(256) void forces_small_kernel(SmallArgs p) {
     }
 }
 
-// One tile: `own` workgroups of round 0 (tiles i <= j of every group, Q waves
-// each), then S^2 per meeting of the launch's other rounds.
-template <int NIMG, bool POT, int TORDER, bool COMPLETE>
-__global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairwise_kernel(PairwiseArgs a) {
-    __shared__ Stage<TORDER> st;
-    const int lane = threadIdx.x;
+// One tile: tiles i <= j of every group (round 0), then S^2 per meeting of the
+// launch's other rounds.  SPLIT: by several waves, in flat calls.  In the one-wave
+// form n is left to run time and barriers stand where a fence would do, for what the
+// compiler makes of the loops: with 64 for n and fences N = 131072, |n| <= 8, takes
+// 28.0 ms without the potential in place of 27.0, with 64 and barriers 32.1 in place
+// of 30.0 with it.
+template <int NIMG, bool POT, int TORDER, bool COMPLETE, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64, waves_per_simd(TORDER)) void forces_pairwise_kernel(
+    PairwiseArgs a) {
+    __shared__ Stage<TORDER> one;
+    extern __shared__ double each[];  // SPLIT: a Stage per wave
+    Stage<TORDER> *const stages = SPLIT ? reinterpret_cast<Stage<TORDER> *>(each) : &one;
+    const int lane = SPLIT ? threadIdx.x & 63 : threadIdx.x;
+    const int wave = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    Stage<TORDER> &st = stages[wave];
     const Tile t = tile_of(a.rd, blockIdx.x);
-    const int n = kPart / a.rd.Q;  // sources of the tile
+    const int n = kPart / (SPLIT ? (int)blockDim.x / 64 : a.rd.Q);              // sources of the wave
     const int64_t g0 = min((int64_t)a.N, (int64_t)t.pa * kPart);                // first owned record
-    const int64_t b0 = min((int64_t)a.N, (int64_t)t.pb * kPart + t.q * n);      // first source record
+    const int64_t b0 = min((int64_t)a.N, (int64_t)t.pb * kPart + wave * n);     // first source record
     const int ocnt = (int)min((int64_t)kPart, (int64_t)a.N - g0);               // owned records
     const int cnt = (int)min((int64_t)n, (int64_t)a.N - b0);                    // sources
     const bool react = t.pa != t.pb;
@@ -465,7 +476,10 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
         st.h[lane] = sr.h;
         const double *w = a.box + (g0 >> 6) * kBox, *b = a.box + (b0 >> 6) * kBox;
         const WaveBox wb = {w[0], w[1], w[2], w[3], w[4], w[5], w[6]};
-        __syncthreads();
+        if (SPLIT)
+            hand_over();
+        else
+            __syncthreads();
         double kL = 0.0;
         const int kind = react ? __builtin_amdgcn_readfirstlane(tile_kind(a, wb, b, kL)) : kNear;
         if (!react)
@@ -476,7 +490,10 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
             far_pass<NIMG, POT, TORDER, COMPLETE, kWrap>(a, o, st, n, kL, acc);
         else
             near_pass<NIMG, POT, TORDER, COMPLETE, true>(a, o, st, n, (int)b0, cnt, (float)b[6], acc);
-        __syncthreads();
+        if (SPLIT)
+            hand_over();
+        else
+            __syncthreads();
         // the lane's addresses are formed here: held over the loops they would cost 4 VGPRs
         asm volatile("" : "+v"(out));
         if (react && out < cnt) {
@@ -493,6 +510,20 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(TORDER)) void forces_pairw
     } else if (a.rd.first && react && lane < cnt) {
 #pragma unroll
         for (int c = 0; c < (POT ? 4 : 3); ++c) pb[(int64_t)c * a.N + lane] = 0.0;
+    }
+    if (SPLIT) {
+        // the waves' sums of the part, in wave order
+        hand_over();
+        double *const mine[4] = {st.x, st.y, st.z, st.r[3]};
+#pragma unroll
+        for (int c = 0; c < (POT ? 4 : 3); ++c) mine[c][lane] = acc[c];
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 1; w < (int)blockDim.x / 64; ++w) {
+            const double *const other[4] = {stages[w].x, stages[w].y, stages[w].z, stages[w].r[3]};
+#pragma unroll
+            for (int c = 0; c < (POT ? 4 : 3); ++c) acc[c] += other[c][lane];
+        }
     }
     if (out < ocnt && (a.rd.first || cnt > 0)) {
 #pragma unroll
@@ -713,10 +744,20 @@ struct Launcher {
                     return hipGetLastError();
                 });
         }
+        // Tiles are split while they would not fill the device (us per call over 1, 2
+        // and 4 waves: |n| <= 8 N = 4096 75, 65, 59; 6000 111, 102, 101; 8000 161, 160,
+        // 158; 9000 196, 196, 198; CIC 4096 58, 59, 54; 8000 131, 131, 136; TSC from the
+        // caches, which more waves share, 2800 55, 46, 47).
+        const int64_t tiles = (int64_t)s.S * (s.S + 1) / 2;
+        const int waves = !s.flat ? 1 : tiles <= (TORDER == 2 ? 1024 : 4096) ? kSplit : tiles <= 8192 ? 2 : 1;
         return each_launch(s, a.N, kPart, [&](const Rounds &rd, unsigned blocks) {
             a.rd = rd;
-            hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE>), dim3(blocks), dim3(kThreads), 0,
-                               stream, a);
+            if (waves > 1)
+                hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE, true>), dim3(blocks),
+                                   dim3(64 * waves), waves * sizeof(Stage<TORDER>), stream, a);
+            else
+                hipLaunchKernelGGL((forces_pairwise_kernel<NIMG, POT, TORDER, COMPLETE, false>), dim3(blocks), dim3(64),
+                                   0, stream, a);
             return hipGetLastError();
         });
     }
@@ -761,13 +802,16 @@ namespace {
 Schedule pairwise_schedule(int64_t N, size_t budget) {
     // groups of 16 parts, 8 above 2^21 particles, where a call has enough
     // meetings and the slots would grow past 1 GiB
-    Schedule s = make_schedule(N, kPart, N <= ((int64_t)1 << 21) ? 16 : 8, budget);
-    // flat: tiles split while they would not fill the device (us per call at
-    // Q = 1, 2, 4: N = 2800 49, 43, 43; 4096 78, 70, 68; 6000 114, 103, 110;
-    // 8000 166, 162, 168)
-    const int64_t tiles = (int64_t)s.S * (s.S + 1) / 2;
-    if (s.flat) s.Q = tiles <= 1024 ? 4 : tiles <= 8192 ? 2 : 1;
-    return s;
+    return make_schedule(N, kPart, N <= ((int64_t)1 << 21) ? 16 : 8, budget);
+}
+
+// The schedule in a workspace too small for the default one: two sets of slots
+// (1 KiB per particle up to 2^21), one with a table.  It takes a launch per round
+// or two (us per call, default and this one, |n| <= 8: N = 4096 59 and 91, 15000
+// 482 and 707, 30000 1770 and 2115, 60000 6800 and 7120).
+Schedule lean_schedule(int64_t N, bool table) {
+    const int S = N <= ((int64_t)1 << 21) ? 16 : 8;
+    return make_schedule(N, kPart, S, (size_t)(table ? 1 : 2) * S * N * kSetBytes);
 }
 
 size_t schedule_bytes(int64_t N, const Schedule &s) {
@@ -789,9 +833,12 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
                            int n_img, const steps_cyl_table *table, int order, float *out_acc, float *out_pot,
                            Workspace &ws, hipStream_t stream, size_t slot_budget) {
     Schedule sch = pairwise_schedule(N, slot_budget);
+    if (slot_budget == 0 && ws.size < schedule_bytes(N, sch)) {
+        const Schedule lean = lean_schedule(N, table != nullptr);
+        if (schedule_bytes(N, lean) < schedule_bytes(N, sch)) sch = lean;
+    }
     int rc = check_workspace(ws, schedule_bytes(N, sch));
     if (rc) return rc;
-    if (table && order == 2 && lds_table(table_view(table), N)) sch.Q = 1;  // fewer slots than there is room for
     PairwiseArgs a;
     a.L = L;
     a.invL = 1.0 / L;

@@ -54,8 +54,8 @@ struct Schedule {
 };
 
 // Groups of `S` parts of `part` particles, as many sets as fit `budget` bytes (0:
-// the default); a budget under the default above kScratchN (the static array's)
-// may take fewer parts per group.  Flat where all parts' slots fit.
+// the default); a budget above kScratchN that holds no set of S (the static
+// array's) takes fewer parts per group.  Flat where all parts' slots fit.
 inline Schedule make_schedule(int64_t N, int part, int S, size_t budget) {
     const int64_t P = (N + part - 1) / part;
     const bool fixed = budget > 0 && N > kScratchN;
@@ -163,9 +163,9 @@ __device__ __forceinline__ void hand_over() { __builtin_amdgcn_fence(__ATOMIC_AC
 
 constexpr int kBox = 8;  // doubles per 64-record box
 
-// Records in the order of `perm` (null: the particles' own) and the bounding
-// box {x_lo, x_hi, y_lo, y_hi, z_lo, z_hi, h_max, 0} of every aligned run of
-// 64; one wave per run.
+// Records in the order of `perm` (null: the particles' own) and, with `box`, the
+// bounding box {x_lo, x_hi, y_lo, y_hi, z_lo, z_hi, h_max, 0} of every aligned run
+// of 64; one wave per run.
 __global__ __launch_bounds__(256) void stage_kernel(const double *pos, const double *mass, const double *eps, int N,
                                                     double L, const int *perm, SrcRec *rec, double *box) {
     const int b = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
@@ -192,6 +192,7 @@ __global__ __launch_bounds__(256) void stage_kernel(const double *pos, const dou
         for (int c = 0; c < 6; ++c) v[c] = HUGE_VAL;  // neutral for the minima
         v[6] = 0.0;
     }
+    if (!box) return;
     // minima of (x, -x, y, -y, z, -z), maximum of h, over the wave
     for (int off = 32; off >= 1; off >>= 1) {
         for (int c = 0; c < 6; ++c) v[c] = fmin(v[c], __shfl_xor(v[c], off));
