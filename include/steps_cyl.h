@@ -51,10 +51,14 @@
  *    m (C = min(ceil(8192 / target blocks), ceil(N / m)), m = 256 sources and
  *    target blocks of 256 targets, with a network 1024 and 128); each chunk's
  *    compensated totals go to the workspace in FP64 (32 C bytes per target)
- *    and are added in a fixed order.  Results are deterministic, and two calls
- *    on the same particles give a target bit for bit the same result whenever
- *    they take the same C (always for N <= 4096 and lists of up to 131,072
- *    targets); otherwise they agree to FP32 rounding.
+ *    and are added in a fixed order.  In a workspace smaller than for that, C =
+ *    min(ceil(2048 / target blocks), ceil(N / 4096)).  For N <= 4096 the chunks
+ *    are the ceil(N / m) ones in any case (a list of more than 8192 / C target
+ *    blocks takes several launches, totals for one of them; without room for
+ *    totals the kernel itself adds the chunks).  Results are deterministic, and
+ *    two calls on the same particles give a target bit for bit the same result
+ *    whenever they take the same C (always for N <= 4096); otherwise they agree
+ *    to FP32 rounding.
  *  - Every call is asynchronous on `stream` (0 = the null stream); results
  *    are valid after the stream is synchronised.  Argument errors are found
  *    on the host before any device work and return a negative status; the

@@ -34,8 +34,9 @@
 // idle, the sources are split into chunks too (a grid of target blocks x
 // source chunks): each workgroup writes its compensated totals in FP64 to
 // the workspace and a second pass adds the chunks in a fixed order.  The chunking
-// depends only on the list's length and N, so results stay deterministic;
-// lists long enough to fill the device take one chunk and the direct write.
+// depends only on the list's length, N and the workspace, so results stay
+// deterministic; lists long enough to fill the device take one chunk and the direct
+// write, or with few sources the same chunks (target_chunks).
 #include <algorithm>
 
 #include "common.h"
@@ -55,14 +56,16 @@ struct ExactArgs {
     const int64_t *targets;  // null: target k is particle k
     const int *perm;         // list positions in spatial order of their targets, or null
     float *ax, *ay, *az, *pot;
-    double *part;            // [chunks][4][n_tgt] chunk totals, or null for one chunk
+    double *part;            // [chunks][4][n_tgt] chunk totals by the targets' order, or null for one chunk
     double L, invL, halfL;
     ImageConsts c;
     int N, n_tgt;
     int chunk;               // sources per chunk (a multiple of kBlock, or N)
+    int fold, fold_run;      // folded: sources per chunk and chunks per run, else 0
 };
 
-template <int NIMG, bool POT, bool COMP>
+// FOLD: the chunks in turn (at run time it cost the others 1 %)
+template <int NIMG, bool POT, bool COMP, bool FOLD>
 __global__ __launch_bounds__(kBlock) void forces_exact_kernel(ExactArgs a) {
     __shared__ SrcRec tile[kBlock];
     const int tid = threadIdx.x;
@@ -77,6 +80,9 @@ __global__ __launch_bounds__(kBlock) void forces_exact_kernel(ExactArgs a) {
     float cx = 0.f, cy = 0.f, cz = 0.f, cp = 0.f;  // Kahan compensations
 
     __shared__ float wave_hmax[kBlock / 64];
+    extern __shared__ double folded[];
+    if (FOLD)
+        for (int c = 0; c < 8; ++c) folded[c * kBlock + tid] = 0.0;
     const int j0 = blockIdx.y * a.chunk, j1 = min(a.N, j0 + a.chunk);
     for (int base = j0; base < j1; base += kBlock) {
         const int j = base + tid;
@@ -152,16 +158,29 @@ __global__ __launch_bounds__(kBlock) void forces_exact_kernel(ExactArgs a) {
             }
         }
         __syncthreads();
+        const int next = base + kBlock;
+        if (FOLD && (next % a.fold == 0 || next >= j1)) {
+            fold_chunk(folded + tid, kBlock, (double)sx - (double)cx, (double)sy - (double)cy, (double)sz - (double)cz,
+                       (double)sp - (double)cp, next >= j1 || next / a.fold % a.fold_run == 0);
+            sx = sy = sz = sp = 0.f;
+            cx = cy = cz = cp = 0.f;
+        }
     }
     if (active) {
         // attraction: a = -sum m_j S (x_i - x_j), potential = -sum m_j / r
         const int64_t o = kk;
         if (a.part) {
-            double *q = a.part + (int64_t)blockIdx.y * 4 * a.n_tgt + o;
+            double *q = a.part + (int64_t)blockIdx.y * 4 * a.n_tgt + k;
             q[0] = (double)sx - (double)cx;
             q[a.n_tgt] = (double)sy - (double)cy;
             q[2 * (int64_t)a.n_tgt] = (double)sz - (double)cz;
             q[3 * (int64_t)a.n_tgt] = (double)sp - (double)cp;
+        } else if (FOLD) {
+            const double *f = folded + 4 * kBlock + tid;
+            a.ax[o] = (float)(-f[0]);
+            a.ay[o] = (float)(-f[kBlock]);
+            a.az[o] = (float)(-f[2 * kBlock]);
+            if (POT) a.pot[o] = (float)(-f[3 * kBlock]);
         } else {
             a.ax[o] = -(sx - cx);
             a.ay[o] = -(sy - cy);
@@ -175,7 +194,11 @@ template <int NIMG, bool POT, bool COMP>
 hipError_t launch_t(const ExactArgs &a, hipStream_t stream) {
     const int grid = (a.n_tgt + kBlock - 1) / kBlock;
     const int chunks = (a.N + a.chunk - 1) / a.chunk;
-    hipLaunchKernelGGL((forces_exact_kernel<NIMG, POT, COMP>), dim3(grid, chunks), dim3(kBlock), 0, stream, a);
+    if (a.fold)
+        hipLaunchKernelGGL((forces_exact_kernel<NIMG, POT, COMP, true>), dim3(grid, chunks), dim3(kBlock),
+                           8 * kBlock * sizeof(double), stream, a);
+    else
+        hipLaunchKernelGGL((forces_exact_kernel<NIMG, POT, COMP, false>), dim3(grid, chunks), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -193,25 +216,10 @@ hipError_t launch_nimg(const ExactArgs &a, hipStream_t stream) {
 
 }  // namespace
 
-// Source chunks of the per-target kernels for n_tgt targets of N sources:
-// enough (target block, chunk) pairs for 8192 workgroups (eight to a CU's
-// four resident ones, so that the last to finish cost little), chunks of at
-// least min_chunk sources; one chunk once the targets fill the device.  The
-// exact kernel's us per call with 2048 workgroups and 4096 sources, and now:
-// 256 of 262144 particles 1428 -> 321, 4096 of them 4215 -> 3945, 1000 of
-// 50000 1365 -> 282, 300 of 10000 484 -> 50.
-int per_target_chunks(int64_t N, int64_t n_tgt, int block, int min_chunk) {
-    const int64_t tblocks = (n_tgt + block - 1) / block;
-    int64_t c = (8192 + tblocks - 1) / tblocks;
-    c = std::min<int64_t>(c, (N + min_chunk - 1) / min_chunk);
-    return (int)std::max<int64_t>(1, c);
-}
-
 // Workspace of the per-target exact kernel: the spatial order of a long
 // list, and the chunk totals of a short one.
 size_t exact_per_target_bytes(int64_t N, int64_t n_tgt) {
-    const int chunks = per_target_chunks(N, n_tgt, kBlock, kBlock);
-    return ws_total({per_target_bytes(n_tgt), chunks > 1 ? (size_t)chunks * 4 * n_tgt * sizeof(double) : 0});
+    return list_bytes(n_tgt, target_chunks(N, n_tgt, kBlock, kBlock, SIZE_MAX));
 }
 
 // Launches the FP32 exact-force kernel; arguments already validated.
@@ -240,27 +248,39 @@ int launch_forces_exact(const double *pos, const double *mass, const double *eps
     a.n_tgt = (int)n_tgt;
     a.perm = nullptr;
     // walk the targets in spatial order (keys and order in the workspace)
-    int rc = check_workspace(ws, exact_per_target_bytes(N, n_tgt));
+    const Chunks chunks = chunks_in(ws.size, N, n_tgt, kBlock, kBlock);
+    int rc = check_workspace(ws, list_bytes(n_tgt, chunks));
     if (rc) return rc;
     if (n_tgt >= kOrderTargetsMin && (rc = order_targets(pos, N, L, targets, n_tgt, stream, ws, &a.perm)))
         return rc;
-    const int chunks = per_target_chunks(N, n_tgt, kBlock, kBlock);
     a.chunk = (int)N;
+    a.fold = a.fold_run = 0;
     a.part = nullptr;
-    if (chunks > 1) {
-        a.chunk = (int)(((N + chunks - 1) / chunks + kBlock - 1) / kBlock * kBlock);
-        a.part = (double *)ws.take((size_t)chunks * 4 * n_tgt * sizeof(double));
+    const int chunk = (int)(((N + chunks.n - 1) / chunks.n + kBlock - 1) / kBlock * kBlock);
+    const int totals = (int)((N + chunk - 1) / chunk);
+    if (chunks.folded) {
+        a.fold = chunk;
+        a.fold_run = (totals + finish_waves(totals) - 1) / finish_waves(totals);
+    } else if (chunks.n > 1) {
+        a.chunk = chunk;
+        a.part = (double *)ws.take(totals_bytes(chunks));
         if (!a.part) return fail(STEPS_EINVAL, "workspace too small for the chunk totals");
     }
-    hipError_t e;
     const bool comp = (mode == STEPS_SUM_COMPENSATED);
-    if (out_pot)
-        e = comp ? launch_nimg<true, true>(a, stream) : launch_nimg<true, false>(a, stream);
-    else
-        e = comp ? launch_nimg<false, true>(a, stream) : launch_nimg<false, false>(a, stream);
-    if (e == hipSuccess && a.part) {
-        const Schedule sch = {(int)((N + a.chunk - 1) / a.chunk), 1, 1, true};  // a slot per chunk
-        e = launch_finish(sch, a.part, kBlock, nullptr, (int)n_tgt, out_acc, out_pot, stream);
+    const int *perm = a.perm;
+    hipError_t e = hipSuccess;
+    for (int64_t k = 0; e == hipSuccess && k < n_tgt; k += chunks.piece) {
+        // a list in pieces has an order
+        a.n_tgt = (int)std::min(chunks.piece, n_tgt - k);
+        a.perm = perm ? perm + k : nullptr;
+        if (out_pot)
+            e = comp ? launch_nimg<true, true>(a, stream) : launch_nimg<true, false>(a, stream);
+        else
+            e = comp ? launch_nimg<false, true>(a, stream) : launch_nimg<false, false>(a, stream);
+        if (e == hipSuccess && a.part) {
+            const Schedule sch = {totals, 1, 1, true};  // a slot per chunk
+            e = launch_finish(sch, a.part, kBlock, a.perm, a.n_tgt, out_acc, n_tgt, out_pot, stream);
+        }
     }
     return hip_status(e, "forces_exact launch");
 }

@@ -61,12 +61,13 @@ struct LearnedArgs {
     const int *perm;  // list positions in spatial order of their targets, or null
     const mlp::Packed *P;
     float *ax, *ay, *az, *pot;
-    double *part;     // [chunks][4][n_tgt] chunk totals of a short list, or null
+    double *part;     // [chunks][4][n_tgt] chunk totals by the targets' order, or null
     double L, invL, halfL;
     float invLf, invL2f;
     ImageConsts c;  // n_img = 1
     int N, n_tgt;
     int chunk;        // sources per chunk (a multiple of kTile, or N)
+    int fold, fold_run;  // folded: sources per chunk and chunks per run, else 0
     BandSeries bs;    // near-axis band
 };
 
@@ -217,6 +218,9 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_kernel(LearnedArgs a
     float sx = 0.f, sy = 0.f, sz = 0.f, sp = 0.f;
     float cx = 0.f, cy = 0.f, cz = 0.f, cp = 0.f;
 
+    extern __shared__ double folded[];
+    if (a.fold)
+        for (int c = 0; c < 8; ++c) folded[c * kBlock + tid] = 0.0;
     const int j0 = blockIdx.y * a.chunk, j1 = min(a.N, j0 + a.chunk);
     for (int base = j0; base < j1; base += kTile) {
         __syncthreads();
@@ -293,6 +297,16 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_kernel(LearnedArgs a
                 if (POT) kahan_add(sp, cp, pp);
             }
         }
+        const int next = base + kTile;
+        if (a.fold && (next % a.fold == 0 || next >= j1)) {
+            const float ox = __shfl_xor(sx - cx, 32), oy = __shfl_xor(sy - cy, 32);
+            const float oz = __shfl_xor(sz - cz, 32), op = __shfl_xor(sp - cp, 32);
+            fold_chunk(folded + tid, kBlock, (double)(sx - cx) + (double)ox, (double)(sy - cy) + (double)oy,
+                       (double)(sz - cz) + (double)oz, (double)(sp - cp) + (double)op,
+                       next >= j1 || next / a.fold % a.fold_run == 0);
+            sx = sy = sz = sp = 0.f;
+            cx = cy = cz = cp = 0.f;
+        }
     }
     // combine the halves: value and compensation of the odd sources join the even ones
     const float ox = __shfl_xor(sx - cx, 32), oy = __shfl_xor(sy - cy, 32);
@@ -300,11 +314,17 @@ __global__ __launch_bounds__(kBlock, 3) void forces_learned_kernel(LearnedArgs a
     if (active && h == 0) {
         const int64_t o = kk;
         if (a.part) {
-            double *q = a.part + (int64_t)blockIdx.y * 4 * a.n_tgt + o;
+            double *q = a.part + (int64_t)blockIdx.y * 4 * a.n_tgt + k;
             q[0] = (double)(sx - cx) + (double)ox;
             q[a.n_tgt] = (double)(sy - cy) + (double)oy;
             q[2 * (int64_t)a.n_tgt] = (double)(sz - cz) + (double)oz;
             q[3 * (int64_t)a.n_tgt] = (double)(sp - cp) + (double)op;
+        } else if (a.fold) {
+            const double *f = folded + 4 * kBlock + tid;
+            a.ax[o] = (float)(-f[0]);
+            a.ay[o] = (float)(-f[kBlock]);
+            a.az[o] = (float)(-f[2 * kBlock]);
+            if (POT) a.pot[o] = (float)(-f[3 * kBlock]);
         } else {
             a.ax[o] = -((sx - cx) + ox);
             a.ay[o] = -((sy - cy) + oy);
@@ -318,7 +338,8 @@ template <bool POT, bool COMP>
 hipError_t launch_t(const LearnedArgs &a, hipStream_t stream) {
     const int grid = (a.n_tgt + kTargets - 1) / kTargets;
     const int chunks = (a.N + a.chunk - 1) / a.chunk;
-    hipLaunchKernelGGL((forces_learned_kernel<POT, COMP>), dim3(grid, chunks), dim3(kBlock), 0, stream, a);
+    hipLaunchKernelGGL((forces_learned_kernel<POT, COMP>), dim3(grid, chunks), dim3(kBlock),
+                       a.fold ? 8 * kBlock * sizeof(double) : 0, stream, a);
     return hipGetLastError();
 }
 
@@ -328,14 +349,11 @@ namespace mlp {
 const Packed *packed_of(const steps_cyl_mlp *net);
 }
 
-int per_target_chunks(int64_t N, int64_t n_tgt, int block, int min_chunk);
-
 // Workspace of the per-target learned kernel: the spatial order of a long
 // list and the chunk totals of a short one (sources split into chunks when
 // the target blocks alone would leave the device idle; see forces_exact.hip).
 size_t learned_per_target_bytes(int64_t N, int64_t n_tgt) {
-    const int chunks = per_target_chunks(N, n_tgt, kTargets, kMinChunk);
-    return ws_total({per_target_bytes(n_tgt), chunks > 1 ? (size_t)chunks * 4 * n_tgt * sizeof(double) : 0});
+    return list_bytes(n_tgt, target_chunks(N, n_tgt, kTargets, kMinChunk, SIZE_MAX));
 }
 
 namespace {
@@ -423,27 +441,39 @@ int launch_forces_learned(const double *pos, const double *mass, const double *e
     a.n_tgt = (int)n_tgt;
     a.perm = nullptr;
     // walk the targets in spatial order (keys and order in the workspace)
-    int rc = check_workspace(ws, learned_per_target_bytes(N, n_tgt));
+    const Chunks chunks = chunks_in(ws.size, N, n_tgt, kTargets, kMinChunk);
+    int rc = check_workspace(ws, list_bytes(n_tgt, chunks));
     if (rc) return rc;
     if (n_tgt >= kOrderTargetsMin && (rc = order_targets(pos, N, L, targets, n_tgt, stream, ws, &a.perm)))
         return rc;
-    const int chunks = per_target_chunks(N, n_tgt, kTargets, kMinChunk);
     a.chunk = (int)N;
+    a.fold = a.fold_run = 0;
     a.part = nullptr;
-    if (chunks > 1) {
-        a.chunk = (int)(((N + chunks - 1) / chunks + kTile - 1) / kTile * kTile);
-        a.part = (double *)ws.take((size_t)chunks * 4 * n_tgt * sizeof(double));
+    const int chunk = (int)(((N + chunks.n - 1) / chunks.n + kTile - 1) / kTile * kTile);
+    const int totals = (int)((N + chunk - 1) / chunk);
+    if (chunks.folded) {
+        a.fold = chunk;
+        a.fold_run = (totals + finish_waves(totals) - 1) / finish_waves(totals);
+    } else if (chunks.n > 1) {
+        a.chunk = chunk;
+        a.part = (double *)ws.take(totals_bytes(chunks));
         if (!a.part) return fail(STEPS_EINVAL, "workspace too small for the chunk totals");
     }
     const bool comp = (mode == STEPS_SUM_COMPENSATED);
-    hipError_t e;
-    if (out_pot)
-        e = comp ? launch_t<true, true>(a, stream) : launch_t<true, false>(a, stream);
-    else
-        e = comp ? launch_t<false, true>(a, stream) : launch_t<false, false>(a, stream);
-    if (e == hipSuccess && a.part) {
-        const Schedule sch = {(int)((N + a.chunk - 1) / a.chunk), 1, 1, true};  // a slot per chunk
-        e = launch_finish(sch, a.part, kTargets, nullptr, (int)n_tgt, out_acc, out_pot, stream);
+    const int *perm = a.perm;
+    hipError_t e = hipSuccess;
+    for (int64_t k = 0; e == hipSuccess && k < n_tgt; k += chunks.piece) {
+        // a list in pieces has an order
+        a.n_tgt = (int)std::min(chunks.piece, n_tgt - k);
+        a.perm = perm ? perm + k : nullptr;
+        if (out_pot)
+            e = comp ? launch_t<true, true>(a, stream) : launch_t<true, false>(a, stream);
+        else
+            e = comp ? launch_t<false, true>(a, stream) : launch_t<false, false>(a, stream);
+        if (e == hipSuccess && a.part) {
+            const Schedule sch = {totals, 1, 1, true};  // a slot per chunk
+            e = launch_finish(sch, a.part, kTargets, a.perm, a.n_tgt, out_acc, n_tgt, out_pot, stream);
+        }
     }
     return hip_status(e, "forces_learned launch");
 }
@@ -718,7 +748,7 @@ int launch_forces_learned_pairwise(const double *pos, const double *mass, const 
                 hipLaunchKernelGGL((forces_learned_pairwise_kernel<false>), dim3(blocks), dim3(kBlock), 0, stream, pa);
             return hipGetLastError();
         });
-    if (e == hipSuccess) e = launch_finish(sch, pa.acc, kOwn, perm, (int)N, out_acc, out_pot, stream);
+    if (e == hipSuccess) e = launch_finish(sch, pa.acc, kOwn, perm, (int)N, out_acc, N, out_pot, stream);
     return hip_status(e, "forces_learned_pairwise launch");
 }
 

@@ -882,7 +882,7 @@ int launch_forces_pairwise(const double *pos, const double *mass, const double *
     hipError_t e = launch_stage(pos, mass, eps, (int)N, L, perm, rec, box, stream);
     if (e == hipSuccess)
         e = dispatch(a.c.n_img, out_pot != nullptr, ord, complete, [&](auto l) { return l.run(a, sch, stream); });
-    if (e == hipSuccess) e = launch_finish(sch, a.sum, kPart, perm, (int)N, out_acc, out_pot, stream);
+    if (e == hipSuccess) e = launch_finish(sch, a.sum, kPart, perm, (int)N, out_acc, N, out_pot, stream);
     return hip_status(e, "forces_pairwise launch");
 }
 

@@ -246,6 +246,72 @@ __global__ __launch_bounds__(1024) void finish_kernel(const double *sum, int slo
     }
 }
 
+// ---- per-target lists: source chunks, whose totals are slots of launch_finish
+
+inline int finish_waves(int slots) { return slots > 64 ? 16 : 4; }
+
+// Up to this many sources a target's bits do not depend on the list.
+constexpr int64_t kSameBits = 4096;
+
+struct Chunks {
+    int n;
+    bool folded;    // a workgroup takes every chunk and adds their totals itself
+    int64_t piece;  // targets per launch
+};
+
+// Source chunks for n_tgt targets of N sources in blocks of `block`: enough
+// (target block, chunk) pairs for 8192 workgroups (eight to a CU's four resident
+// ones, so that the last to finish cost little), chunks of at least min_chunk
+// sources; one chunk once the targets fill the device.  The exact kernel's us per
+// call with 2048 workgroups and 4096 sources, and so: 256 of 262144 particles 1428
+// -> 321, 4096 of them 4215 -> 3945, 1000 of 50000 1365 -> 282, 300 of 10000 484 ->
+// 50.  Where `room` bytes do not hold the totals the former two numbers apply.  Up to
+// kSameBits sources the chunks are the same in any case: long lists go in pieces that
+// fill the device, and where the totals have no room they are folded (140,003
+// targets of 4096, |n| <= 8: 2321 and 3240 us).
+inline Chunks target_chunks(int64_t N, int64_t n_tgt, int block, int min_chunk, size_t room) {
+    const int64_t blocks = (n_tgt + block - 1) / block;
+    auto chunks = [&](int64_t groups, int64_t least) {
+        return (int)std::min((groups + blocks - 1) / blocks, (N + least - 1) / least);
+    };
+    if (N > kSameBits) {
+        const int c = chunks(8192, min_chunk);
+        return {(size_t)c * 4 * n_tgt * sizeof(double) <= room ? c : chunks(2048, 4096), false, n_tgt};
+    }
+    const int all = (int)((N + min_chunk - 1) / min_chunk);
+    const int64_t pieces = all > 1 ? (blocks * all + 8191) / 8192 : 1;
+    const int64_t piece = std::min(n_tgt, (blocks + pieces - 1) / pieces * block);
+    const bool folded = all > 1 && (size_t)all * 4 * piece * sizeof(double) > room;
+    return {all, folded, folded ? n_tgt : piece};
+}
+
+// Bytes of a launch's totals, and of those and a list's spatial order.
+inline size_t totals_bytes(const Chunks &c) {
+    return c.n > 1 && !c.folded ? (size_t)c.n * 4 * c.piece * sizeof(double) : 0;
+}
+
+inline size_t list_bytes(int64_t n_tgt, const Chunks &c) {
+    return ws_total({per_target_bytes(n_tgt), totals_bytes(c)});
+}
+
+// The chunks that a workspace of `size` bytes has room for.
+inline Chunks chunks_in(size_t size, int64_t N, int64_t n_tgt, int block, int min_chunk) {
+    const Chunks c = target_chunks(N, n_tgt, block, min_chunk, SIZE_MAX);
+    return size < list_bytes(n_tgt, c) ? target_chunks(N, n_tgt, block, min_chunk, 0) : c;
+}
+
+// Adds a chunk's totals as finish_kernel adds slots: in runs, then the runs in
+// order.  f: LDS, [8][stride], the run's sums and the total's; `ends`: of the run.
+__device__ __forceinline__ void fold_chunk(double *f, int stride, double x, double y, double z, double p, bool ends) {
+    const double v[4] = {x, y, z, p};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double r = f[c * stride] + v[c];
+        if (ends) f[(4 + c) * stride] += r;
+        f[c * stride] = ends ? 0.0 : r;
+    }
+}
+
 hipError_t launch_stage(const double *pos, const double *mass, const double *eps, int N, double L, const int *perm,
                         SrcRec *rec, double *box, hipStream_t stream) {
     const int nbox = (N + 63) / 64;
@@ -253,11 +319,12 @@ hipError_t launch_stage(const double *pos, const double *mass, const double *eps
     return hipGetLastError();
 }
 
+// `stride`: elements between the components of out_acc
 hipError_t launch_finish(const Schedule &s, const double *sum, int part, const int *perm, int N, float *out_acc,
-                         float *out_pot, hipStream_t stream) {
+                         int64_t stride, float *out_pot, hipStream_t stream) {
     const int slots = s.S * s.M;
-    hipLaunchKernelGGL(finish_kernel, dim3((N + 63) / 64, out_pot ? 4 : 3), dim3(slots * s.Q > 64 ? 1024 : 256), 0,
-                       stream, sum, slots, s.Q, part, perm, N, out_acc, out_acc + N, out_acc + 2 * (int64_t)N, out_pot);
+    hipLaunchKernelGGL(finish_kernel, dim3((N + 63) / 64, out_pot ? 4 : 3), dim3(64 * finish_waves(slots * s.Q)), 0,
+                       stream, sum, slots, s.Q, part, perm, N, out_acc, out_acc + stride, out_acc + 2 * stride, out_pot);
     return hipGetLastError();
 }
 

@@ -111,3 +111,86 @@ def test_learned(sc, N):
         assert need < full or N < 1000
         assert over_terms(a, acc, d, p.L) <= 1e-6 and (torch.abs(q - pot) / torch.abs(pot)).max().item() <= 1e-6
     net.close()
+
+
+# ---- lists of targets: the totals of the source chunks
+
+
+def lists(N, long):
+    rng = np.random.default_rng(N)
+    for T in (1, 300, 4097, long):
+        yield torch.from_numpy(rng.integers(0, N, T)).cuda()
+
+
+@pytest.mark.parametrize("N", [256, 257, 1025, 3000, 4096])
+@pytest.mark.parametrize("mode", ["compensated", "plain"])
+def test_few_sources_give_the_same_bits_in_every_list(sc, N, mode):
+    # 131,073 targets and more leave no room for chunks on the device
+    print(f"[case] lists N={N} {mode}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    d = to_dev(p)
+    m = sc.STEPS_SUM_COMPENSATED if mode == "compensated" else sc.STEPS_SUM_PLAIN
+    for n_img in (0, 1, 2, 3, 4, 8):
+        acc, pot = sc.steps_cyl_forces_ex(*d, p.L, n_img, mode=m)
+        only, _ = sc.steps_cyl_forces_ex(*d, p.L, n_img, mode=m, potential=False)
+        for t in lists(N, 140003):
+            a, q = sc.steps_cyl_forces_ex(*d, p.L, n_img, targets=t, mode=m)
+            assert torch.equal(a, acc[:, t]) and torch.equal(q, pot[t]), (n_img, t.numel())
+            # a workspace of the spatial order alone
+            n = t.numel()
+            w = nan_bytes(order_bytes(sc, n) + 256 if n >= 4096 else 256)
+            a, q = sc.steps_cyl_forces_ex_ws(*d, p.L, n_img, w, targets=t, mode=m)
+            assert torch.equal(a, acc[:, t]) and torch.equal(q, pot[t]), (n_img, n)
+            a, _ = sc.steps_cyl_forces_ex_ws(*d, p.L, n_img, w, targets=t, mode=m, potential=False)
+            assert torch.equal(a, only[:, t]), (n_img, n)
+
+
+@pytest.mark.parametrize("N", [1024, 1025, 4096])
+def test_few_sources_give_the_same_bits_with_a_network(sc, N):
+    print(f"[case] learned lists N={N}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    d = to_dev(p)
+    net = sc.Mlp.create(synth.mlp_init(seed=21, out_gain=1.0))
+    acc, pot = sc.steps_cyl_forces_learned_ex(*d, p.L, net)
+    for t in lists(N, 350003):
+        a, q = sc.steps_cyl_forces_learned_ex(*d, p.L, net, targets=t)
+        assert torch.equal(a, acc[:, t]) and torch.equal(q, pot[t]), t.numel()
+        n = t.numel()
+        a, q = sc.steps_cyl_forces_learned_ex_ws(*d, p.L, net, nan_bytes(order_bytes(sc, n) + 256 if n >= 4096 else 256),
+                                                 targets=t)
+        assert torch.equal(a, acc[:, t]) and torch.equal(q, pot[t]), n
+    net.close()
+
+
+# chunk totals in the room of 2048 workgroups of at least 4096 sources
+@pytest.mark.parametrize("N,T", [(4097, 100), (20011, 300), (60000, 5000)])
+def test_lists_in_less_workspace(sc, N, T):
+    print(f"[case] lists N={N} T={T}", flush=True)
+    p = synth.cylinder_load(N, seed=N)
+    d = to_dev(p)
+    t = torch.from_numpy(np.random.default_rng(T).choice(N, size=T, replace=False).astype(np.int64)).cuda()
+    ref, ref_pot = sc.steps_cyl_forces_f64(*d, p.L, 2, targets=t)
+    net = sc.Mlp.create(synth.mlp_init(seed=21, out_gain=1.0))
+    far, far_pot = sc.steps_cyl_forces_learned_ex(*d, p.L, net, targets=t)
+    for block, path in ((256, sc.STEPS_PATH_EXACT), (128, sc.STEPS_PATH_LEARNED)):
+        chunks = min(-(-2048 // -(-T // block)), -(-N // 4096))
+        w = nan_bytes((order_bytes(sc, T) if T >= 4096 else 0) + 32 * chunks * T + 512)
+        full = sc.steps_cyl_forces_workspace(path, N, 2, T, sc.STEPS_SUM_COMPENSATED)
+        assert w.numel() < full
+        if path == sc.STEPS_PATH_EXACT:
+            a, q = sc.steps_cyl_forces_ex_ws(*d, p.L, 2, w, targets=t)
+            r, rq = ref, ref_pot
+        else:
+            a, q = sc.steps_cyl_forces_learned_ex_ws(*d, p.L, net, w, targets=t)
+            r, rq = far, far_pot
+        # FP32 sums of 32 terms: 32 roundings of 6e-8, and the terms' own 5e-7
+        (x, y, z), m, e = d
+        dz = z[t, None] - z[None]
+        dz = dz - p.L * torch.floor(dz / p.L + 0.5)
+        r2 = (x[t, None] - x[None]) ** 2 + (y[t, None] - y[None]) ** 2 + dz ** 2
+        size = (m / torch.maximum(r2, (e[t, None] + e[None]) ** 2 / 2.2)).sum(1)
+        assert (torch.linalg.norm((a - r).double(), dim=0) / size).max().item() <= 2.5e-6
+        assert (torch.abs(q - rq) / torch.abs(rq)).max().item() <= 2.5e-6
+    with pytest.raises(sc.StepsError, match="workspace"):
+        sc.steps_cyl_forces_ex_ws(*d, p.L, 2, nan_bytes(32), targets=t)
+    net.close()
