@@ -280,14 +280,17 @@ template <int ORDER, bool POT, bool COMPLETE>
 hipError_t launch_c(const TableArgs &a, hipStream_t stream) {
     if constexpr (ORDER == 2) {
         // A workgroup per CU and round, rounds of equal size.  A table that fits the L1
-        // stays there where the last round would be nearly empty (43 x 43 nodes, ms from
-        // the L1 and from LDS: 262144 targets 260 and 193, 270000 303 and 320, 300000 349
-        // and 362, 350000 432 and 421).
+        // stays there where the last round would be nearly empty (ms from the L1 and from
+        // LDS: 43 x 43 nodes 270000 targets 288 and 320, 300000 331 and 362, 350000 424
+        // and 422; 63 x 63 nodes 480000 932 and 735), a small one from three rounds on
+        // until they are nearly full (27 x 27 nodes 600000 1065 and 1282, 700000 1402 and
+        // 1518, 750000 1589 and 1613; 63 x 63 nodes 700000 1687 and 1565).
         constexpr int round = kCus * kLdsBlock;
         const int nodes = a.tv.w * (a.tv.n_r + 3);
         const int rounds = (a.n_tgt + round - 1) / round;
-        const bool empty = rounds > 1 && a.n_tgt - (rounds - 1) * round <= round / 4;
-        if (nodes <= kLdsNodes && !(empty && nodes <= kL1Nodes)) {
+        const bool empty = a.n_tgt - (rounds - 1) * round <= round / 4;
+        const bool loose = rounds > 2 && nodes <= kL1Nodes / 2 && a.n_tgt / rounds < round / 10 * 9;
+        if (nodes <= kLdsNodes && !(rounds > 1 && nodes <= kL1Nodes && (empty || loose))) {
             const int per = (a.n_tgt + kCus * rounds - 1) / (kCus * rounds);
             const int block = std::max(kBlock, (per + 63) / 64 * 64);
             hipLaunchKernelGGL((forces_table_kernel<ORDER, POT, COMPLETE, true>), dim3((a.n_tgt + block - 1) / block),
@@ -295,10 +298,15 @@ hipError_t launch_c(const TableArgs &a, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    // TSC from the L1, once every CU has work: smaller workgroups look up less at
-    // once (160 x 160 nodes, ms per call with 256, 128 and 64 threads: 65536 of 262144
-    // particles 125, 142, 139, 200000 309, 283, 270, 2^19 1244, 1142, 1187)
-    const int block = ORDER == 2 && a.n_tgt > kCus * kBlock ? 128 : kBlock;
+    // TSC from the L1, once every CU has work: workgroups of 128 look up less at once
+    // than those of 256 (160 x 160 nodes, ms per call with 256 and 128 threads: 65536 of
+    // 262144 particles 125 and 142, 200000 309 and 283, 2^19 1244 and 1142), but waves
+    // that walk together hit more: 256 where they are all resident and no fuller on any
+    // CU (43 x 43 nodes, 300000 targets 345 and 331, 327000 378 and 354, 280000 287 and
+    // 304).
+    const int resident = kCus * kBlock * (POT ? 5 : 7);
+    const bool halves = a.n_tgt > kCus * kBlock && (a.n_tgt > resident || (a.n_tgt + kCus * 128 - 1) / (kCus * 128) % 2);
+    const int block = ORDER == 2 && halves ? 128 : kBlock;
     hipLaunchKernelGGL((forces_table_kernel<ORDER, POT, COMPLETE, false>), dim3((a.n_tgt + block - 1) / block),
                        dim3(block), 0, stream, a);
     return hipGetLastError();

@@ -56,3 +56,24 @@ def test_tsc_lists(sc, n_grid, complete, pot):
         err = np.linalg.norm(acc.double().cpu().numpy()[:, tg] - ref, axis=0)
         assert err.max() <= 2e-5 * rms
     tab.close()
+
+
+# small tables and a large one past one round of 262144 targets: in the caches with
+# workgroups of 128 and of 256 threads, in LDS over two and three rounds
+@pytest.mark.parametrize("n_grid", [24, 60, 140])
+@pytest.mark.parametrize("n", [98305, 280000, 300000, 327681, 480000, 600000, 786432])
+def test_long_tsc_lists(sc, n_grid, n):
+    N = 257
+    print(f"[case] TSC lists grid={n_grid} n={n}", flush=True)
+    p = synth.clustered_load(N, n_clumps=4, clump_frac=0.02, seed=n_grid)
+    d = [torch.from_numpy(x).cuda() for x in (p.pos, p.mass, p.eps)]
+    tab = sc.CorrectionTable(n_grid, n_grid, 5.0, 64)
+    every = torch.arange(N, dtype=torch.int64, device="cuda")
+    t = torch.from_numpy(np.random.default_rng(n).integers(0, N, n)).cuda()
+    for pot in (False, True):
+        acc, q = sc.steps_cyl_forces_table(*d, p.L, tab, order=2, targets=every, potential=pot)
+        a, b = sc.steps_cyl_forces_table(*d, p.L, tab, order=2, targets=t, potential=pot)
+        torch.cuda.synchronize()
+        assert torch.equal(a, acc[:, t])
+        assert not pot or torch.equal(b, q[t])
+    tab.close()
