@@ -54,8 +54,8 @@ PEAK_FP32_UNPACKED = 78.6e12     # 256 CU x 4 SIMD x 16 lanes x 2 FLOP x 2.4 GHz
 # what the counter reads for a 256 MiB copy
 # (profiles/forces_pairwise_N1M_nimg8_counters.md).  Valid only for the
 # kernel sources they were measured on (hash below); None until measured.
-TRAFFIC_EXACT_N1M = {"bytes": 1.2608e12, "fetch_scale": 1.99974, "write_scale": 1.0,
-                     "sources_sha256_16": "557f82eb946cd22b"}
+TRAFFIC_EXACT_N1M = {"bytes": 1.2609e12, "fetch_scale": 1.99974, "write_scale": 1.0,
+                     "sources_sha256_16": "67e919ffe422f8b9"}
 TRAFFIC_SOURCES = ["forces_pairwise.hip", "pair_schedule.h", "pair_fp32.h", "pair_f64.h", "target_order.hip"]
 
 
@@ -219,7 +219,7 @@ def exact_leg(args, dev):
             "time_base": "whole steps_cyl_forces call",
             "pair_launches_per_call": pair_launches(N),
             "frac_of_unpacked_fp32_peak": round(achieved / PEAK_FP32_UNPACKED, 4),
-            "kernel": f"forces_pairwise_kernel<{n_img},true,0,false> (tournament meetings, one-wave workgroups)",
+            "kernel": f"forces_pairwise_kernel<{n_img},true,0,false,false> (tournament meetings, one-wave workgroups)",
         },
         # the metric's N^2 count (F_pair for every ordered pair, including the
         # half that symmetry skips): a dense-equivalent figure
@@ -228,7 +228,7 @@ def exact_leg(args, dev):
         "one_sided": {
             "ms": round(ms1, 3), "runs": len(ms1_all), "G_pairs_per_s": round(pairs / (ms1 * 1e-3) / 1e9, 3),
             "frac_fp32_vector_peak": round(flops_per_pair(n_img) * pairs / (ms1 * 1e-3) / PEAK_FP32_VECTOR, 4),
-            "kernel": "forces_exact_kernel<8,true,true> (steps_cyl_forces_ex, all targets)",
+            "kernel": "forces_exact_kernel<8,true,true,false> (steps_cyl_forces_ex, all targets)",
         },
     }
 

@@ -50,9 +50,10 @@ namespace {
 
 constexpr int kPart = 64;  // particles per part, one per lane
 constexpr int kSplit = 4;  // most waves of a split tile
-// The one-launch form up to this many particles.  Per call (us, |n| <= 8 with
-// the potential), one launch against tiles: N = 500 13 and 50, 1000 13 and 38,
-// 2000 29 and 40, 2500 47 and 42.
+// The one-launch form, without workspace, up to this many particles.  Per call (us,
+// |n| <= 8 with the potential), one launch against tiles: N = 500 13 and 36, 1000 13
+// and 36, 2000 29 and 36, 2300 43 and 36, 2500 47 and 37 (38 to 42 before tiles were
+// split over four waves; calls up to here need no workspace, so the line stays).
 constexpr int kSmallMax = 2304;
 // Waves per SIMD.  Measured per call at N = 2^20, |n| <= 8 with the potential
 // (ms) with one launch per round: 1 particle per lane at 4, 5, 6 and 8 waves
@@ -545,7 +546,10 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64, waves_per_simd(TORDER)) v
 // out of three, a permute for each fourth step), so that every lane meets every
 // source.  us per call: N = 10000 393 -> 269, 20011 (with the potential) 1272 ->
 // 1024, 40000 4342 -> 3332, 100000 23800 -> 19100; what bounds it then is bank
-// conflicts of the gathers and the VALU (124 instructions) about alike.
+// conflicts of the gathers and the VALU (124 instructions) about alike, and with the
+// potential 128 registers: 68 bytes of scratch a lane with a complete table, 80 with
+// a band, four of whose loads and stores fall in each step of the far loop (20011
+// particles, complete: 962 us).
 constexpr int kLdsWaves = 16;
 constexpr int kLdsNodes = 20480;  // 160 KiB
 constexpr int kLdsGroups = 256;   // one per CU
@@ -558,7 +562,7 @@ inline bool lds_table(const TableView &tv, int64_t N) {
 }
 
 // The mass moves in FP32, which leaves the form with the potential a register more
-// (32 x 32 nodes, N = 6000: 154 us, with an FP64 mass 155 to 185 by what else spills).
+// (32 x 32 nodes, N = 6000: 150 us, with an FP64 mass 155 to 185 by what else spills).
 struct MovingSource {
     double x, y, z;
     double r[4];  // reactions

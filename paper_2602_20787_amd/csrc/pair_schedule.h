@@ -22,7 +22,8 @@
 //
 // As many rounds share a launch as the slots' memory allows, up to one launch of
 // one group of all parts (flat: S = P, every slot written once); there each tile
-// may be split over Q workgroups of 1/Q of its sources.
+// may be split over Q workgroups of 1/Q of its sources (the learned path; the others
+// split it over the waves of a workgroup).
 #pragma once
 
 #include <algorithm>
@@ -43,9 +44,9 @@ constexpr size_t kSetBytes = 32;  // per particle and slot
 
 // Below this many particles the parts are runs of the particles' own order:
 // what the order saves in near tiles is less than the 60 us that sorting costs
-// (us per call without and with it: N = 8000 167 and 200, 12000 339 and 352;
-// with a CIC table 148 and 171, 283 and 284; learned 1967 and 1995, 4413 and
-// 4402).
+// (us per call without and with it: N = 8000 160 and 191, 10000 247 and 266, 12000
+// 331 and 349, 14000 432 and 436; with a CIC table 130 and 152, 205 and 207, 273 and
+// 262; learned 1879 and 1910, 2932 and 2956, 4226 and 4237).
 constexpr int64_t kSortMin = 10240;
 
 struct Schedule {

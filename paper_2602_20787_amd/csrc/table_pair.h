@@ -87,7 +87,11 @@ __device__ __forceinline__ void band_wave(float delta, float r, int n_far, float
 
 // rho and 1/rho of a pair (both 0 on the axis) from one reciprocal square root:
 // the correctly rounded square root and the reciprocal of it took 18 VALU
-// instructions more, of the 107 of a CIC pair in the pairwise kernel.
+// instructions more, of the 107 of a CIC pair in the pairwise kernel.  rho is within
+// 1.5 ulp, 1/rho within one where the reciprocal of the root was within 1.5.  With
+// rho correctly rounded (a Newton step, 1.4 % longer) the accelerations' rms error
+// against 64 bits is the same within 3 % and larger in 21 of 24 calls (272 to 24893
+// particles, both orders and kinds of table, 3.3e-8 to 9.4e-8).
 __device__ __forceinline__ void rho_of(float rho2, float &rho, float &rinv) {
     rinv = rho2 >= 1.17549435e-38f ? __builtin_amdgcn_rsqf(rho2) : 0.f;
     rho = rho2 * rinv;
